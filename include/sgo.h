@@ -295,17 +295,17 @@ int sgo_subspace_solve(int device, int n, int mode, const double* S, const doubl
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops that forbid hipMalloc): the subspace step of
  * sgo_subspace_solve on device arrays, with its workspace (descriptor,
- * status block, working copies of S and H and one more n x n matrix) in a
- * fixed array of the library on each GPU (about 1.5 MiB, held until the
- * process ends).  S, H [n*n] (H ignored for mode 1) are device inputs, left
+ * status block, working copies of S and H, one more n x n matrix and the
+ * Jacobi rotations of a solve) in a fixed array of the library on each GPU
+ * (about 14 MiB, held until the process ends).  S, H [n*n] (H ignored for mode 1) are device inputs, left
  * unchanged; M [n*n] and eps [n] (mode 3) are device outputs in the layout
  * of sgo_subspace_solve; all are owned by the caller.  Work is enqueued on
  * hip_stream (NULL: the null stream) of `device`.  status (device int,
  * nullable): when given, the call only enqueues, and *status receives 0 or
  * SGO_ENUMERIC (S not positive definite) in stream order; when NULL, the
  * call waits for the stream and returns SGO_ENUMERIC itself.  n must be
- * 1..256 (SGO_EINVAL otherwise: the workspace holds no more); the solve runs
- * in one workgroup at every size.  Calls no allocator.  All calls on one GPU
+ * 1..256 (SGO_EINVAL otherwise: the workspace holds no more).  Calls no
+ * allocator.  All calls on one GPU
  * share its workspace, which keeps the last call's contents: calls that
  * overlap on one GPU (other streams, other host threads) race. */
 int sgo_subspace_solve_noalloc(int device, int n, int mode, const double* S, const double* H,
@@ -313,8 +313,8 @@ int sgo_subspace_solve_noalloc(int device, int n, int mode, const double* S, con
 
 /* Launch-schedule tuning (process-wide; read when a solve starts).  Keys:
  * "SGO_GRAM_KC" (K range of one split-K Gram block, multiple of 32),
- * "SGO_SUB_THREADS" (threads of the subspace solver's workgroup, 64..512; the
- * Jacobi rounds of 65 to 128 bands always run on 1024 threads),
+ * "SGO_SUB_THREADS" (threads of the subspace solver's workgroup above 128
+ * bands, 64..512; the smaller problems' kernels have their own),
  * "SGO_SP_CHUNK" (stick pairs per block of the LDS z transforms, used by
  * FP64 and by lines longer than 64; the FP32 register z passes take 16),
  * "SGO_DENS_CHUNKS" (band-pair chunks of the density planes),
@@ -337,7 +337,7 @@ int sgo_subspace_solve_noalloc(int device, int n, int mode, const double* S, con
  * of the PCG preconditioner, thousandths of max|tau|, default 100),
  * "SGO_JAC_GRID" (band count from which the subspace products and Jacobi
  * rounds run over the whole GPU instead of one workgroup per candidate,
- * default 160), "SGO_PLANE_GROUP" (consecutive z-planes per four-wavefront
+ * default 199), "SGO_PLANE_GROUP" (consecutive z-planes per four-wavefront
  * workgroup of the FP32 register H psi plane kernel, 2..8; 1 = one plane per
  * wavefront; by default the size that keeps the most lanes busy while two
  * groups still share a compute unit's LDS, or 1 where no group saves 10%),

@@ -535,6 +535,7 @@ class Engine {
     const size_t np16 = (size_t)(c.nproj + 15) / 16 * 16;
     const int ntile = (std::max(c.nb, c.nproj) + 63) / 64;
     c.red_doubles = std::max((size_t)kRedSlots, (size_t)2 * ntile * ntile * 32 * 4096);
+    if (c.nb <= kJacWideMax) c.red_doubles = std::max(c.red_doubles, jac_log_doubles(c.nb, kJacMaxSweeps));
     c.dens_chunks = g.dens_chunks;
     struct Item {
       void** p;
@@ -2350,7 +2351,7 @@ int sgo_subspace_solve(int device, int n, int mode, const double* S, const doubl
     HIPCHK(hipMalloc(&dclk, 8 * sizeof(long long)));
     double* dred;
     int *djac, *hjac;
-    HIPCHK(hipMalloc(&dred, 2048 * 8));
+    HIPCHK(hipMalloc(&dred, (n <= sgo::kJacWideMax ? sgo::jac_log_doubles(n, sgo::kJacMaxSweeps) : 2048) * 8));
     HIPCHK(hipMalloc(&djac, sizeof(int)));
     HIPCHK(hipHostMalloc((void**)&hjac, sizeof(int), hipHostMallocDefault));
     HIPCHK(hipMemset(dscal, 0, sgo::S_COUNT * 8));

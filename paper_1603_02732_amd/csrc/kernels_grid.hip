@@ -6,8 +6,7 @@
 // and the FP64 subspace solver (Cholesky orthonormalisation + Jacobi
 // diagonalisation: the orthogonalisation and subspace-diagonalisation steps
 // of Algorithm 1).
-#include "device.hpp"
-#include "launch.hpp"
+#include "jacobi.hpp"
 
 #include <algorithm>
 #include <cstring>
@@ -910,17 +909,6 @@ __device__ __forceinline__ void jacobi_pair(int r, int k, int n2, int* p, int* q
 // Rotation (c, s) that zeroes A[p][q] of the symmetric matrix A:
 // theta = (a_qq - a_pp) / (2 a_pq), t = sgn(theta) / (|theta| + sqrt(theta^2 + 1)).
 // Entries at rounding level (|a_pq| <= 1e-17 sqrt|a_pp a_qq|) are left alone.
-// 1/x and 1/sqrt(x) from the hardware approximations refined by one Newton
-// step (about 1 ulp; the rotation only has to be orthogonal to rounding, and
-// c^2 + s^2 = 1 holds by construction below).
-__device__ __forceinline__ double rcp_nr(double x) {
-  const double r = __builtin_amdgcn_rcp(x);
-  return fma(r, fma(-x, r, 1.0), r);
-}
-__device__ __forceinline__ double rsq_nr(double x) {
-  const double r = __builtin_amdgcn_rsq(x);
-  return r * fma(-0.5 * x * r, r, 1.5);
-}
 __device__ __forceinline__ void jacobi_rot(const double* A, int n, int ld, int p, int q, double* c,
                                            double* s) {
   *c = 1.0;
@@ -942,135 +930,6 @@ __device__ __forceinline__ void jacobi_rot(const double* A, int n, int ld, int p
   const double cc = rsq_nr(fma(t, t, 1.0));
   *c = cc;
   *s = t * cc;
-}
-
-// One work item of a fast Jacobi round: block (P, Q) of H' and columns 2Q,
-// 2Q + 1 of V^T's rows of pair P, loaded into registers, then rotated and
-// stored.  Every lane of the wavefront calls load and update (the pair
-// indices and rotations come from other lanes' registers).
-struct JacItem {
-  int P, Q, p1, p2, q1, q2;
-  bool ok;
-  double a11, a12, a21, a22, vp0, vq0, vp1, vq1;
-  __device__ __forceinline__ void load(const double* H, int ldh, const double* Vt, int ldv, int n,
-                                       int npair, unsigned inv, int nitem, int t, int pk, int qk) {
-    ok = t < nitem;
-    const int tc = ok ? t : 0;
-    P = (int)(((unsigned)tc * inv) >> 20);
-    Q = tc - P * npair;
-    p1 = __shfl(pk, P);
-    p2 = __shfl(qk, P);
-    q1 = __shfl(pk, Q);
-    q2 = __shfl(qk, Q);
-    const bool p2v = p2 < n, q2v = q2 < n;
-    const int p2c = p2v ? p2 : p1, q2c = q2v ? q2 : q1;
-    a11 = H[p1 * ldh + q1];
-    a12 = q2v ? H[p1 * ldh + q2c] : 0.0;
-    a21 = p2v ? H[p2c * ldh + q1] : 0.0;
-    a22 = (p2v && q2v) ? H[p2c * ldh + q2c] : 0.0;
-    const int i0 = min(2 * Q, n - 1), i1 = min(2 * Q + 1, n - 1);
-    vp0 = Vt[p1 * ldv + i0];
-    vq0 = Vt[p2c * ldv + i0];
-    vp1 = Vt[p1 * ldv + i1];
-    vq1 = Vt[p2c * ldv + i1];
-  }
-  __device__ __forceinline__ void update(double* H, int ldh, double* Vt, int ldv, int n, double ck,
-                                         double sk) const {
-    const double cP = __shfl(ck, P), sP = __shfl(sk, P);
-    const double cQ = __shfl(ck, Q), sQ = __shfl(sk, Q);
-    if (!ok) return;
-    const bool p2v = p2 < n, q2v = q2 < n;
-    const double b11 = fma(cP, a11, -(sP * a21)), b21 = fma(sP, a11, cP * a21);
-    const double b12 = fma(cP, a12, -(sP * a22)), b22 = fma(sP, a12, cP * a22);
-    H[p1 * ldh + q1] = fma(cQ, b11, -(sQ * b12));
-    if (q2v) H[p1 * ldh + q2] = fma(sQ, b11, cQ * b12);
-    if (p2v) H[p2 * ldh + q1] = fma(cQ, b21, -(sQ * b22));
-    if (p2v && q2v) H[p2 * ldh + q2] = fma(sQ, b21, cQ * b22);
-    if (p2v && sP != 0.0) {
-      const int i = 2 * Q;
-      if (i < n) {
-        Vt[p1 * ldv + i] = fma(cP, vp0, -(sP * vq0));
-        Vt[p2 * ldv + i] = fma(sP, vp0, cP * vq0);
-      }
-      if (i + 1 < n) {
-        Vt[p1 * ldv + i + 1] = fma(cP, vp1, -(sP * vq1));
-        Vt[p2 * ldv + i + 1] = fma(sP, vp1, cP * vq1);
-      }
-    }
-  }
-};
-// Cyclic Jacobi sweeps, in place, for up to 128 indices (64 pairs).  A round
-// is a chain of dependent steps (pair indices, loads, rotation, update), and
-// one wavefront issues a vector instruction every few cycles, so the round's
-// time is that chain's instruction count and memory latency, not its FP64
-// work:
-//  - a work item is the 2x2 block (row pair P, column pair Q) of H' together
-//    with columns 2Q and 2Q + 1 of V^T's rows of pair P: items own disjoint
-//    entries, so they update in place; wavefronts without items skip the
-//    round;
-//  - each wavefront computes the round's rotations itself (lane k: pair
-//    k mod npair) and the items read them, and the pair indices, from those
-//    lanes' registers; the first items' loads are issued beside the
-//    rotations, and one barrier then separates every read of the round's
-//    rotation inputs from the first write.
-// The updates are written as fma(x, y, -/+ z w) for x y -/+ z w, the rounding
-// the compiler gives the two-barrier rounds in k_subspace (used above 128
-// bands), so both give the same bits.
-// Stops when the off-diagonal norm is below 1e-13 of the diagonal norm;
-// returns the sweeps done.
-constexpr int kJacFastPairs = 64;
-// nthr_norm: the thread stride of the off-diagonal norm's partial sums (the
-// block's thread count, or a smaller one whose sums another launch shape
-// must reproduce bit for bit)
-__device__ int jacobi_sweeps_fast(double* H, int ldh, double* Vt, int ldv, int n, int max_sweeps,
-                                  double* sh, int tid, int nthr, int nthr_norm) {
-  const int n2 = n + (n & 1), npair = n2 / 2, m = n2 - 1;
-  const int lane = tid & 63;
-  // item t = P npair + Q; t / npair as a multiply-shift (exact for t < 4096,
-  // npair <= 64)
-  const int nitem = npair * npair;
-  const unsigned inv = (1u << 20) / (unsigned)npair + 1u;
-  const int kl = lane % npair;
-  const bool has_items = (tid & ~63) < nitem;
-  int nsweep = 0;
-  for (int sweep = 0; sweep < max_sweeps; ++sweep) {
-    // the norms in the two-barrier form's order (the same sweep counts)
-    double v[2] = {0.0, 0.0};
-    if (tid < nthr_norm)
-      for (int e = tid; e < n * n; e += nthr_norm) {
-        const int i = e / n, j = e - i * n;
-        const double a = H[i * ldh + j];
-        if (i == j) v[1] += a * a;
-        else v[0] += a * a;
-      }
-    block_sum<2>(v, sh);
-    if (!(v[0] > 1e-26 * v[1] + 1e-300)) break;
-    ++nsweep;
-    for (int r = 0; r < m; ++r) {
-      int pk = 0, qk = 0;
-      double ck = 1.0, sk = 0.0;
-      JacItem it;
-      if (has_items) {
-        // lane k: the rotation of pair k mod npair (the lanes above npair
-        // repeat it: branch-free, so the register reads below see every lane)
-        jacobi_pair(r, kl, n2, &pk, &qk);
-        jacobi_rot(H, n, ldh, pk, qk, &ck, &sk);
-        it.load(H, ldh, Vt, ldv, n, npair, inv, nitem, tid, pk, qk);  // the first pass's item
-      }
-      __syncthreads();  // every rotation input is read before any block is written
-      if (has_items) {
-        for (int base = 0; base < nitem; base += nthr) {
-          if (base + (tid & ~63) >= nitem) break;  // uniform per wavefront
-          // later passes load after the barrier: their entries belong to
-          // their own items only
-          if (base > 0) it.load(H, ldh, Vt, ldv, n, npair, inv, nitem, base + tid, pk, qk);
-          it.update(H, ldh, Vt, ldv, n, ck, sk);
-        }
-      }
-      __syncthreads();
-    }
-  }
-  return nsweep;
 }
 
 // Blocked Cholesky S = L L^T (lower, over A in place) and W = L^-1 (into Wm)
@@ -1194,53 +1053,24 @@ __device__ __forceinline__ bool chol_inv_blocked(double* __restrict__ A, double*
   return true;
 }
 
-// phase 0: the whole solve; 1: Cholesky and W = L^-1 only (the congruence,
-// and M = W^T V then run over the whole GPU: k_sub_*; the Jacobi rounds too
-// from g.jac_grid bands, k_jac_*); 3: the Jacobi rounds of the H' that
-// k_sub_wh/k_sub_twt formed, in the workgroup (H' in LDS up to 128 bands);
-// 2: eigenvalue order and the sorted M, eps from the converged H' and the
-// product W^T V already in S.  Phases 1-3 keep W, V and the products in
-// global memory.
-// USE_LDS (see below) is a template parameter: the matrix pointers of each
-// form then come from one address space only, so the LDS-resident ones are
-// accessed with LDS instructions rather than flat ones
-template <int USE_LDS>
+// In global memory (above kJacWideMax bands, and the Cholesky above 128; the
+// smaller problems' kernels are in kernels_sub.hip).  phase 0: the whole solve;
+// 1: Cholesky and W = L^-1 only (the congruence, the Jacobi rounds from
+// g.jac_grid bands and M = W^T V then run over the whole GPU: k_sub_*, k_jac_*);
+// 3: the Jacobi rounds of the H' that k_sub_wh/k_sub_twt formed; 2: eigenvalue
+// order and the sorted M, eps from the converged H' and the product W^T V
+// already in S.
 __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict__ cds, int mode,
                                                      int max_sweeps, int phase) {
-  constexpr int use_lds = USE_LDS;
   const CandDesc& cd = cds[blockIdx.x];
   if (!cd.active) return;
   const int n = cd.nb;
   const int tid = threadIdx.x, nthr = blockDim.x;
-  // use_lds 1: the four matrices in LDS; 0: in global memory; 2: in global
-  // memory except H', which the Jacobi rounds keep in LDS (up to 128 bands)
-  const bool all_lds = use_lds == 1;
-  // row stride of the four matrices: n + 1 in LDS (rows and columns of
-  // FP64 entries then fall in different banks), n in global memory
-  const int ld = all_lds ? n + 1 : n;
+  const int ld = n;
   extern __shared__ __align__(16) char smem[];
-  double *P0, *P1, *P2, *P3;  // L, H / H', W = L^-1, scratch / V
-  if (all_lds) {
-    P0 = (double*)smem;
-    P1 = P0 + n * ld;
-    P2 = P1 + n * ld;
-    P3 = P2 + n * ld;
-    for (int e = tid; e < n * n; e += nthr) {
-      const int i = e / n, j = e - i * n;
-      P0[i * ld + j] = cd.S[e];
-      P1[i * ld + j] = cd.Hs[e];
-    }
-  } else {
-    P0 = cd.S;
-    P1 = cd.Hs;
-    P2 = cd.C;
-    P3 = cd.M;
-  }
-  // H' from the congruence on (the input H stays in P1)
-  const bool h_lds = use_lds == 2;
-  double* H1 = h_lds ? (double*)smem : P1;
-  const int ldh = h_lds ? n + 1 : ld;
-  __shared__ int fail;
+  double *P0 = cd.S, *P1 = cd.Hs, *P2 = cd.C, *P3 = cd.M;  // L, H / H', W = L^-1, scratch / V
+  double* H1 = P1;
+  const int ldh = ld;
   __shared__ double sh[16 * 2];
   __shared__ int rank[640];
   __shared__ double rc[320], rs[320];
@@ -1259,78 +1089,15 @@ __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict_
     // Jacobi of the H' that the products over the GPU formed (in Hs; V^T = I
     // in M), unless this call's Cholesky failed
     if (cd.scal[S_ERR] == 2.0) return;
-    if (h_lds)
-      for (int e = tid; e < n * n; e += nthr) {
-        const int i = e / n, j = e - i * n;
-        H1[i * ldh + j] = cd.Hs[e];
-      }
-    __syncthreads();
   }
   if (phase != 2) {
    if (phase != 3) {
-    if (tid == 0) fail = 0;
     if (clk && tid == 0) clk[0] = clock64();
     __syncthreads();
-    if (!all_lds) {
-      // global-memory solver: blocked, panels in the dynamic LDS
-      if (!chol_inv_blocked(P0, P2, n, ld, (double*)smem, tid, nthr)) {
-        if (tid == 0) cd.scal[S_ERR] = 2.0;
-        for (int e = tid; e < n * n; e += nthr) cd.M[e] = (e / n == e % n) ? 1.0 : 0.0;
-        return;
-      }
-    } else {
-      // Cholesky S = L L^T (lower, in place, right-looking; two barriers per
-      // column).  The pivots are kept aside in P3 and written to the diagonal at
-      // the end, so no thread overwrites a pivot another thread still reads.
-      for (int k = 0; k < n; ++k) {
-        __syncthreads();  // trailing update of the previous column is complete
-        const double d = P0[k * ld + k];
-        if (!(d > 0.0)) {
-          if (tid == 0) fail = 1;
-          break;
-        }
-        const double piv = sqrt(d);
-        const double inv = 1.0 / piv;
-        if (tid == 0) P3[k] = piv;
-        for (int i = k + 1 + tid; i < n; i += nthr) P0[i * ld + k] *= inv;
-        __syncthreads();
-        const int m = n - k - 1;
-        for (int t = tid; t < m * m; t += nthr) {
-          const int i = k + 1 + t / m, j = k + 1 + t % m;
-          if (j <= i) P0[i * ld + j] -= P0[i * ld + k] * P0[j * ld + k];
-        }
-      }
-      __syncthreads();
-      if (!fail)
-        for (int k = tid; k < n; k += nthr) P0[k * ld + k] = P3[k];
-      __syncthreads();
-      if (fail) {
-        if (tid == 0) cd.scal[S_ERR] = 2.0;
-        for (int e = tid; e < n * n; e += nthr) cd.M[e] = (e / n == e % n) ? 1.0 : 0.0;
-        return;
-      }
-      // W = L^-1 by elimination on [L | I]: at step j, rows i > j subtract
-      // L[i][j] * row j (final since step j-1); row j+1 is complete after this
-      // step and is divided by its pivot.  One barrier per step.
-      for (int e = tid; e < n * n; e += nthr) {
-        const int i = e / n, j = e % n;
-        P2[i * ld + j] = i == j ? (i == 0 ? 1.0 / P0[0] : 1.0) : 0.0;
-      }
-      __syncthreads();
-      for (int j = 0; j + 1 < n; ++j) {
-        const int rows = n - 1 - j, cols = j + 1;
-        for (int t = tid; t < rows * cols + 1; t += nthr) {
-          if (t == rows * cols) {
-            P2[(j + 1) * ld + j + 1] = 1.0 / P0[(j + 1) * ld + j + 1];
-            continue;
-          }
-          const int i = j + 1 + t / cols, c = t % cols;
-          double w = P2[i * ld + c] - P0[i * ld + j] * P2[j * ld + c];
-          if (i == j + 1) w /= P0[i * ld + i];
-          P2[i * ld + c] = w;
-        }
-        __syncthreads();
-      }
+    if (!chol_inv_blocked(P0, P2, n, ld, (double*)smem, tid, nthr)) {
+      if (tid == 0) cd.scal[S_ERR] = 2.0;
+      for (int e = tid; e < n * n; e += nthr) cd.M[e] = (e / n == e % n) ? 1.0 : 0.0;
+      return;
     }
     if (clk && tid == 0) clk[1] = clock64();
     if (mode == 1) {
@@ -1339,42 +1106,20 @@ __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict_
     }
     if (phase == 1) return;  // W is ready; the products run over the GPU
     // H' = W H W^T (symmetrised)
-    if (all_lds) {
-      // lane j: column j (32 or 64 columns per wavefront), rows over the
-      // wavefronts; one operand of each product is an LDS broadcast
-      const int lw = n <= 32 ? 32 : 64, j = tid & (lw - 1);
-      const int r0 = (tid >> 6) * (64 / lw) + ((tid & 63) >= lw ? 1 : 0);
-      const int rstep = (nthr >> 6) * (64 / lw);
-      if (j < n)
-        for (int i = r0; i < n; i += rstep) {
-          double s = 0.0;
-          for (int k = 0; k <= i; ++k) s = fma(P2[i * ld + k], P1[k * ld + j], s);
-          P3[i * ld + j] = s;
-        }
-      __syncthreads();
-      if (j < n)
-        for (int i = r0; i < n; i += rstep) {
-          double s = 0.0;
-          for (int k = 0; k <= j; ++k) s = fma(P3[i * ld + k], P2[j * ld + k], s);
-          H1[i * ldh + j] = s;
-        }
-      __syncthreads();
-    } else {
-      for (int e = tid; e < n * n; e += nthr) {
-        const int i = e / n, j = e % n;
-        double s = 0.0;
-        for (int k = 0; k <= i; ++k) s = fma(P2[i * ld + k], P1[k * ld + j], s);
-        P3[i * ld + j] = s;
-      }
-      __syncthreads();
-      for (int e = tid; e < n * n; e += nthr) {
-        const int i = e / n, j = e % n;
-        double s = 0.0;
-        for (int k = 0; k <= j; ++k) s = fma(P3[i * ld + k], P2[j * ld + k], s);
-        H1[i * ldh + j] = s;
-      }
-      __syncthreads();
+    for (int e = tid; e < n * n; e += nthr) {
+      const int i = e / n, j = e % n;
+      double s = 0.0;
+      for (int k = 0; k <= i; ++k) s = fma(P2[i * ld + k], P1[k * ld + j], s);
+      P3[i * ld + j] = s;
     }
+    __syncthreads();
+    for (int e = tid; e < n * n; e += nthr) {
+      const int i = e / n, j = e % n;
+      double s = 0.0;
+      for (int k = 0; k <= j; ++k) s = fma(P3[i * ld + k], P2[j * ld + k], s);
+      H1[i * ldh + j] = s;
+    }
+    __syncthreads();
     for (int e = tid; e < n * n; e += nthr) {
       const int i = e / n, j = e % n;
       if (i < j) {
@@ -1396,9 +1141,7 @@ __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict_
     const int npair = n2 / 2;
     if (clk && tid == 0) clk[2] = clock64();
     int nsweep = 0;
-    const bool fast = npair <= kJacFastPairs;
-    if (fast) nsweep = jacobi_sweeps_fast(H1, ldh, P3, ld, n, max_sweeps, sh, tid, nthr, nthr);
-    for (int sweep = 0; sweep < (fast ? 0 : max_sweeps); ++sweep) {
+    for (int sweep = 0; sweep < max_sweeps; ++sweep) {
       double v[2] = {0.0, 0.0};
       for (int e = tid; e < n * n; e += nthr) {
         const int i = e / n, j = e % n;
@@ -1468,15 +1211,7 @@ __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict_
       clk[3] = clock64();
       clk[5] = nsweep;
     }
-    if (phase == 3) {
-      // H' back for the sort (phase 2); M = W^T V runs over the GPU
-      if (h_lds)
-        for (int e = tid; e < n * n; e += nthr) {
-          const int i = e / n, j = e - i * n;
-          cd.Hs[e] = H1[i * ldh + j];
-        }
-      return;
-    }
+    if (phase == 3) return;  // M = W^T V and the sort (phase 2) follow
   }
   // ranks of the eigenvalues (ascending, ties by index)
   for (int i = tid; i < n; i += nthr) {
@@ -1490,18 +1225,7 @@ __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict_
   }
   // M = W^T V into P0 (L is no longer needed); P3 holds V^T.  In phase 2
   // the product has already been formed over the GPU (k_sub_compose).
-  if (phase != 2 && all_lds) {
-    // lane i: column i of M (V^T row i), rows j over the wavefronts
-    const int lw = n <= 32 ? 32 : 64, i = tid & (lw - 1);
-    const int r0 = (tid >> 6) * (64 / lw) + ((tid & 63) >= lw ? 1 : 0);
-    const int rstep = (nthr >> 6) * (64 / lw);
-    if (i < n)
-      for (int j = r0; j < n; j += rstep) {
-        double s = 0.0;
-        for (int k = j; k < n; ++k) s = fma(P2[k * ld + j], P3[i * ld + k], s);
-        P0[j * ld + i] = s;
-      }
-  } else if (phase != 2) {
+  if (phase != 2) {
     for (int e = tid; e < n * n; e += nthr) {
       const int j = e / n, i = e % n;
       double s = 0.0;
@@ -1516,34 +1240,6 @@ __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict_
   }
   for (int i = tid; i < n; i += nthr) cd.eps[rank[i]] = H1[i * ldh + i];
   if (clk && tid == 0) clk[4] = clock64();
-}
-
-// The Jacobi rounds of the mid path (65-128 bands) on their own: H' (formed
-// over the GPU, in Hs) in LDS, V^T (= I, in M) rotated in global memory.  At
-// 112 bands a sweep has 111 rounds of 3,136 items each; 1024 threads take a
-// round's items in four passes where k_subspace's 512 (bounded by the
-// registers of its Cholesky) need seven.  The off-diagonal norm keeps the partial sums
-// of `nthr_norm` threads, so the results are those of k_subspace's phase 3
-// bit for bit.
-constexpr int kSubJacThreads = 1024;
-__global__ void __launch_bounds__(kSubJacThreads) k_sub_jacobi(const CandDesc* __restrict__ cds,
-                                                              int max_sweeps, int nthr_norm) {
-  const CandDesc& cd = cds[blockIdx.x];
-  if (!cd.active || cd.scal[S_ERR] == 2.0) return;  // inactive, or this call's Cholesky failed
-  const int n = cd.nb, tid = threadIdx.x, nthr = blockDim.x, ldh = n + 1;
-  extern __shared__ __align__(16) char smem[];
-  double* H = (double*)smem;
-  __shared__ double sh[16 * 2];
-  for (int e = tid; e < n * n; e += nthr) {
-    const int i = e / n, j = e - i * n;
-    H[i * ldh + j] = cd.Hs[e];
-  }
-  __syncthreads();
-  jacobi_sweeps_fast(H, ldh, cd.M, n, n, max_sweeps, sh, tid, nthr, min(nthr_norm, nthr));
-  for (int e = tid; e < n * n; e += nthr) {
-    const int i = e / n, j = e - i * n;
-    cd.Hs[e] = H[i * ldh + j];
-  }
 }
 
 // ------------------------------------- subspace products over the GPU
@@ -1601,7 +1297,6 @@ __global__ void __launch_bounds__(kNT) k_sub_compose(const CandDesc* __restrict_
 // launch over all candidates (k_jac_round).  The per-candidate convergence
 // flag lives at the start of the reduction scratch (free while the subspace
 // problem is solved).
-constexpr int kJacDone = 0;  // 1.0 once the candidate's H' is diagonal
 
 // Off-diagonal vs diagonal norm of H' (one block per candidate): sets the
 // candidate's flag and done_all[c] (1 for inactive candidates).
@@ -1898,33 +1593,20 @@ void launch_occupations(const LaunchCtx& L) {
   check_launch("k_occupations");
   prof_after("k_occupations", L.stream);
 }
-// Where the subspace solver keeps its matrices: all four in LDS up to 64
-// bands, H' alone in LDS up to 128 (the Jacobi rounds then touch global
-// memory only for V's column pairs), else all in global memory; and the
-// dynamic LDS that form needs (the blocked Cholesky's panels share it).
-// LDS form of the subspace solver by band count: 1 up to 64 (all four
-// matrices), 2 up to 128 (H' only), else 0
-static int sub_lds_form(int n) { return n <= 64 ? 1 : (n <= 128 ? 2 : 0); }
-static size_t sub_lds_bytes(int n, int form) {
-  if (form == 1) return sizeof(double) * 4 * (size_t)n * (n + 1);
-  const size_t chol = (size_t)chol_inv_lds_doubles(n);
-  const size_t h = form == 2 ? (size_t)n * (n + 1) : 0;
-  return sizeof(double) * std::max(chol, h);
-}
-
-static void launch_k_subspace(int form, dim3 grid, dim3 block, size_t lds, hipStream_t st,
-                              const CandDesc* desc, int mode, int max_sweeps, int phase) {
-  switch (form) {
-    case 1:
-      hipLaunchKernelGGL(k_subspace<1>, grid, block, lds, st, desc, mode, max_sweeps, phase);
-      break;
-    case 2:
-      hipLaunchKernelGGL(k_subspace<2>, grid, block, lds, st, desc, mode, max_sweeps, phase);
-      break;
-    default:
-      hipLaunchKernelGGL(k_subspace<0>, grid, block, lds, st, desc, mode, max_sweeps, phase);
-  }
+static void launch_k_subspace(int ncand, int n, int nthr, hipStream_t st, const CandDesc* desc, int mode,
+                              int max_sweeps, int phase) {
+  const size_t lds = phase < 2 ? sizeof(double) * (size_t)chol_inv_lds_doubles(n) : 0;
+  hipLaunchKernelGGL(k_subspace, dim3(ncand), dim3(nthr), lds, st, desc, mode, max_sweeps, phase);
   check_launch("k_subspace");
+}
+void launch_sub_chol_blocked(hipStream_t st, const CandDesc* desc, int ncand, int n, int mode, int nthr) {
+  launch_k_subspace(ncand, n, nthr, st, desc, mode, 0, 1);
+}
+void launch_sub_congruence(hipStream_t st, const CandDesc* desc, int ncand, int n) {
+  const dim3 ge((n * n + kNT - 1) / kNT, ncand);
+  hipLaunchKernelGGL(k_sub_wh, ge, dim3(kNT), 0, st, desc);
+  hipLaunchKernelGGL(k_sub_twt, ge, dim3(kNT), 0, st, desc);
+  check_launch("k_sub_twt");
 }
 
 // One Jacobi sweep over the GPU (n2 - 1 rounds of two launches each),
@@ -1983,67 +1665,49 @@ static void jacobi_sweep(const LaunchCtx& L, int n, int n2, dim3 ga) {
 }
 
 void launch_subspace(const LaunchCtx& L, int mode, int max_sweeps) {
-  // up to 64 bands the matrices live in LDS; the thread count is a tuning
-  // parameter (a single wavefront makes barriers almost free).  From
-  // g.jac_grid bands on, the Jacobi rounds run over the whole GPU (one
-  // workgroup would take tens of microseconds per round in global memory);
-  // that needs a host read of the convergence flags per sweep, so it is not
-  // used while a graph is being captured.
-  const int n = L.g.nb_max;
-  const int use_lds = sub_lds_form(n);
-  const size_t lds = sub_lds_bytes(n, use_lds);
+  // up to kJacWideMax bands one workgroup per candidate (kernels_sub.hip);
+  // from g.jac_grid bands on, the Jacobi rounds run over the whole GPU (above
+  // kJacWideMax the triangle of H' does not fit the LDS, and one workgroup
+  // would take tens of microseconds per round in global memory); that needs a
+  // host read of the convergence flags per sweep, so it is not used while a
+  // graph is being captured.
+  const int n = L.g.nb_max, nc = L.g.ncand;
   const int nthr = L.g.sub_threads;
   prof_before("k_subspace", L.stream);
   if (mode == 3 && n >= L.g.jac_grid && L.jac_done && host_sync_allowed()) {
-    launch_k_subspace(0, dim3(L.g.ncand), dim3(nthr), sub_lds_bytes(n, 0), L.stream, L.desc, mode,
-                      max_sweeps, 1);
-    const dim3 ge((n * n + kNT - 1) / kNT, L.g.ncand);
-    hipLaunchKernelGGL(k_sub_wh, ge, dim3(kNT), 0, L.stream, L.desc);
-    hipLaunchKernelGGL(k_sub_twt, ge, dim3(kNT), 0, L.stream, L.desc);
-    check_launch("k_sub_twt");
+    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 1);
+    launch_sub_congruence(L.stream, L.desc, nc, n);
     const int n2 = n + (n & 1), npair = n2 / 2;
-    const dim3 ga((npair * npair + npair * n + kNT - 1) / kNT, L.g.ncand);
+    const dim3 ga((npair * npair + npair * n + kNT - 1) / kNT, nc);
     int done_sweeps = 0;
     for (int sweep = 0; sweep < max_sweeps; ++sweep) {
-      hipLaunchKernelGGL(k_jac_offnorm, dim3(L.g.ncand), dim3(kNT), 0, L.stream, L.desc,
-                         L.jac_done);
+      hipLaunchKernelGGL(k_jac_offnorm, dim3(nc), dim3(kNT), 0, L.stream, L.desc, L.jac_done);
       check_launch("k_jac_offnorm");
-      hip_check(hipMemcpyAsync(L.jac_done_host, L.jac_done, sizeof(int) * L.g.ncand,
-                               hipMemcpyDeviceToHost, L.stream),
+      hip_check(hipMemcpyAsync(L.jac_done_host, L.jac_done, sizeof(int) * nc, hipMemcpyDeviceToHost,
+                               L.stream),
                 "Jacobi flags");
       hip_check(hipStreamSynchronize(L.stream), "Jacobi flags");
       bool all = true;
-      for (int c = 0; c < L.g.ncand; ++c) all = all && L.jac_done_host[c] != 0;
+      for (int c = 0; c < nc; ++c) all = all && L.jac_done_host[c] != 0;
       if (all) break;
       jacobi_sweep(L, n, n2, ga);
       ++done_sweeps;
     }
-    hipLaunchKernelGGL(k_sub_compose, ge, dim3(kNT), 0, L.stream, L.desc);
+    hipLaunchKernelGGL(k_sub_compose, dim3((n * n + kNT - 1) / kNT, nc), dim3(kNT), 0, L.stream, L.desc);
     check_launch("k_sub_compose");
     // phase 2 takes the sweep count in place of the sweep limit (debug clocks)
-    launch_k_subspace(0, dim3(L.g.ncand), dim3(nthr), 0, L.stream, L.desc, mode, done_sweeps, 2);
-  } else if (mode == 3 && n > 64) {
-    // Cholesky and W in the workgroup, the congruence and M = W^T V over the
-    // whole GPU (one thread per element: these n^3 products were the slow
-    // part of the one-workgroup solve in global memory), the Jacobi rounds
-    // in the workgroup with H' in LDS up to 128 bands; no host sync, so the
-    // same path serves graph capture
-    const dim3 ge((n * n + kNT - 1) / kNT, L.g.ncand);
-    launch_k_subspace(0, dim3(L.g.ncand), dim3(nthr), sub_lds_bytes(n, 0), L.stream, L.desc, mode,
-                      max_sweeps, 1);
-    hipLaunchKernelGGL(k_sub_wh, ge, dim3(kNT), 0, L.stream, L.desc);
-    hipLaunchKernelGGL(k_sub_twt, ge, dim3(kNT), 0, L.stream, L.desc);
-    if (n <= 128) {
-      hipLaunchKernelGGL(k_sub_jacobi, dim3(L.g.ncand), dim3(kSubJacThreads),
-                         sizeof(double) * (size_t)n * (n + 1), L.stream, L.desc, max_sweeps, nthr);
-      check_launch("k_sub_jacobi");
-    } else {
-      launch_k_subspace(0, dim3(L.g.ncand), dim3(nthr), 0, L.stream, L.desc, mode, max_sweeps, 3);
-    }
-    hipLaunchKernelGGL(k_sub_compose, ge, dim3(kNT), 0, L.stream, L.desc);
-    launch_k_subspace(0, dim3(L.g.ncand), dim3(nthr), 0, L.stream, L.desc, mode, max_sweeps, 2);
+    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, done_sweeps, 2);
+  } else if (n <= kJacWideMax) {
+    launch_sub_block(L.stream, L.desc, nc, n, mode, max_sweeps, nthr);
+  } else if (mode == 3) {
+    // under graph capture: the rounds in one workgroup, in global memory
+    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 1);
+    launch_sub_congruence(L.stream, L.desc, nc, n);
+    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 3);
+    hipLaunchKernelGGL(k_sub_compose, dim3((n * n + kNT - 1) / kNT, nc), dim3(kNT), 0, L.stream, L.desc);
+    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 2);
   } else {
-    launch_k_subspace(use_lds, dim3(L.g.ncand), dim3(nthr), lds, L.stream, L.desc, mode, max_sweeps, 0);
+    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 0);
   }
   prof_after("k_subspace", L.stream);
 }
@@ -2061,7 +1725,9 @@ void launch_subspace(const LaunchCtx& L, int mode, int max_sweeps) {
 constexpr size_t kNoAllocDescBytes = 1024;
 constexpr size_t kNoAllocScalBytes = 256;
 constexpr size_t kNoAllocMatBytes = (size_t)8 * kNoAllocMaxN * kNoAllocMaxN;
-constexpr size_t kNoAllocBytes = kNoAllocDescBytes + kNoAllocScalBytes + 3 * kNoAllocMatBytes;
+constexpr size_t kNoAllocLogBytes = sizeof(double) * jac_log_doubles(kJacWideMax, kJacMaxSweeps);
+constexpr size_t kNoAllocBytes =
+    kNoAllocDescBytes + kNoAllocScalBytes + 3 * kNoAllocMatBytes + kNoAllocLogBytes;
 static_assert(sizeof(CandDesc) <= kNoAllocDescBytes, "descriptor slot too small");
 static_assert(S_COUNT * 8 <= kNoAllocScalBytes, "status slot too small");
 static __device__ __align__(256) char scratch[kNoAllocBytes];
@@ -2115,6 +1781,7 @@ int subspace_noalloc(int device, int n, int mode, const double* S, const double*
   d.S = (double*)(ws + kNoAllocDescBytes + kNoAllocScalBytes);
   d.Hs = (double*)((char*)d.S + kNoAllocMatBytes);
   d.C = (double*)((char*)d.Hs + kNoAllocMatBytes);
+  d.red_part = (double*)((char*)d.C + kNoAllocMatBytes);  // the rotation log
   d.M = M;
   d.eps = eps;
   CandDesc* dd = (CandDesc*)ws;
@@ -2123,9 +1790,8 @@ int subspace_noalloc(int device, int n, int mode, const double* S, const double*
   hipLaunchKernelGGL(k_noalloc_stage, dim3((nel + kNT - 1) / kNT), dim3(kNT), 0, stream, d, dd, S,
                      mode == 3 ? H : nullptr, nn);
   check_launch("k_noalloc_stage");
-  const int use_lds = sub_lds_form(n);
-  const size_t lds = sub_lds_bytes(n, use_lds);
-  launch_k_subspace(use_lds, dim3(1), dim3(nthreads), lds, stream, dd, mode, 40, 0);
+  if (n <= kJacWideMax) launch_sub_block(stream, dd, 1, n, mode, kJacMaxSweeps, nthreads);
+  else launch_k_subspace(1, n, nthreads, stream, dd, mode, kJacMaxSweeps, 0);
   if (status) {
     hipLaunchKernelGGL(k_noalloc_status, dim3(1), dim3(64), 0, stream, d.scal, status, fail_code);
     check_launch("k_noalloc_status");
@@ -2141,10 +1807,8 @@ void configure_wave();
 void configure_kernels() {
   allow_lds((const void*)k_grid_fft_x);
   allow_lds((const void*)k_grid_fft_yz);
-  allow_lds((const void*)k_subspace<0>);
-  allow_lds((const void*)k_subspace<1>);
-  allow_lds((const void*)k_subspace<2>);
-  allow_lds((const void*)k_sub_jacobi);
+  allow_lds((const void*)k_subspace);
+  configure_sub_kernels();
   configure_wave();
   configure_plane_kernels();
   configure_kpt_kernels();

@@ -12,8 +12,24 @@ enum MArr { M_S = 0, M_H = 1, M_M = 2, M_C = 3 };
 // Launch geometry shared by all candidates of a batch (maxima over them).
 // Default band count from which the subspace products and Jacobi rounds run
 // over the whole GPU instead of one workgroup per candidate (BatchGeom
-// jac_grid, tuning key SGO_JAC_GRID).
-constexpr int kJacGridBandsDefault = 160;
+// jac_grid, tuning key SGO_JAC_GRID): one above what the one-workgroup rounds
+// hold.  At 164 bands a round over the GPU is one 3.6 us launch, in one
+// workgroup 1.7 us.
+constexpr int kJacGridBandsDefault = 199;
+
+// The subspace solver's part of a candidate's reduction scratch (doubles;
+// free while the subspace problem is solved): the sweeps done, the ranks of
+// the eigenvalues, and the rotations (c, s) of every round, for at most
+// kJacMaxSweeps sweeps.
+constexpr int kJacWideMax = 198;  // largest problem of the one-workgroup rounds
+constexpr int kJacMaxSweeps = 40;
+constexpr int kJacDone = 0;    // over the GPU: 1.0 once the candidate's H' is diagonal
+constexpr int kJacSweeps = 1;
+constexpr int kJacRanks = 2;   // int [640]
+constexpr int kJacLog = kJacRanks + 320;
+constexpr size_t jac_log_doubles(int n, int sweeps) {
+  return kJacLog + (size_t)sweeps * (n + (n & 1) - 1) * (n + (n & 1));
+}
 
 struct BatchGeom {
   int ncand;
@@ -67,6 +83,14 @@ template <typename T> void launch_force_nonlocal(const LaunchCtx& L);
 template <typename T> void launch_stress_waves(const LaunchCtx& L);
 template <typename T> void launch_potential_finalize(const LaunchCtx& L);
 void launch_subspace(const LaunchCtx& L, int mode, int max_sweeps = 40);
+// Its parts: the one-workgroup step up to kJacWideMax bands (kernels_sub.hip)
+// and the products and the blocked Cholesky that it shares with the larger
+// problems (nthr: that Cholesky's threads).
+void launch_sub_block(hipStream_t st, const CandDesc* desc, int ncand, int n, int mode, int max_sweeps,
+                      int nthr);
+void launch_sub_chol_blocked(hipStream_t st, const CandDesc* desc, int ncand, int n, int mode, int nthr);
+void launch_sub_congruence(hipStream_t st, const CandDesc* desc, int ncand, int n);
+void configure_sub_kernels();
 // The subspace step with its workspace in a fixed per-device array (no
 // allocation): S, H (mode 3) device inputs [n*n], M [n*n] and eps [n] device
 // outputs; n <= kNoAllocMaxN.  With status != NULL it only enqueues on
