@@ -106,6 +106,11 @@ struct CandDesc {
   // atoms (FP64)
   const double* pos;    // [nat*3]
   const int* spec;      // [nat]
+  // phase factors e^{i m b_a.R_I}, m >= 0: phase[(I * 3 + a) * phase_m + m]
+  cplx<double>* phase;
+  int phase_m;          // entries per atom and axis: max(N_a / 2, ew_m[a]) + 1
+  int nagroup;          // atom groups: at most kAtomGroup atoms of one species
+  const int* agroup;    // [nagroup * kAtomGroup] atom indices, -1 past a group's end
   double* force;        // [nat*3] total
   double* force_ew;     // [nat*3]
   double* force_part;   // [nat*3*4] local / nonlocal scratch
@@ -127,6 +132,16 @@ struct CandDesc {
 };
 
 constexpr int kRedSlots = 1 << 16;
+
+// Local forces: a block sums kNT columns of the half grid (m1 >= 0) over
+// kForceZ planes for one atom group; their partial sums, [block][nat][3], lie
+// in red_part.
+constexpr int kAtomGroup = 8;
+constexpr int kForceZ = 16;
+constexpr int kSetupZ = 4;  // planes a thread of the geometry setup takes
+__host__ __device__ inline int force_blocks(int N1, int N2, int N3) {
+  return ((N1 + 1) / 2 * N2 + kNT - 1) / kNT * ((N3 + kForceZ - 1) / kForceZ);
+}
 
 // Stress partial sums (doubles): per band kinetic [nb][6]; per projector and
 // band (P, Q_xx..Q_xy) [nproj][nb][7]; grid blocks [kStressBlocks][16];

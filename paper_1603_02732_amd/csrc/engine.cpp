@@ -185,7 +185,8 @@ struct HostCand {
   double nelec = 0;
   int nocc = 0;
   int npwh = 0, K = 0, Kp = 0, nsp = 0, nst = 0, npair = 0, nproj = 0, ntot = 0;
-  std::vector<int> gmill, gmeta, sp_off, stick_xy, proj_atom, proj_lm;
+  std::vector<int> gmill, gmeta, sp_off, stick_xy, proj_atom, proj_lm, agroup;
+  int phase_m = 0;
   int pl_nx = 0, pl_nxl = 0, pl_sx = 1;  // active plane columns (register FFT kernels)
   int N_req[3] = {0, 0, 0}, nb_req = 0;  // as requested (0: automatic)
   std::vector<double> kin, hproj, proj_r;
@@ -500,6 +501,17 @@ class Engine {
       }
     }
     c.nproj = (int)c.proj_atom.size();
+    // atom groups of one species each
+    c.agroup.clear();
+    for (int s = 0; s < kMaxSpecies; ++s) {
+      int k = 0;
+      for (int I = 0; I < c.nat; ++I)
+        if (c.spec[I] == s) {
+          c.agroup.push_back(I);
+          ++k;
+        }
+      for (; k % kAtomGroup; ++k) c.agroup.push_back(-1);
+    }
     // Ewald ranges: erfc(eta rcut) and exp(-gcut^2/4eta^2) below ~1e-17
     c.ew_eta = std::sqrt(kPiH) * std::pow(c.nat / (c.omega * c.omega), 1.0 / 6.0);
     c.ew_rcut = 6.2 / c.ew_eta;
@@ -520,6 +532,8 @@ class Engine {
     }
     c.ew_ng = (2 * c.ew_m[0] + 1) * (2 * c.ew_m[1] + 1) * (2 * c.ew_m[2] + 1);
     c.ew_nimg = (2 * c.ew_n[0] + 1) * (2 * c.ew_n[1] + 1) * (2 * c.ew_n[2] + 1);
+    c.phase_m = 0;
+    for (int i = 0; i < 3; ++i) c.phase_m = std::max(c.phase_m, std::max(c.N[i] / 2, c.ew_m[i]) + 1);
   }
 
   size_t tsize() const { return prec_ == SGO_FP64 ? sizeof(double) : sizeof(float); }
@@ -535,6 +549,7 @@ class Engine {
     const size_t np16 = (size_t)(c.nproj + 15) / 16 * 16;
     const int ntile = (std::max(c.nb, c.nproj) + 63) / 64;
     c.red_doubles = std::max((size_t)kRedSlots, (size_t)2 * ntile * ntile * 32 * 4096);
+    c.red_doubles = std::max(c.red_doubles, (size_t)3 * c.nat * force_blocks(c.N[0], c.N[1], c.N[2]));
     if (c.nb <= kJacWideMax) c.red_doubles = std::max(c.red_doubles, jac_log_doubles(c.nb, kJacMaxSweeps));
     c.dens_chunks = g.dens_chunks;
     struct Item {
@@ -563,6 +578,7 @@ class Engine {
         {(void**)&d.hist_res, kMaxHist * nt * hist_bytes()}, {(void**)&d.pulay, kMaxHist * kMaxHist * 8},
         {(void**)&d.coef, kMaxHist * 8}, {(void**)&d.dens_part, (size_t)c.dens_chunks * nt * 8},
         {(void**)&d.pos, (size_t)3 * c.nat * 8}, {(void**)&d.spec, (size_t)c.nat * sizeof(int)},
+        {(void**)&d.phase, (size_t)3 * c.nat * c.phase_m * 16}, {(void**)&d.agroup, c.agroup.size() * sizeof(int)},
         {(void**)&d.force, (size_t)3 * c.nat * 8}, {(void**)&d.force_ew, (size_t)3 * c.nat * 8},
         {(void**)&d.force_part, (size_t)6 * c.nat * 8}, {(void**)&d.nlwork, (size_t)c.nproj * nb * 4 * 8 + 8},
         {(void**)&d.stwork, stress_layout(c.nb, c.nproj, c.nat).total * 8},
@@ -634,6 +650,8 @@ class Engine {
     }
     d.ew_ng = c.ew_ng;
     d.ew_nimg = c.ew_nimg;
+    d.phase_m = c.phase_m;
+    d.nagroup = (int)c.agroup.size() / kAtomGroup;
     auto up = [&](const void* dst, const void* src, size_t bytes) {
       if (bytes) {
         HIPCHK(hipMemcpyAsync((void*)dst, src, bytes, hipMemcpyHostToDevice, stream_));
@@ -650,6 +668,7 @@ class Engine {
     up(d.proj_lm, c.proj_lm.data(), c.nproj * 4);
     up(d.proj_r, c.proj_r.data(), c.nproj * 8);
     up(d.spec, c.spec.data(), c.nat * 4);
+    up(d.agroup, c.agroup.data(), c.agroup.size() * 4);
     up(d.pos, c.pos.data(), 3 * c.nat * 8);
   }
 
@@ -683,6 +702,10 @@ class Engine {
       g.plane_max = std::max(g.plane_max, c.N[0] * c.N[1]);
       g.K_max = std::max(g.K_max, c.K);
       g.ew_ng_max = std::max(g.ew_ng_max, c.ew_ng);
+      g.phase_max = std::max(g.phase_max, 3 * c.nat * c.phase_m);
+      g.setup_max = std::max(g.setup_max, c.N[0] * c.N[1] * ((c.N[2] + kSetupZ - 1) / kSetupZ));
+      g.nagroup_max = std::max(g.nagroup_max, (int)c.agroup.size() / kAtomGroup);
+      g.force_blocks_max = std::max(g.force_blocks_max, force_blocks(c.N[0], c.N[1], c.N[2]));
       g.pl_sx_max = std::max(g.pl_sx_max, c.pl_sx);
     }
     g.sp_chunk = std::max(1, tune("SGO_SP_CHUNK", std::max(1, 640 / std::max(1, g.N3max))));
@@ -1392,8 +1415,8 @@ class Engine {
       kpt_force_nl(stream_, kP_, kdP_, c.nproj, c.nb, c.d.hproj, c.d.proj_atom, kocc_ + (size_t)ik * c.nb,
                    k.w, c.nat, kfnl_, ik == 0 ? 1 : 0);
     }
-    kpt_force_total(stream_, c.d.force_part, kfnl_, c.d.force_ew, c.nat, c.d.force,
-                    c.d.force_part + 3 * c.nat);
+    kpt_force_total(stream_, c.d.red_part, force_blocks(c.N[0], c.N[1], c.N[2]), kfnl_, c.d.force_ew, c.nat,
+                    c.d.force, c.d.force_part + 3 * c.nat);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(stream_));
     c.have_psi = false;  // the Gamma bands were not solved

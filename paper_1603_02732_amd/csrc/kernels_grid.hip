@@ -23,6 +23,7 @@ __device__ __forceinline__ int gfreq(int i, int n) { return i < (n + 1) / 2 ? i 
 struct GPoint {
   double G[3];
   double g2;
+  int m1, m2, m3;
   bool inD;
 };
 __device__ __forceinline__ GPoint gpoint(const CandDesc& cd, int e) {
@@ -32,6 +33,9 @@ __device__ __forceinline__ GPoint gpoint(const CandDesc& cd, int e) {
   const int z = yz / cd.N2;
   const int m1 = gfreq(x, cd.N1), m2 = gfreq(y, cd.N2), m3 = gfreq(z, cd.N3);
   GPoint p;
+  p.m1 = m1;
+  p.m2 = m2;
+  p.m3 = m3;
   p.G[0] = m1 * cd.B[0] + m2 * cd.B[3] + m3 * cd.B[6];
   p.G[1] = m1 * cd.B[1] + m2 * cd.B[4] + m3 * cd.B[7];
   p.G[2] = m1 * cd.B[2] + m2 * cd.B[5] + m3 * cd.B[8];
@@ -400,35 +404,96 @@ __global__ void __launch_bounds__(kNT) k_mix(const CandDesc* __restrict__ cds, i
 }
 
 // --------------------------------------------------------------- setup
+// Phase factors e^{i m b_a.R_I} of every atom and axis.  The structure-factor
+// sums below take e^{iG.R} as a product of three of them: an FP64 sincos per
+// (grid point, atom) was nearly all of their time.
+__global__ void __launch_bounds__(kNT) k_phase(const CandDesc* __restrict__ cds) {
+  const CandDesc& cd = cds[blockIdx.z];
+  if (!cd.active) return;
+  const int n = cd.nat * 3 * cd.phase_m;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+    const int m = t % cd.phase_m, Ia = t / cd.phase_m, a = Ia % 3, I = Ia / 3;
+    const double th = cd.B[3 * a] * cd.pos[3 * I] + cd.B[3 * a + 1] * cd.pos[3 * I + 1] +
+                      cd.B[3 * a + 2] * cd.pos[3 * I + 2];
+    double sn, cs;
+    sincos(m * th, &sn, &cs);
+    cd.phase[t] = {cs, sn};
+  }
+}
+// e^{i m b_a.R_I}, any sign of m
+__device__ __forceinline__ cplx<double> phase_of(const CandDesc& cd, int I, int a, int m) {
+  cplx<double> z = cd.phase[(I * 3 + a) * cd.phase_m + abs(m)];
+  if (m < 0) z.y = -z.y;
+  return z;
+}
+
 // V_loc(G) = (1/Omega) sum_I v_s(|G|) e^{-iG.R_I} and the starting density
-// rho_0(G) = (1/Omega) sum_I Z_I e^{-G^2 w^2/2} e^{-iG.R_I} on D.
+// rho_0(G) = (1/Omega) sum_I Z_I e^{-G^2 w^2/2} e^{-iG.R_I} on D.  A thread
+// takes kSetupZ grid points of one (x, y) column, so the product of the two
+// in-plane phase factors and the species' transforms are shared: bounded by
+// the two grids it writes.  32 clusters of 13 atoms on 48^3: 309 us with a
+// sincos per point and atom.
 __global__ void __launch_bounds__(kNT) k_setup_grid(const CandDesc* __restrict__ cds,
                                                     const SpeciesDev* __restrict__ sp) {
   const CandDesc& cd = cds[blockIdx.z];
   if (!cd.active) return;
-  const double io = 1.0 / cd.omega;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < cd.ntot; e += gridDim.x * blockDim.x) {
-    const GPoint p = gpoint(cd, e);
-    cplx<double> vl = {0.0, 0.0}, r0 = {0.0, 0.0};
-    if (p.inD) {
-      double ztot = 0.0;
-      for (int I = 0; I < cd.nat; ++I) {
-        const SpeciesDev& s = sp[cd.spec[I]];
-        double sn, cs;
-        sincos(-(p.G[0] * cd.pos[3 * I] + p.G[1] * cd.pos[3 * I + 1] + p.G[2] * cd.pos[3 * I + 2]),
-               &sn, &cs);
-        const double v = p.g2 > 0.0 ? vloc_ft(s, p.g2) : vloc_g0(s);
-        vl.x += v * cs;
-        vl.y += v * sn;
-        const double a = s.Z * exp(-0.5 * p.g2 * s.rho0_width * s.rho0_width);
-        r0.x += a * cs;
-        r0.y += a * sn;
-        ztot += s.Z;
-      }
-      if (p.g2 == 0.0) r0.x += cd.nelec - ztot;
+  const int N12 = cd.N1 * cd.N2, nz = (cd.N3 + kSetupZ - 1) / kSetupZ;
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= N12 * nz) return;
+  const int col = t % N12, z0 = t / N12 * kSetupZ;
+  const int m1 = gfreq(col % cd.N1, cd.N1), m2 = gfreq(col / cd.N1, cd.N2);
+  const bool in12 = 2 * abs(m1) < cd.N1 && 2 * abs(m2) < cd.N2;
+  int m3[kSetupZ];
+  double g2[kSetupZ];
+  cplx<double> vl[kSetupZ], r0[kSetupZ];
+#pragma unroll
+  for (int q = 0; q < kSetupZ; ++q) {
+    m3[q] = gfreq(min(z0 + q, cd.N3 - 1), cd.N3);
+    double s = 0.0;
+    for (int k = 0; k < 3; ++k) {
+      const double G = m1 * cd.B[k] + m2 * cd.B[3 + k] + m3[q] * cd.B[6 + k];
+      s += G * G;
     }
-    cd.vloc_G[e] = {vl.x * io, vl.y * io};
-    cd.rho0_G[e] = {r0.x * io, r0.y * io};
+    g2[q] = s;
+    vl[q] = r0[q] = {0.0, 0.0};
+  }
+  double ztot = 0.0;
+  if (in12)
+    for (int g = 0; g < cd.nagroup; ++g) {
+      const int* at = cd.agroup + g * kAtomGroup;
+      const SpeciesDev& s = sp[cd.spec[at[0]]];
+      cplx<double> S[kSetupZ];
+#pragma unroll
+      for (int q = 0; q < kSetupZ; ++q) S[q] = {0.0, 0.0};
+      for (int i = 0; i < kAtomGroup && at[i] >= 0; ++i) {
+        const cplx<double> e12 = cmul(phase_of(cd, at[i], 0, m1), phase_of(cd, at[i], 1, m2));
+        ztot += s.Z;
+#pragma unroll
+        for (int q = 0; q < kSetupZ; ++q) {
+          const cplx<double> z = cmul(e12, phase_of(cd, at[i], 2, m3[q]));
+          S[q].x += z.x;
+          S[q].y -= z.y;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kSetupZ; ++q) {
+        const double v = g2[q] > 0.0 ? vloc_ft(s, g2[q]) : vloc_g0(s);
+        const double a = s.Z * exp(-0.5 * g2[q] * s.rho0_width * s.rho0_width);
+        vl[q].x += v * S[q].x;
+        vl[q].y += v * S[q].y;
+        r0[q].x += a * S[q].x;
+        r0[q].y += a * S[q].y;
+      }
+    }
+  const double io = 1.0 / cd.omega;
+#pragma unroll
+  for (int q = 0; q < kSetupZ; ++q) {
+    if (z0 + q >= cd.N3) break;
+    const int e = (z0 + q) * N12 + col;
+    const bool in = 2 * abs(m3[q]) < cd.N3;
+    if (g2[q] == 0.0) r0[q].x += cd.nelec - ztot;
+    cd.vloc_G[e] = in ? cplx<double>{vl[q].x * io, vl[q].y * io} : cplx<double>{0.0, 0.0};
+    cd.rho0_G[e] = in ? cplx<double>{r0[q].x * io, r0[q].y * io} : cplx<double>{0.0, 0.0};
   }
 }
 
@@ -455,11 +520,11 @@ __global__ void __launch_bounds__(kNT) k_ewald_recip(const CandDesc* __restrict_
     cplx<double> S = {0.0, 0.0};
     if (g2 > 0.0 && g2 <= cd.ew_gcut * cd.ew_gcut) {
       for (int J = 0; J < cd.nat; ++J) {
-        double sn, cs;
-        sincos(G0 * cd.pos[3 * J] + G1 * cd.pos[3 * J + 1] + G2 * cd.pos[3 * J + 2], &sn, &cs);
+        const cplx<double> z =
+            cmul(cmul(phase_of(cd, J, 0, m1), phase_of(cd, J, 1, m2)), phase_of(cd, J, 2, m3));
         const double Z = sp[cd.spec[J]].Z;
-        S.x += Z * cs;
-        S.y += Z * sn;
+        S.x += Z * z.x;
+        S.y += Z * z.y;
       }
       v[0] += exp(-g2 / (4.0 * eta * eta)) / g2 * (S.x * S.x + S.y * S.y);
     }
@@ -474,8 +539,11 @@ __global__ void __launch_bounds__(kNT) k_ewald_recip(const CandDesc* __restrict_
 
 // Ewald, per atom I: real-space pair sum over images, reciprocal force from
 // S(G); the last block adds self and background terms to the total.
-__global__ void __launch_bounds__(kNT) k_ewald_atom(const CandDesc* __restrict__ cds,
-                                                    const SpeciesDev* __restrict__ sp) {
+// A thread takes an image cell and loops over the atoms J, so the cell's
+// indices are worked out once.
+constexpr int kEwaldNT = 512;
+__global__ void __launch_bounds__(kEwaldNT) k_ewald_atom(const CandDesc* __restrict__ cds,
+                                                         const SpeciesDev* __restrict__ sp) {
   const CandDesc& cd = cds[blockIdx.z];
   if (!cd.active) return;
   const int I = blockIdx.x;
@@ -487,27 +555,29 @@ __global__ void __launch_bounds__(kNT) k_ewald_atom(const CandDesc* __restrict__
   const int n1 = 2 * cd.ew_n[0] + 1, n2 = 2 * cd.ew_n[1] + 1;
   double v[4] = {0.0, 0.0, 0.0, 0.0};  // energy, Fx, Fy, Fz
   const double rc2 = cd.ew_rcut * cd.ew_rcut;
-  const long total = (long)cd.nat * cd.ew_nimg;
-  for (long t = threadIdx.x; t < total; t += blockDim.x) {
-    const int J = (int)(t / cd.ew_nimg);
-    const int im = (int)(t - (long)J * cd.ew_nimg);
+  for (int im = threadIdx.x; im < cd.ew_nimg; im += blockDim.x) {
     const int a = im % n1 - cd.ew_n[0];
     const int b = (im / n1) % n2 - cd.ew_n[1];
     const int c = im / (n1 * n2) - cd.ew_n[2];
-    const double d0 = RI0 - cd.pos[3 * J] + a * cd.A[0] + b * cd.A[3] + c * cd.A[6];
-    const double d1 = RI1 - cd.pos[3 * J + 1] + a * cd.A[1] + b * cd.A[4] + c * cd.A[7];
-    const double d2 = RI2 - cd.pos[3 * J + 2] + a * cd.A[2] + b * cd.A[5] + c * cd.A[8];
-    const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-    if (r2 < 1e-24 || r2 > rc2) continue;
-    const double r = sqrt(r2);
-    const double ZZ = ZI * sp[cd.spec[J]].Z;
-    const double ec = erfc(eta * r);
-    v[0] += 0.5 * ZZ * ec / r;
-    const double dphi = ec / r2 + 2.0 * eta / sqrt(kPi) * exp(-eta * eta * r2) / r;
-    const double f = ZZ * dphi / r;
-    v[1] += f * d0;
-    v[2] += f * d1;
-    v[3] += f * d2;
+    const double L0 = a * cd.A[0] + b * cd.A[3] + c * cd.A[6];
+    const double L1 = a * cd.A[1] + b * cd.A[4] + c * cd.A[7];
+    const double L2 = a * cd.A[2] + b * cd.A[5] + c * cd.A[8];
+    for (int J = 0; J < cd.nat; ++J) {
+      const double d0 = RI0 - cd.pos[3 * J] + L0;
+      const double d1 = RI1 - cd.pos[3 * J + 1] + L1;
+      const double d2 = RI2 - cd.pos[3 * J + 2] + L2;
+      const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+      if (r2 < 1e-24 || r2 > rc2) continue;
+      const double r = sqrt(r2);
+      const double ZZ = ZI * sp[cd.spec[J]].Z;
+      const double ec = erfc(eta * r);
+      v[0] += 0.5 * ZZ * ec / r;
+      const double dphi = ec / r2 + 2.0 * eta / sqrt(kPi) * exp(-eta * eta * r2) / r;
+      const double f = ZZ * dphi / r;
+      v[1] += f * d0;
+      v[2] += f * d1;
+      v[3] += f * d2;
+    }
   }
   const int w1 = 2 * cd.ew_m[0] + 1, w2 = 2 * cd.ew_m[1] + 1;
   for (int t = threadIdx.x; t < cd.ew_ng; t += blockDim.x) {
@@ -520,10 +590,10 @@ __global__ void __launch_bounds__(kNT) k_ewald_atom(const CandDesc* __restrict__
     const double g2 = G0 * G0 + G1 * G1 + G2 * G2;
     if (!(g2 > 0.0) || g2 > cd.ew_gcut * cd.ew_gcut) continue;
     const cplx<double> S = cd.ewS[t];
-    double sn, cs;
-    sincos(G0 * RI0 + G1 * RI1 + G2 * RI2, &sn, &cs);
+    const cplx<double> z =
+        cmul(cmul(phase_of(cd, I, 0, m1), phase_of(cd, I, 1, m2)), phase_of(cd, I, 2, m3));
     // Im[conj(S) e^{iG.R_I}]
-    const double im = S.x * sn - S.y * cs;
+    const double im = S.x * z.y - S.y * z.x;
     const double w = 4.0 * kPi / cd.omega * ZI * exp(-g2 / (4.0 * eta * eta)) / g2 * im;
     v[1] += w * G0;
     v[2] += w * G1;
@@ -553,56 +623,105 @@ __global__ void __launch_bounds__(kNT) k_ewald_atom(const CandDesc* __restrict__
 }
 
 // ------------------------------------------------------------------ forces
-// F_loc,I = sum_{G in D, G != 0} G v_s(|G|) Im[e^{iG.R_I} rho(G)].
+// F_loc,I = sum_{G in D, G != 0} G v_s(|G|) Im[e^{iG.R_I} rho(G)].  rho(r) is
+// real, so G and -G give the same: the m1 >= 0 half of the grid, m1 > 0
+// counted twice.  A thread takes one (x, y) column and sums e^{i m3 b_3.R}
+// v_s rho and m3 times it over kForceZ planes for the atoms of a group (one
+// species: v_s(G) once for all of them); the in-plane factors come in once at
+// the end.  With a block per atom and a sincos per grid point: 516 us for 32
+// clusters of 13 atoms on 48^3, 309 us for one 24-atom sheet.
 __global__ void __launch_bounds__(kNT) k_force_local(const CandDesc* __restrict__ cds,
                                                      const SpeciesDev* __restrict__ sp) {
   const CandDesc& cd = cds[blockIdx.z];
   if (!cd.active) return;
-  const int I = blockIdx.x;
-  if (I >= cd.nat) return;
-  __shared__ double sh[16 * 3];
-  const SpeciesDev& s = sp[cd.spec[I]];
-  const double R0 = cd.pos[3 * I], R1 = cd.pos[3 * I + 1], R2 = cd.pos[3 * I + 2];
-  double v[3] = {0.0, 0.0, 0.0};
-  for (int e = threadIdx.x; e < cd.ntot; e += blockDim.x) {
-    const GPoint p = gpoint(cd, e);
-    if (!p.inD || !(p.g2 > 0.0)) continue;
-    const double vs = vloc_ft(s, p.g2);
-    double sn, cs;
-    sincos(p.G[0] * R0 + p.G[1] * R1 + p.G[2] * R2, &sn, &cs);
-    const cplx<double> r = cd.rho_out_G[e];
-    const double im = vs * (cs * r.y + sn * r.x);
-    v[0] += p.G[0] * im;
-    v[1] += p.G[1] * im;
-    v[2] += p.G[2] * im;
+  if ((int)blockIdx.y >= cd.nagroup) return;
+  const int h1 = (cd.N1 + 1) / 2, ncol = h1 * cd.N2, ncb = (ncol + kNT - 1) / kNT;
+  const int zc = blockIdx.x / ncb;
+  if (zc * kForceZ >= cd.N3) return;
+  const int* at = cd.agroup + blockIdx.y * kAtomGroup;
+  const SpeciesDev& s = sp[cd.spec[at[0]]];
+  const int c = (blockIdx.x - zc * ncb) * kNT + threadIdx.x;
+  const int m1 = c % h1, m2 = gfreq(min(c / h1, cd.N2 - 1), cd.N2);
+  const bool in12 = c < ncol && 2 * m1 < cd.N1 && 2 * abs(m2) < cd.N2;
+  const int y = min(c / h1, cd.N2 - 1);
+  const double w12 = !in12 ? 0.0 : (m1 == 0 ? 1.0 : 2.0);
+  int I[kAtomGroup];
+  double a0r[kAtomGroup], a0i[kAtomGroup], a1r[kAtomGroup], a1i[kAtomGroup];
+#pragma unroll
+  for (int i = 0; i < kAtomGroup; ++i) {
+    I[i] = at[i] < 0 ? at[0] : at[i];
+    a0r[i] = a0i[i] = a1r[i] = a1i[i] = 0.0;
   }
-  block_sum<3>(v, sh);
-  if (threadIdx.x == 0) {
-    cd.force_part[3 * I] = v[0];
-    cd.force_part[3 * I + 1] = v[1];
-    cd.force_part[3 * I + 2] = v[2];
+  const double b0 = m1 * cd.B[0] + m2 * cd.B[3], b1 = m1 * cd.B[1] + m2 * cd.B[4],
+               b2 = m1 * cd.B[2] + m2 * cd.B[5];
+  for (int z = zc * kForceZ; z < min(cd.N3, (zc + 1) * kForceZ); ++z) {
+    const int m3 = gfreq(z, cd.N3);
+    if (2 * abs(m3) >= cd.N3) continue;
+    const double G0 = b0 + m3 * cd.B[6], G1 = b1 + m3 * cd.B[7], G2 = b2 + m3 * cd.B[8];
+    const double g2 = G0 * G0 + G1 * G1 + G2 * G2;
+    const double vs = g2 > 0.0 ? w12 * vloc_ft(s, g2) : 0.0;
+    const cplx<double> r = cd.rho_out_G[((size_t)z * cd.N2 + y) * cd.N1 + m1];
+    const double wr = vs * r.x, wi = vs * r.y;
+#pragma unroll
+    for (int i = 0; i < kAtomGroup; ++i) {
+      const cplx<double> e = phase_of(cd, I[i], 2, m3);
+      const double ur = e.x * wr - e.y * wi, ui = e.x * wi + e.y * wr;
+      a0r[i] += ur;
+      a0i[i] += ui;
+      a1r[i] += m3 * ur;
+      a1i[i] += m3 * ui;
+    }
+  }
+  __shared__ double sh[kNT / 64][3 * kAtomGroup];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < kAtomGroup; ++i) {
+    const cplx<double> e = cmul(phase_of(cd, I[i], 0, m1), phase_of(cd, I[i], 1, m2));
+    const double im0 = e.x * a0i[i] + e.y * a0r[i];
+    const double im3 = wave_sum(e.x * a1i[i] + e.y * a1r[i]);
+    const double im1 = wave_sum(m1 * im0), im2 = wave_sum(m2 * im0);
+    if (lane < 3) sh[w][3 * i + lane] = im1 * cd.B[lane] + im2 * cd.B[3 + lane] + im3 * cd.B[6 + lane];
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < 3 * kAtomGroup; t += blockDim.x) {
+    if (at[t / 3] < 0) continue;
+    double f = 0.0;
+    for (int k = 0; k < kNT / 64; ++k) f += sh[k][t];
+    cd.red_part[((size_t)blockIdx.x * cd.nat + at[t / 3]) * 3 + t % 3] = f;
   }
 }
 
 // Total force: local + nonlocal (-2 sum_i f_i sum_{p on I} h_p P dP) + Ewald.
-__global__ void k_force_finalize(const CandDesc* __restrict__ cds) {
-  const CandDesc& cd = cds[blockIdx.x];
+// One wavefront per atom, lanes over the bands (and over the blocks of the
+// local sums), added in a fixed order.
+__global__ void __launch_bounds__(64) k_force_finalize(const CandDesc* __restrict__ cds) {
+  const CandDesc& cd = cds[blockIdx.y];
   if (!cd.active) return;
-  for (int t = threadIdx.x; t < 3 * cd.nat; t += blockDim.x) {
-    const int I = t / 3, a = t - 3 * I;
-    double fnl = 0.0;
-    for (int p = 0; p < cd.nproj; ++p) {
-      if (cd.proj_atom[p] != I) continue;
-      double s = 0.0;
-      for (int i = 0; i < cd.nb; ++i) {
-        const double* w = cd.nlwork + ((size_t)p * cd.nb + i) * 4;
-        s += cd.occ[i] * w[0] * w[1 + a];
-      }
-      fnl += -2.0 * cd.hproj[p] * s;
+  const int I = blockIdx.x, lane = threadIdx.x;
+  if (I >= cd.nat) return;
+  double f[3] = {0.0, 0.0, 0.0}, l[3] = {0.0, 0.0, 0.0};
+  for (int p = 0; p < cd.nproj; ++p) {
+    if (cd.proj_atom[p] != I) continue;
+    const double h = -2.0 * cd.hproj[p];
+    for (int i = lane; i < cd.nb; i += 64) {
+      const double* w = cd.nlwork + ((size_t)p * cd.nb + i) * 4;
+      const double c = h * cd.occ[i] * w[0];
+      for (int a = 0; a < 3; ++a) f[a] += c * w[1 + a];
     }
-    cd.force_part[3 * cd.nat + t] = fnl;
-    cd.force[t] = cd.force_part[t] + fnl + cd.force_ew[t];
   }
+  const int nb = force_blocks(cd.N1, cd.N2, cd.N3);
+  for (int b = lane; b < nb; b += 64)
+    for (int a = 0; a < 3; ++a) l[a] += cd.red_part[((size_t)b * cd.nat + I) * 3 + a];
+  for (int a = 0; a < 3; ++a) {
+    f[a] = wave_sum(f[a]);
+    l[a] = wave_sum(l[a]);
+  }
+  if (lane == 0)
+    for (int a = 0; a < 3; ++a) {
+      cd.force_part[3 * I + a] = l[a];
+      cd.force_part[3 * cd.nat + 3 * I + a] = f[a];
+      cd.force[3 * I + a] = l[a] + f[a] + cd.force_ew[3 * I + a];
+    }
 }
 
 // ------------------------------------------------------------------ stress
@@ -648,11 +767,15 @@ __global__ void __launch_bounds__(kNT) k_stress_grid(const CandDesc* __restrict_
         v[12] += h;
         add_voigt(v, h / p.g2, p.G);
         double loc = 0.0;
-        for (int I = 0; I < cd.nat; ++I) {
-          double sn, cs;
-          sincos(p.G[0] * cd.pos[3 * I] + p.G[1] * cd.pos[3 * I + 1] + p.G[2] * cd.pos[3 * I + 2],
-                 &sn, &cs);
-          loc += vloc_dq(sp[cd.spec[I]], p.g2) * (cs * r.x - sn * r.y);
+        for (int k = 0; k < cd.nagroup; ++k) {
+          const int* at = cd.agroup + k * kAtomGroup;
+          double re = 0.0;
+          for (int i = 0; i < kAtomGroup && at[i] >= 0; ++i) {
+            const cplx<double> z = cmul(cmul(phase_of(cd, at[i], 0, p.m1), phase_of(cd, at[i], 1, p.m2)),
+                                        phase_of(cd, at[i], 2, p.m3));
+            re += z.x * r.x - z.y * r.y;
+          }
+          loc += vloc_dq(sp[cd.spec[at[0]]], p.g2) * re;
         }
         add_voigt(v + 6, -2.0 * loc, p.G);
       }
@@ -674,8 +797,8 @@ __global__ void __launch_bounds__(kNT) k_stress_grid(const CandDesc* __restrict_
 // and the reciprocal points t = I (mod nat) of the enumerated box
 //   v[6..11] sum_G |S|^2 w(G) 2 G_a G_b (1/(4 eta^2) + 1/G^2),  v[12] sum_G |S|^2 w(G)
 // with w = e^{-G^2/4eta^2}/G^2.
-__global__ void __launch_bounds__(kNT) k_stress_ewald(const CandDesc* __restrict__ cds,
-                                                      const SpeciesDev* __restrict__ sp) {
+__global__ void __launch_bounds__(kEwaldNT) k_stress_ewald(const CandDesc* __restrict__ cds,
+                                                           const SpeciesDev* __restrict__ sp) {
   const CandDesc& cd = cds[blockIdx.z];
   if (!cd.active) return;
   const int I = blockIdx.x;
@@ -688,29 +811,28 @@ __global__ void __launch_bounds__(kNT) k_stress_ewald(const CandDesc* __restrict
   const double ZI = sp[cd.spec[I]].Z;
   const int n1 = 2 * cd.ew_n[0] + 1, n2 = 2 * cd.ew_n[1] + 1;
   const double rc2 = cd.ew_rcut * cd.ew_rcut;
-  const long total = (long)cd.nat * cd.ew_nimg;
-  for (long t = threadIdx.x; t < total; t += blockDim.x) {
-    const int J = (int)(t / cd.ew_nimg);
-    const int im = (int)(t - (long)J * cd.ew_nimg);
+  for (int im = threadIdx.x; im < cd.ew_nimg; im += blockDim.x) {
     const int a = im % n1 - cd.ew_n[0];
     const int b = (im / n1) % n2 - cd.ew_n[1];
     const int c = im / (n1 * n2) - cd.ew_n[2];
-    double d[3];
-    d[0] = cd.pos[3 * I] - cd.pos[3 * J] + a * cd.A[0] + b * cd.A[3] + c * cd.A[6];
-    d[1] = cd.pos[3 * I + 1] - cd.pos[3 * J + 1] + a * cd.A[1] + b * cd.A[4] + c * cd.A[7];
-    d[2] = cd.pos[3 * I + 2] - cd.pos[3 * J + 2] + a * cd.A[2] + b * cd.A[5] + c * cd.A[8];
-    const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-    if (r2 < 1e-24 || r2 > rc2) continue;
-    const double r = sqrt(r2);
-    const double dphi = -(erfc(eta * r) / r2 + 2.0 * eta / sqrt(kPi) * exp(-eta * eta * r2) / r);
-    add_voigt(v, 0.5 * ZI * sp[cd.spec[J]].Z * dphi / r, d);
+    double L[3];
+    for (int k = 0; k < 3; ++k)
+      L[k] = cd.pos[3 * I + k] + a * cd.A[k] + b * cd.A[3 + k] + c * cd.A[6 + k];
+    for (int J = 0; J < cd.nat; ++J) {
+      const double d[3] = {L[0] - cd.pos[3 * J], L[1] - cd.pos[3 * J + 1], L[2] - cd.pos[3 * J + 2]};
+      const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+      if (r2 < 1e-24 || r2 > rc2) continue;
+      const double r = sqrt(r2);
+      const double dphi = -(erfc(eta * r) / r2 + 2.0 * eta / sqrt(kPi) * exp(-eta * eta * r2) / r);
+      add_voigt(v, 0.5 * ZI * sp[cd.spec[J]].Z * dphi / r, d);
+    }
   }
   const int w1 = 2 * cd.ew_m[0] + 1, w2 = 2 * cd.ew_m[1] + 1;
   const double q4 = 1.0 / (4.0 * eta * eta);
-  for (long t = (long)threadIdx.x * cd.nat + I; t < cd.ew_ng; t += (long)blockDim.x * cd.nat) {
-    const int m1 = (int)(t % w1) - cd.ew_m[0];
-    const int m2 = (int)((t / w1) % w2) - cd.ew_m[1];
-    const int m3 = (int)(t / ((long)w1 * w2)) - cd.ew_m[2];
+  for (int t = threadIdx.x * cd.nat + I; t < cd.ew_ng; t += blockDim.x * cd.nat) {
+    const int m1 = t % w1 - cd.ew_m[0];
+    const int m2 = (t / w1) % w2 - cd.ew_m[1];
+    const int m3 = t / (w1 * w2) - cd.ew_m[2];
     double G[3];
     G[0] = m1 * cd.B[0] + m2 * cd.B[3] + m3 * cd.B[6];
     G[1] = m1 * cd.B[1] + m2 * cd.B[4] + m3 * cd.B[7];
@@ -815,14 +937,23 @@ __global__ void __launch_bounds__(kNT) k_stress_finalize(const CandDesc* __restr
 
 // ------------------------------------------------------------ occupations
 // Fixed: f = 2 on the lowest nocc bands.  Fermi-Dirac: f = 2/(1+e^{(e-mu)/s})
-// with mu from 200 bisection steps so that sum f = N_el; entropy
-// S = -2 sum [g ln g + (1-g) ln(1-g)], g = f/2.
-__global__ void __launch_bounds__(64) k_occupations(const CandDesc* __restrict__ cds) {
-  // one wavefront per candidate: all reductions are cross-lane sums
+// with mu to the last bit so that sum f = N_el; entropy
+// S = -2 sum [g ln g + (1-g) ln(1-g)], g = f/2.  The electron count is monotone
+// in mu, so each of the kOccWaves wavefronts counts at its own point of the
+// bracket and a round narrows it (kOccWaves + 1)-fold: a serial chain of
+// about 20 exponentials instead of the bisection's 60 (32 bands: 30 us).
+constexpr int kOccWaves = 8;
+__device__ __forceinline__ double occ_count(const double* eps, int n, double mu, double sg, int lane) {
+  double v = 0.0;
+  for (int i = lane; i < n; i += 64) v += 2.0 / (1.0 + exp((eps[i] - mu) / sg));
+  return wave_sum(v);
+}
+__global__ void __launch_bounds__(64 * kOccWaves) k_occupations(const CandDesc* __restrict__ cds) {
   const CandDesc& cd = cds[blockIdx.x];
   if (!cd.active) return;
-  const int n = cd.nb, lane = threadIdx.x;
+  const int n = cd.nb, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if (cd.occ_kind == 0) {
+    if (w != 0) return;
     double v = 0.0;
     for (int i = lane; i < n; i += 64) {
       const double f = i < cd.nocc ? 2.0 : 0.0;
@@ -849,15 +980,22 @@ __global__ void __launch_bounds__(64) k_occupations(const CandDesc* __restrict__
   }
   lo -= 40.0 * sg;
   hi += 40.0 * sg;
-  for (int it = 0; it < 200; ++it) {
-    const double mu = 0.5 * (lo + hi);
-    if (mu <= lo || mu >= hi) break;  // interval exhausted in FP64
-    double v = 0.0;
-    for (int i = lane; i < n; i += 64) v += 2.0 / (1.0 + exp((cd.eps[i] - mu) / sg));
-    v = wave_sum(v);
-    if (v > cd.nelec) hi = mu;
-    else lo = mu;
+  __shared__ int over[2][kOccWaves];
+  for (int it = 0; it < 80; ++it) {
+    const double mid = 0.5 * (lo + hi);
+    if (mid <= lo || mid >= hi) break;  // interval exhausted in FP64
+    // the points lo + (hi - lo) (w + 1) / (kOccWaves + 1), ascending, inside the bracket
+    const double mu = fmin(fmax(lo + (hi - lo) * ((w + 1) / (kOccWaves + 1.0)), lo), hi);
+    const double v = occ_count(cd.eps, n, mu, sg, lane);
+    if (lane == 0) over[it & 1][w] = v > cd.nelec;
+    __syncthreads();
+    int k = 0;  // points that do not hold too many electrons
+    while (k < kOccWaves && !over[it & 1][k]) ++k;
+    const double a = lo, d = hi - lo;
+    if (k > 0) lo = fmin(fmax(a + d * (k / (kOccWaves + 1.0)), a), hi);
+    if (k < kOccWaves) hi = fmin(fmax(a + d * ((k + 1) / (kOccWaves + 1.0)), a), hi);
   }
+  if (w != 0) return;
   const double mu = 0.5 * (lo + hi);
   double v0 = 0.0, v1 = 0.0;
   for (int i = lane; i < n; i += 64) {
@@ -1538,9 +1676,12 @@ void launch_mix(const LaunchCtx& L, int initial, double alpha, double q0) {
   prof_after("k_mix", L.stream);
 }
 void launch_setup_grid(const LaunchCtx& L) {
+  hipLaunchKernelGGL(k_phase, dim3((L.g.phase_max + kNT - 1) / kNT, 1, L.g.ncand), dim3(kNT), 0, L.stream,
+                     L.desc);
+  check_launch("k_phase");
   prof_before("k_setup_grid", L.stream);
-  hipLaunchKernelGGL(k_setup_grid, dim3(grid_blocks(L.g), 1, L.g.ncand), dim3(kNT), 0, L.stream,
-                     L.desc, L.species);
+  hipLaunchKernelGGL(k_setup_grid, dim3((L.g.setup_max + kNT - 1) / kNT, 1, L.g.ncand), dim3(kNT), 0,
+                     L.stream, L.desc, L.species);
   check_launch("k_setup_grid");
   prof_after("k_setup_grid", L.stream);
 }
@@ -1552,21 +1693,21 @@ void launch_ewald(const LaunchCtx& L) {
   check_launch("k_ewald_recip");
   prof_after("k_ewald_recip", L.stream);
   prof_before("k_ewald_atom", L.stream);
-  hipLaunchKernelGGL(k_ewald_atom, dim3(L.g.nat_max, 1, L.g.ncand), dim3(kNT), 0, L.stream,
+  hipLaunchKernelGGL(k_ewald_atom, dim3(L.g.nat_max, 1, L.g.ncand), dim3(kEwaldNT), 0, L.stream,
                      L.desc, L.species);
   check_launch("k_ewald_atom");
   prof_after("k_ewald_atom", L.stream);
 }
 void launch_force_local(const LaunchCtx& L) {
   prof_before("k_force_local", L.stream);
-  hipLaunchKernelGGL(k_force_local, dim3(L.g.nat_max, 1, L.g.ncand), dim3(kNT), 0, L.stream,
-                     L.desc, L.species);
+  hipLaunchKernelGGL(k_force_local, dim3(L.g.force_blocks_max, L.g.nagroup_max, L.g.ncand), dim3(kNT), 0,
+                     L.stream, L.desc, L.species);
   check_launch("k_force_local");
   prof_after("k_force_local", L.stream);
 }
 void launch_force_finalize(const LaunchCtx& L) {
   prof_before("k_force_finalize", L.stream);
-  hipLaunchKernelGGL(k_force_finalize, dim3(L.g.ncand), dim3(kNT), 0, L.stream, L.desc);
+  hipLaunchKernelGGL(k_force_finalize, dim3(L.g.nat_max, L.g.ncand), dim3(64), 0, L.stream, L.desc);
   check_launch("k_force_finalize");
   prof_after("k_force_finalize", L.stream);
 }
@@ -1577,7 +1718,7 @@ void launch_stress_grid(const LaunchCtx& L) {
   check_launch("k_stress_grid");
   prof_after("k_stress_grid", L.stream);
   prof_before("k_stress_ewald", L.stream);
-  hipLaunchKernelGGL(k_stress_ewald, dim3(L.g.nat_max, 1, L.g.ncand), dim3(kNT), 0, L.stream,
+  hipLaunchKernelGGL(k_stress_ewald, dim3(L.g.nat_max, 1, L.g.ncand), dim3(kEwaldNT), 0, L.stream,
                      L.desc, L.species);
   check_launch("k_stress_ewald");
   prof_after("k_stress_ewald", L.stream);
@@ -1589,7 +1730,7 @@ void launch_stress_grid(const LaunchCtx& L) {
 }
 void launch_occupations(const LaunchCtx& L) {
   prof_before("k_occupations", L.stream);
-  hipLaunchKernelGGL(k_occupations, dim3(L.g.ncand), dim3(64), 0, L.stream, L.desc);
+  hipLaunchKernelGGL(k_occupations, dim3(L.g.ncand), dim3(64 * kOccWaves), 0, L.stream, L.desc);
   check_launch("k_occupations");
   prof_after("k_occupations", L.stream);
 }

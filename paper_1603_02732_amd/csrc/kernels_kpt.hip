@@ -613,13 +613,15 @@ __global__ void k_kpt_force_nl(const zc* __restrict__ P, const zc* __restrict__ 
   }
 }
 
-// total force: local (force_part) + nonlocal + Ewald
-__global__ void k_kpt_force_total(const double* __restrict__ floc, const double* __restrict__ fnl,
+// total force: local (the partial sums [nblk][nat][3]) + nonlocal + Ewald
+__global__ void k_kpt_force_total(const double* __restrict__ floc, int nblk, const double* __restrict__ fnl,
                                   const double* __restrict__ few, int nat, double* __restrict__ force,
                                   double* __restrict__ fnl_part) {
   for (int t = threadIdx.x; t < 3 * nat; t += blockDim.x) {
+    double l = 0.0;
+    for (int b = 0; b < nblk; ++b) l += floc[(size_t)b * 3 * nat + t];
     fnl_part[t] = fnl[t];
-    force[t] = floc[t] + fnl[t] + few[t];
+    force[t] = l + fnl[t] + few[t];
   }
 }
 
@@ -763,9 +765,9 @@ void kpt_force_nl(hipStream_t s, const zc* P, const zc* dP, int nproj, int nb, c
   check_launch("k_kpt_force_nl");
 }
 
-void kpt_force_total(hipStream_t s, const double* floc, const double* fnl, const double* few, int nat,
-                     double* force, double* fnl_part) {
-  hipLaunchKernelGGL(k_kpt_force_total, dim3(1), dim3(256), 0, s, floc, fnl, few, nat, force, fnl_part);
+void kpt_force_total(hipStream_t s, const double* floc, int nblk, const double* fnl, const double* few,
+                     int nat, double* force, double* fnl_part) {
+  hipLaunchKernelGGL(k_kpt_force_total, dim3(1), dim3(256), 0, s, floc, nblk, fnl, few, nat, force, fnl_part);
   check_launch("k_kpt_force_total");
 }
 

@@ -50,7 +50,9 @@ struct BatchGeom {
   int nkc_max;       // number of K ranges
   int dens_chunks;   // band-pair chunks of the density planes
   int ew_ng_max;     // reciprocal Ewald vectors enumerated (box size)
-  int ew_nimg_max;
+  int phase_max;         // phase factors of one candidate
+  int setup_max;         // threads of the grid setup
+  int nagroup_max, force_blocks_max;  // local forces: atom groups, blocks per group
   int sub_threads;   // threads of the LDS-resident subspace solver
   int jac_grid = kJacGridBandsDefault;  // band count from which the subspace solve runs over the GPU
   int plane_group = 1;  // z-planes per workgroup of the H psi plane kernel (1: one per wavefront)
@@ -173,8 +175,8 @@ void kpt_density(hipStream_t s, const cplx<double>* zk, const double* occ, doubl
 void kpt_force_nl(hipStream_t s, const cplx<double>* P, const cplx<double>* dP, int nproj, int nb,
                   const double* h, const int* patom, const double* occ, double wk, int nat, double* fnl,
                   int first);
-void kpt_force_total(hipStream_t s, const double* floc, const double* fnl, const double* few, int nat,
-                     double* force, double* fnl_part);
+void kpt_force_total(hipStream_t s, const double* floc, int nblk, const double* fnl, const double* few,
+                     int nat, double* force, double* fnl_part);
 void configure_kpt_kernels();
 // BF16-input projector products (FP32_BF16PROJ form).
 void launch_beta_bf16(const LaunchCtx& L);
