@@ -44,6 +44,28 @@ struct FftPlan {
   int radix[kMaxStages];
 };
 
+// Pointer of the descriptor: on the device it is a pointer to global memory
+// (converted where it is used), so the accesses compile to global loads and
+// stores.  As a plain pointer read from memory it could point into LDS as far
+// as the compiler knows: every access was a flat one, which also waits on the
+// LDS counter and which no later load may overtake.
+#ifdef __HIP_DEVICE_COMPILE__
+template <typename T>
+struct GPtr {
+  __attribute__((address_space(1))) T* p;
+  __device__ __forceinline__ operator T*() const { return (T*)p; }
+  template <typename U>  // of the untyped ones
+  __device__ __forceinline__ explicit operator U*() const {
+    return (U*)(T*)p;
+  }
+  GPtr() = default;
+  __host__ __device__ GPtr(T* q) : p((__attribute__((address_space(1))) T*)q) {}
+};
+#else
+template <typename T>
+using GPtr = T*;
+#endif
+
 // Per-candidate device descriptor.  Pointers typed void* hold arrays of the
 // wavefunction precision T (float or double); double* arrays are FP64.
 struct CandDesc {
@@ -59,74 +81,74 @@ struct CandDesc {
   double B[9];
   FftPlan plan[3];  // lengths N1, N2, N3
   // wavefunction side (precision T)
-  void* X;
-  void* HX;
-  void* D;
-  void* HD;
-  void* sticks;   // cplx<T> [npair][N3][nst]
-  void* veff_t;   // T [N3][N2][N1]
-  void* beta;     // T [nproj][K]
-  void* beta16;   // bfloat16 [2][np16][Kp] hi, lo parts (FP32_BF16PROJ form only)
-  void* betaT16;  // bfloat16 [2][Kp][np16]
-  const double* kin;     // [npwh]
-  const int* gmeta;      // [npwh] stick | z << 20
-  const int* sp_off;     // [nsp + 1]
-  const int* stick_xy;   // [nst] i1 | i2 << 16
-  const int* gmill;      // [npwh*3] Miller indices of the half sphere
-  const double* hproj;   // [nproj]
-  const int* proj_atom;  // [nproj]
-  const int* proj_lm;    // [nproj] l*4 + m
-  const double* proj_r;  // [nproj] projector width
+  GPtr<void> X;
+  GPtr<void> HX;
+  GPtr<void> D;
+  GPtr<void> HD;
+  GPtr<void> sticks;   // cplx<T> [npair][N3][nst]
+  GPtr<void> veff_t;   // T [N3][N2][N1]
+  GPtr<void> beta;     // T [nproj][K]
+  GPtr<void> beta16;   // bfloat16 [2][np16][Kp] hi, lo parts (FP32_BF16PROJ form only)
+  GPtr<void> betaT16;  // bfloat16 [2][Kp][np16]
+  GPtr<const double> kin;     // [npwh]
+  GPtr<const int> gmeta;      // [npwh] stick | z << 20
+  GPtr<const int> sp_off;     // [nsp + 1]
+  GPtr<const int> stick_xy;   // [nst] i1 | i2 << 16
+  GPtr<const int> gmill;      // [npwh*3] Miller indices of the half sphere
+  GPtr<const double> hproj;   // [nproj]
+  GPtr<const int> proj_atom;  // [nproj]
+  GPtr<const int> proj_lm;    // [nproj] l*4 + m
+  GPtr<const double> proj_r;  // [nproj] projector width
   // subspace (FP64)
-  double* S;       // [nb*nb]
-  double* Hs;      // [nb*nb]
-  double* M;       // [nb*nb]
-  double* C;       // [max(nb,nproj)*nb] general product
-  double* eps;     // [nb]
-  double* occ;     // [nb]
-  double* gam;     // [nb]  gamma of the previous CG step
-  double* bandw;   // [nb]  per-band scratch
-  double* resn;    // [nb]  |H psi - eps psi|^2 of each band at the last CG direction
+  GPtr<double> S;       // [nb*nb]
+  GPtr<double> Hs;      // [nb*nb]
+  GPtr<double> M;       // [nb*nb]
+  GPtr<double> C;       // [max(nb,nproj)*nb] general product
+  GPtr<double> eps;     // [nb]
+  GPtr<double> occ;     // [nb]
+  GPtr<double> gam;     // [nb]  gamma of the previous CG step
+  GPtr<double> bandw;   // [nb]  per-band scratch
+  GPtr<double> resn;    // [nb]  |H psi - eps psi|^2 of each band at the last CG direction
   // grid side (FP64)
-  double* rho_in_r;     // [ntot]
-  double* rho_out_r;    // [ntot]
-  double* veff_r;       // [ntot]
-  cplx<double>* zgrid;  // [ntot] FFT work
-  cplx<double>* vloc_G; // [ntot] on D, zero elsewhere
-  cplx<double>* rho0_G; // [ntot]
-  cplx<double>* rho_out_G;  // [ntot]
-  void* hist_in;            // [kMaxHist][ntot] complex, FP64 or FP32 (hist_f32)
-  void* hist_res;           // [kMaxHist][ntot]
-  double* pulay;        // [kMaxHist*kMaxHist] residual dot products
-  double* coef;         // [kMaxHist]
-  double* dens_part;    // [nchunk][ntot]
+  GPtr<double> rho_in_r;     // [ntot]
+  GPtr<double> rho_out_r;    // [ntot]
+  GPtr<double> veff_r;       // [ntot]
+  GPtr<cplx<double>> zgrid;  // [ntot] FFT work
+  GPtr<cplx<double>> vloc_G; // [ntot] on D, zero elsewhere
+  GPtr<cplx<double>> rho0_G; // [ntot]
+  GPtr<cplx<double>> rho_out_G;  // [ntot]
+  GPtr<void> hist_in;            // [kMaxHist][ntot] complex, FP64 or FP32 (hist_f32)
+  GPtr<void> hist_res;           // [kMaxHist][ntot]
+  GPtr<double> pulay;        // [kMaxHist*kMaxHist] residual dot products
+  GPtr<double> coef;         // [kMaxHist]
+  GPtr<double> dens_part;    // [nchunk][ntot]
   int ndens_chunk;
   int hist_len;         // history capacity in use
   int hist_f32;         // Pulay history stored as complex FP32 (FP32 bulk forms)
   // atoms (FP64)
-  const double* pos;    // [nat*3]
-  const int* spec;      // [nat]
+  GPtr<const double> pos;    // [nat*3]
+  GPtr<const int> spec;      // [nat]
   // phase factors e^{i m b_a.R_I}, m >= 0: phase[(I * 3 + a) * phase_m + m]
-  cplx<double>* phase;
+  GPtr<cplx<double>> phase;
   int phase_m;          // entries per atom and axis: max(N_a / 2, ew_m[a]) + 1
   int nagroup;          // atom groups: at most kAtomGroup atoms of one species
-  const int* agroup;    // [nagroup * kAtomGroup] atom indices, -1 past a group's end
-  double* force;        // [nat*3] total
-  double* force_ew;     // [nat*3]
-  double* force_part;   // [nat*3*4] local / nonlocal scratch
-  double* nlwork;       // [nproj*nb*4]
-  double* stwork;       // stress partial sums, layout in stress_layout()
-  double* stress;       // [9] total, then [6][9] parts (kin, nl, H, loc, xc, Ewald)
-  double* scal;         // [S_COUNT]
-  cplx<double>* ewS;    // [ew_ng] Ewald structure factors
+  GPtr<const int> agroup;    // [nagroup * kAtomGroup] atom indices, -1 past a group's end
+  GPtr<double> force;        // [nat*3] total
+  GPtr<double> force_ew;     // [nat*3]
+  GPtr<double> force_part;   // [nat*3*4] local / nonlocal scratch
+  GPtr<double> nlwork;       // [nproj*nb*4]
+  GPtr<double> stwork;       // stress partial sums, layout in stress_layout()
+  GPtr<double> stress;       // [9] total, then [6][9] parts (kin, nl, H, loc, xc, Ewald)
+  GPtr<double> scal;         // [S_COUNT]
+  GPtr<cplx<double>> ewS;    // [ew_ng] Ewald structure factors
   double ew_eta, ew_rcut, ew_gcut, pad2;
   int ew_m[3], ew_n[3];  // reciprocal / image enumeration half-widths
   int ew_ng, ew_nimg;
-  long long* dbg_clk;   // optional phase timestamps of the subspace solver
-  int* iter_state;      // SCF iteration counter of the batch (device memory)
+  GPtr<long long> dbg_clk;   // optional phase timestamps of the subspace solver
+  GPtr<int> iter_state;      // SCF iteration counter of the batch (device memory)
   // reduction scratch: partial sums and tickets (zeroed at allocation)
-  double* red_part;     // [kRedSlots]
-  unsigned* tickets;    // [kTickets]
+  GPtr<double> red_part;     // [kRedSlots]
+  GPtr<unsigned> tickets;    // [kTickets]
   unsigned seed;
   int pad1;
 };

@@ -12,6 +12,27 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Sum 64 values over the wavefront, the total of value l left in lane l: each
+// step halves the values a lane holds, 63 exchanges instead of 64 x 6.
+template <int O>
+__device__ __forceinline__ void wave_fold(double (&v)[64]) {
+  const bool up = (threadIdx.x & O) != 0;
+#pragma unroll
+  for (int j = 0; j < O; ++j) {
+    const double keep = up ? v[j + O] : v[j], send = up ? v[j] : v[j + O];
+    v[j] = keep + __shfl_xor(send, O, 64);
+  }
+}
+__device__ __forceinline__ double wave_sum64(double (&v)[64]) {
+  wave_fold<32>(v);
+  wave_fold<16>(v);
+  wave_fold<8>(v);
+  wave_fold<4>(v);
+  wave_fold<2>(v);
+  wave_fold<1>(v);
+  return v[0];
+}
+
 // Sum N values over the block; every thread receives the totals.  The order
 // of additions is fixed by the thread layout, so results are reproducible.
 // sh must hold 16*N doubles.

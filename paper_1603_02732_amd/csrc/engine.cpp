@@ -559,11 +559,11 @@ class Engine {
     CandDesc& d = c.d;
     std::memset(&d, 0, sizeof(d));
     std::vector<Item> items = {
-        {&d.X, nb * K * ts}, {&d.HX, nb * K * ts}, {&d.D, nb * K * ts}, {&d.HD, nb * K * ts},
-        {&d.sticks, (size_t)c.npair * c.N[2] * c.nst * 2 * ts}, {&d.veff_t, nt * ts},
-        {&d.beta, (size_t)c.nproj * K * ts + 256},
-        {&d.beta16, prec_ == SGO_FP32_BF16PROJ ? (size_t)2 * np16 * K * 2 + 256 : 0},
-        {&d.betaT16, prec_ == SGO_FP32_BF16PROJ ? (size_t)2 * np16 * K * 2 + 256 : 0},
+        {(void**)&d.X, nb * K * ts}, {(void**)&d.HX, nb * K * ts}, {(void**)&d.D, nb * K * ts}, {(void**)&d.HD, nb * K * ts},
+        {(void**)&d.sticks, (size_t)c.npair * c.N[2] * c.nst * 2 * ts}, {(void**)&d.veff_t, nt * ts},
+        {(void**)&d.beta, (size_t)c.nproj * K * ts + 256},
+        {(void**)&d.beta16, prec_ == SGO_FP32_BF16PROJ ? (size_t)2 * np16 * K * 2 + 256 : 0},
+        {(void**)&d.betaT16, prec_ == SGO_FP32_BF16PROJ ? (size_t)2 * np16 * K * 2 + 256 : 0},
         {(void**)&d.kin, c.npwh * sizeof(double)}, {(void**)&d.gmeta, c.npwh * sizeof(int)},
         {(void**)&d.sp_off, (c.nsp + 1) * sizeof(int)}, {(void**)&d.stick_xy, c.nst * sizeof(int)},
         {(void**)&d.gmill, 3 * c.npwh * sizeof(int)},
