@@ -1138,17 +1138,12 @@ class Engine {
   struct KPt {
     double kf[3] = {0, 0, 0};
     double w = 0;
-    int npw = 0;
-    char* mem = nullptr;
-    KptBands kb{};
-    cplx<double>*X = nullptr, *HX = nullptr, *D = nullptr, *HD = nullptr;
   };
   std::vector<KPt> kpts_;
-  char* kshared_ = nullptr;
-  cplx<double>*kz_ = nullptr, *kS_ = nullptr, *kH_ = nullptr, *kW_ = nullptr, *kV_ = nullptr,
-              *kM_ = nullptr, *kC_ = nullptr, *kP_ = nullptr, *kdP_ = nullptr, *ktmp_ = nullptr;
-  double *keps_ = nullptr, *kocc_ = nullptr, *kgam_ = nullptr, *kbandw_ = nullptr, *kw_ = nullptr,
-         *kfnl_ = nullptr;
+  char* kmem_ = nullptr;  // one arena for all k-points, kept while it is large enough
+  size_t kmem_bytes_ = 0;
+  KptSet kset_{};
+  double *keps_ = nullptr, *kocc_ = nullptr, *kbandw_ = nullptr, *kw_ = nullptr;
   int* kfail_ = nullptr;
   int k_nb_ = 0;
   bool k_solved_ = false;
@@ -1157,13 +1152,9 @@ class Engine {
   int nkpts() const { return (int)kpts_.size(); }
 
   void k_free() {
-    for (auto& k : kpts_)
-      if (k.mem) {
-        (void)hipFree(k.mem);
-        k.mem = nullptr;
-      }
-    if (kshared_) (void)hipFree(kshared_);
-    kshared_ = nullptr;
+    if (kmem_) (void)hipFree(kmem_);
+    kmem_ = nullptr;
+    kmem_bytes_ = 0;
     k_nb_ = 0;
   }
 
@@ -1191,17 +1182,18 @@ class Engine {
   }
 
   // Host basis of every k (shifted sphere, grid indices, |k+G|^2/2, k+G)
-  // and the device arrays: per k the basis, projectors and bands; shared
-  // FFT grids, subspace matrices and per-(k, band) scalars.
+  // and the device arrays, in one arena: per k the basis, projectors, bands
+  // and subspace matrices; per (k, band) the scalars; the grids of a chunk of
+  // k-points (grids too large for LDS) or the partial densities.
   void k_build(HostCand& c) {
-    k_free();
+    k_nb_ = 0;
     const int nb = c.nb, nproj = c.nproj, nk = nkpts();
     const double gmax = std::sqrt(2.0 * c.ecut);
     int npw_max = 0;
     std::vector<std::vector<int>> boxes(nk);
     std::vector<std::vector<double>> kins(nk), qs(nk);
     for (int ik = 0; ik < nk; ++ik) {
-      KPt& k = kpts_[ik];
+      const KPt& k = kpts_[ik];
       int mmax[3];
       for (int i = 0; i < 3; ++i) {
         const double an = std::sqrt(c.A[3 * i] * c.A[3 * i] + c.A[3 * i + 1] * c.A[3 * i + 1] +
@@ -1226,109 +1218,128 @@ class Engine {
             kins[ik].push_back(0.5 * q2);
             for (int a = 0; a < 3; ++a) qs[ik].push_back(q[a]);
           }
-      k.npw = (int)boxes[ik].size();
-      if (k.npw < nb) throw Error(SGO_EINVAL, "fewer plane waves than bands at a k-point");
-      npw_max = std::max(npw_max, k.npw);
+      const int npw = (int)boxes[ik].size();
+      if (npw < nb) throw Error(SGO_EINVAL, "fewer plane waves than bands at a k-point");
+      npw_max = std::max(npw_max, npw);
     }
-    auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t zc = sizeof(cplx<double>);
-    for (int ik = 0; ik < nk; ++ik) {
-      KPt& k = kpts_[ik];
-      const size_t n = k.npw;
-      const size_t bytes = al(n * 4) + al(n * 8) + al(n * 24) + al((size_t)nproj * n * zc) + 4 * al((size_t)nb * n * zc);
-      HIPCHK(hipMalloc(&k.mem, bytes));
-      char* p = k.mem;
-      int* box = (int*)p;
-      p += al(n * 4);
-      double* kin = (double*)p;
-      p += al(n * 8);
-      double* q = (double*)p;
-      p += al(n * 24);
-      k.kb.beta = (cplx<double>*)p;
-      p += al((size_t)nproj * n * zc);
-      k.X = (cplx<double>*)p;
-      p += al((size_t)nb * n * zc);
-      k.HX = (cplx<double>*)p;
-      p += al((size_t)nb * n * zc);
-      k.D = (cplx<double>*)p;
-      p += al((size_t)nb * n * zc);
-      k.HD = (cplx<double>*)p;
-      HIPCHK(hipMemcpy(box, boxes[ik].data(), n * 4, hipMemcpyHostToDevice));
-      HIPCHK(hipMemcpy(kin, kins[ik].data(), n * 8, hipMemcpyHostToDevice));
-      HIPCHK(hipMemcpy(q, qs[ik].data(), n * 24, hipMemcpyHostToDevice));
-      k.kb.npw = k.npw;
-      k.kb.nb = nb;
-      k.kb.nproj = nproj;
-      k.kb.box = box;
-      k.kb.kin = kin;
-      k.kb.q = q;
-    }
     const size_t nbb = (size_t)nb * nb, nkb = (size_t)nk * nb;
-    const size_t pw = std::max<size_t>(nproj, 1) * nb;
-    const size_t bytes = al((size_t)nb * c.ntot * zc) + 6 * al(nbb * zc) + al(pw * zc) + al(3 * pw * zc) +
-                         al((size_t)nb * npw_max * zc) + 4 * al(nkb * 8) + al((size_t)nk * 8) +
-                         al((size_t)3 * c.nat * 8) + al(8);
-    HIPCHK(hipMalloc(&kshared_, bytes));
-    char* p = kshared_;
+    const size_t pw = (size_t)std::max(nproj, 1) * nb;
+    KptSet K{};
+    K.stream = stream_;
+    K.nk = nk;
+    K.nb = nb;
+    K.nproj = nproj;
+    K.npw_max = npw_max;
+    K.ntot = c.ntot;
+    for (int a = 0; a < 3; ++a) K.N[a] = c.N[a];
+    K.plans = c.plan;
+    K.lds_class = kpt_lds_class(c.N, (size_t)g_lds_limit);
+    // grids of as many k-points at a time as 4 GB hold (at least one); partial
+    // densities of enough blocks to fill the chip
+    const size_t grids = (size_t)nb * c.ntot * zc;
+    K.kchunk = (int)std::max<size_t>(1, std::min<size_t>(nk, (size_t)4e9 / grids));
+    K.nchunk = std::max(1, std::min(nb, 512 / nk));
+    // the arena: what the host fills first (copied in one piece), then the rest
+    std::vector<KptDev> dev(nk);
+    std::vector<char> up;
+    char* base = nullptr;
+    size_t at = 0;
     auto take = [&](size_t b) {
-      char* r = p;
-      p += al(b);
+      char* r = base + at;
+      at += (b + 255) / 256 * 256;
       return r;
     };
-    kz_ = (cplx<double>*)take((size_t)nb * c.ntot * zc);
-    kS_ = (cplx<double>*)take(nbb * zc);
-    kH_ = (cplx<double>*)take(nbb * zc);
-    kW_ = (cplx<double>*)take(nbb * zc);
-    kV_ = (cplx<double>*)take(nbb * zc);
-    kM_ = (cplx<double>*)take(nbb * zc);
-    kC_ = (cplx<double>*)take(nbb * zc);
-    kP_ = (cplx<double>*)take(pw * zc);
-    kdP_ = (cplx<double>*)take(3 * pw * zc);
-    ktmp_ = (cplx<double>*)take((size_t)nb * npw_max * zc);
-    keps_ = (double*)take(nkb * 8);
-    kocc_ = (double*)take(nkb * 8);
-    kgam_ = (double*)take(nkb * 8);
-    kbandw_ = (double*)take(nkb * 8);
-    kw_ = (double*)take((size_t)nk * 8);
-    kfnl_ = (double*)take((size_t)3 * c.nat * 8);
-    kfail_ = (int*)take(8);
-    std::vector<double> w(nk);
-    for (int ik = 0; ik < nk; ++ik) w[ik] = kpts_[ik].w;
-    HIPCHK(hipMemcpy(kw_, w.data(), nk * 8, hipMemcpyHostToDevice));
-    HIPCHK(hipMemset(kfail_, 0, 8));
-    k_nb_ = nb;
-  }
-
-  // Rayleigh-Ritz of one k: S = X^H X, H = X^H HX, Cholesky and complex
-  // Jacobi (k_kpt_subspace), then X, HX (and D) <- . M
-  void k_rr(const HostCand& c, KPt& k, double* eps, bool with_d) {
-    const int nb = c.nb, npw = k.npw;
-    kpt_zdot(stream_, k.X, nb, k.X, nb, npw, kS_, nb, nullptr, 0);
-    kpt_zdot(stream_, k.X, nb, k.HX, nb, npw, kH_, nb, nullptr, 0);
-    kpt_subspace(stream_, kS_, kH_, kW_, kV_, kM_, eps, nb, 3, kfail_);
-    cplx<double>* arr[3] = {k.X, k.HX, k.D};
-    for (int a = 0; a < (with_d ? 3 : 2); ++a) {
-      kpt_zgemm(stream_, arr[a], nb, kM_, nb, ktmp_, nb, npw, 1.0, 0.0, nullptr);
-      kpt_copy(stream_, arr[a], ktmp_, (long)nb * npw);
+    size_t nup = 0;
+    auto layout = [&] {
+      at = 0;
+      K.dev = (const KptDev*)take(nk * sizeof(KptDev));
+      kw_ = (double*)take((size_t)nk * 8);
+      kfail_ = (int*)take(8);
+      for (int ik = 0; ik < nk; ++ik) {
+        const size_t n = boxes[ik].size();
+        KptDev& k = dev[ik];
+        k.npw = (int)n;
+        k.nb = nb;
+        k.nproj = nproj;
+        k.w = kpts_[ik].w;
+        k.box = (const int*)take(n * 4);
+        k.kin = (const double*)take(n * 8);
+        k.q = (const double*)take(n * 24);
+      }
+      nup = at;
+      keps_ = (double*)take(nkb * 8);
+      kocc_ = (double*)take(nkb * 8);
+      kbandw_ = (double*)take(nkb * 8);
+      double* gam = (double*)take(nkb * 8);
+      for (int ik = 0; ik < nk; ++ik) {
+        KptDev& k = dev[ik];
+        const size_t n = k.npw;
+        k.eps = keps_ + (size_t)ik * nb;
+        k.occ = kocc_ + (size_t)ik * nb;
+        k.bandw = kbandw_ + (size_t)ik * nb;
+        k.gam = gam + (size_t)ik * nb;
+        k.beta = (cplx<double>*)take((size_t)nproj * n * zc);
+        k.X = (cplx<double>*)take(nb * n * zc);
+        k.HX = (cplx<double>*)take(nb * n * zc);
+        k.D = (cplx<double>*)take(nb * n * zc);
+        k.HD = (cplx<double>*)take(nb * n * zc);
+        k.S = (cplx<double>*)take(nbb * zc);
+        k.H = (cplx<double>*)take(nbb * zc);
+        k.W = (cplx<double>*)take(nbb * zc);
+        k.V = (cplx<double>*)take(nbb * zc);
+        k.M = (cplx<double>*)take(nbb * zc);
+        k.C = (cplx<double>*)take(nbb * zc);
+        k.P = (cplx<double>*)take(pw * zc);
+        k.dP = (cplx<double>*)take(3 * pw * zc);
+      }
+      if (K.lds_class) K.dpart = (double*)take((size_t)nk * K.nchunk * c.ntot * 8);
+      else K.z = (cplx<double>*)take(K.kchunk * grids);
+    };
+    layout();
+    if (kmem_bytes_ < at) {
+      k_free();
+      HIPCHK(hipMalloc(&kmem_, at));
+      kmem_bytes_ = at;
     }
+    base = kmem_;
+    layout();
+    up.assign(nup, 0);  // the failure flag starts at 0
+    auto put = [&](const void* dst, const void* src, size_t b) { std::memcpy(up.data() + ((const char*)dst - base), src, b); };
+    put(K.dev, dev.data(), nk * sizeof(KptDev));
+    for (int ik = 0; ik < nk; ++ik) {
+      put(kw_ + ik, &kpts_[ik].w, 8);
+      put((const int*)dev[ik].box, boxes[ik].data(), boxes[ik].size() * 4);
+      put((const double*)dev[ik].kin, kins[ik].data(), kins[ik].size() * 8);
+      put((const double*)dev[ik].q, qs[ik].data(), qs[ik].size() * 8);
+    }
+    HIPCHK(hipStreamSynchronize(stream_));  // a solve that threw may still be using the arena
+    HIPCHK(hipMemcpy(kmem_, up.data(), nup, hipMemcpyHostToDevice));
+    k_nb_ = nb;
+    kset_ = K;
   }
 
-  // Algorithm 1 at one k: H psi, subspace diagonalisation, then ncg steps
+  // Rayleigh-Ritz: S = X^H X, H = X^H HX, Cholesky and complex Jacobi, then X,
+  // HX (and D) <- . M, at every k
+  void k_rr(bool with_d) {
+    kpt_zdot(kset_, 2, {W_X, W_X, 0}, {W_X, W_HX, 1});
+    kpt_subspace(kset_, kfail_);
+    kpt_zgemm(kset_, -1, W_X | W_HX << 4 | W_D << 8, with_d ? 3 : 2, 0, 1.0, 0.0, nullptr);
+  }
+
+  // Algorithm 1 at every k: H psi, subspace diagonalisation, then ncg steps
   // of residual, preconditioning, projection, line minimisation and
   // Rayleigh-Ritz.
-  void k_eigensolve(const HostCand& c, int ik, int ncg) {
-    KPt& k = kpts_[ik];
-    double* eps = keps_ + (size_t)ik * c.nb;
-    double* gam = kgam_ + (size_t)ik * c.nb;
-    kpt_hpsi(stream_, k.kb, k.X, k.HX, kz_, c.d.veff_r, c.N, c.plan, kP_, c.d.hproj);
-    k_rr(c, k, eps, false);
+  void k_eigensolve(const HostCand& c, int ncg) {
+    kpt_hpsi(kset_, W_X, W_HX, c.d.veff_r, c.d.hproj);
+    k_rr(false);
     for (int st = 0; st < ncg; ++st) {
-      kpt_cg_dir(stream_, k.kb, k.X, k.HX, k.D, eps, gam, st == 0 ? 1 : 0);
-      kpt_zdot(stream_, k.X, c.nb, k.D, c.nb, k.npw, kC_, c.nb, nullptr, 0);
-      kpt_zgemm(stream_, k.X, c.nb, kC_, c.nb, k.D, c.nb, k.npw, -1.0, 1.0, nullptr);
-      kpt_hpsi(stream_, k.kb, k.D, k.HD, kz_, c.d.veff_r, c.N, c.plan, kP_, c.d.hproj);
-      kpt_linemin(stream_, k.kb, k.X, k.HX, k.D, k.HD);
-      k_rr(c, k, eps, true);
+      kpt_cg_dir(kset_, st == 0 ? 1 : 0);
+      kpt_zdot(kset_, 1, {W_X, W_D, 2}, {});
+      kpt_zgemm(kset_, W_X, W_D, 1, 1, -1.0, 1.0, nullptr);
+      kpt_hpsi(kset_, W_D, W_HD, c.d.veff_r, c.d.hproj);
+      kpt_linemin(kset_);
+      k_rr(true);
     }
   }
 
@@ -1336,28 +1347,15 @@ class Engine {
   // one chemical potential, the k-weighted density into the structure's
   // density chunk, then the Gamma path's density, residual and control.
   void k_iteration(const LaunchCtx& L, HostCand& c, const sgo_scf_opts& o, int ncg) {
-    const int nk = nkpts(), nb = c.nb;
-    for (int ik = 0; ik < nk; ++ik) k_eigensolve(c, ik, ncg);
-    kpt_occupations(stream_, keps_, kw_, nk, nb, c.nelec, c.occ_kind, c.sigma, kocc_, c.d.scal);
-    for (int ik = 0; ik < nk; ++ik) kpt_band_kinetic(stream_, kpts_[ik].kb, kpts_[ik].X, kbandw_ + (size_t)ik * nb);
-    kpt_kinetic_total(stream_, kbandw_, kocc_, kw_, nk, nb, c.d.occ, c.d.bandw, c.nb);
-    for (int ik = 0; ik < nk; ++ik) {
-      KPt& k = kpts_[ik];
-      kpt_zero(stream_, kz_, (long)nb * c.ntot);
-      k_density_grid(c, k);
-      kpt_density(stream_, kz_, kocc_ + (size_t)ik * nb, k.w, nb, c.ntot, c.d.dens_part, ik == 0 ? 1 : 0);
-    }
+    k_eigensolve(c, ncg);
+    kpt_occupations(stream_, keps_, kw_, nkpts(), c.nb, c.nelec, c.occ_kind, c.sigma, kocc_, c.d.scal);
+    kpt_kinetic(kset_, kbandw_, kocc_, kw_, c.d.occ, c.d.bandw, c.nb);
+    kpt_density(kset_, c.d.dens_part);
     launch_density_finalize(L);
     launch_grid_fft(L, -1);
     launch_gspace_residual(L);
     launch_scf_control(L, o.tol_e, o.tol_rho, 0.0);
     launch_iter_set(L, d_iter_, 1, 1);
-  }
-
-  // u_n(r) of every band of k on the grid (kz_)
-  void k_density_grid(const HostCand& c, KPt& k) {
-    kpt_scatter_bands(stream_, kz_, k.X, k.kb, c.ntot);
-    kpt_fft3(stream_, kz_, c.nb, c.N, c.plan, +1);
   }
 
   int scf_k(const sgo_scf_opts& o) {
@@ -1369,7 +1367,7 @@ class Engine {
     launch_iter_set(L, d_iter_, 0, 0);
     setup_geometry<double>(L);
     k_build(c);
-    for (auto& k : kpts_) kpt_beta(stream_, k.kb, c.d.proj_atom, c.d.proj_lm, c.d.proj_r, c.d.pos, c.omega);
+    kpt_beta(kset_, c.d.proj_atom, c.d.proj_lm, c.d.proj_r, c.d.pos, c.omega);
     // the k density goes into the structure's first density chunk
     c.d.ndens_chunk = 1;
     upload_desc();
@@ -1377,10 +1375,7 @@ class Engine {
       HostCand& c;
       ~RestoreChunks() { c.d.ndens_chunk = c.dens_chunks; }
     } restore{c};
-    for (int ik = 0; ik < nkpts(); ++ik) {
-      KPt& k = kpts_[ik];
-      kpt_init(stream_, k.kb, k.X, o.seed, ik);
-    }
+    kpt_init(kset_, o.seed);
     launch_mix(L, 1, o.mix_alpha, o.kerker_q0);
     launch_grid_fft(L, +1);
     launch_potential_finalize<double>(L);
@@ -1404,19 +1399,8 @@ class Engine {
     upload_desc();
     // forces: local (from rho) + nonlocal at every k + Ewald
     launch_force_local(L);
-    for (int ik = 0; ik < nkpts(); ++ik) {
-      KPt& k = kpts_[ik];
-      if (c.nproj > 0) {
-        kpt_zdot(stream_, k.kb.beta, c.nproj, k.X, c.nb, k.npw, kP_, c.nb, nullptr, 0);
-        for (int a = 0; a < 3; ++a)
-          kpt_zdot(stream_, k.kb.beta, c.nproj, k.X, c.nb, k.npw, kdP_ + (size_t)a * c.nproj * c.nb, c.nb,
-                   k.kb.q, a);
-      }
-      kpt_force_nl(stream_, kP_, kdP_, c.nproj, c.nb, c.d.hproj, c.d.proj_atom, kocc_ + (size_t)ik * c.nb,
-                   k.w, c.nat, kfnl_, ik == 0 ? 1 : 0);
-    }
-    kpt_force_total(stream_, c.d.red_part, force_blocks(c.N[0], c.N[1], c.N[2]), kfnl_, c.d.force_ew, c.nat,
-                    c.d.force, c.d.force_part + 3 * c.nat);
+    kpt_force(kset_, c.d.hproj, c.d.proj_atom, c.d.red_part, force_blocks(c.N[0], c.N[1], c.N[2]), c.d.force_ew,
+              c.nat, c.d.force, c.d.force_part + 3 * c.nat);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(stream_));
     c.have_psi = false;  // the Gamma bands were not solved

@@ -139,44 +139,70 @@ void launch_z_forward_reg(const LaunchCtx& L, int src, int dst);
 void configure_plane_kernels();
 // ---- k-point sampling (kernels_kpt.hip): complex bands on the shifted
 // sphere |k+G|^2/2 <= Ecut of one k-point, FP64
-struct KptBands {
-  int npw, nb, nproj;
-  const int* box;        // [npw] index of each coefficient in the [N3][N2][N1] grid
-  const double* kin;     // [npw] |k+G|^2 / 2
-  const double* q;       // [npw][3] k + G (Cartesian, bohr^-1)
-  cplx<double>* beta;    // [nproj][npw] projectors at k + G
+// Device descriptor of one k-point.
+struct KptDev {
+  int npw, nb, nproj, pad;
+  double w;                  // weight
+  GPtr<const int> box;       // [npw] index of each coefficient in the [N3][N2][N1] grid
+  GPtr<const double> kin;    // [npw] |k+G|^2 / 2
+  GPtr<const double> q;      // [npw][3] k + G (Cartesian, bohr^-1)
+  GPtr<cplx<double>> beta;   // [nproj][npw] projectors at k + G
+  GPtr<cplx<double>> X;      // bands [nb][npw], H X, directions, H D
+  GPtr<cplx<double>> HX;
+  GPtr<cplx<double>> D;
+  GPtr<cplx<double>> HD;
+  GPtr<cplx<double>> S;      // [nb][nb] subspace matrices
+  GPtr<cplx<double>> H;
+  GPtr<cplx<double>> W;
+  GPtr<cplx<double>> V;
+  GPtr<cplx<double>> M;
+  GPtr<cplx<double>> C;
+  GPtr<cplx<double>> P;      // [nproj][nb] projections, [3][nproj][nb] their derivatives
+  GPtr<cplx<double>> dP;
+  GPtr<double> eps;          // [nb]
+  GPtr<double> occ;
+  GPtr<double> gam;
+  GPtr<double> bandw;
 };
+// All k-points of a structure: every launch covers them.
+struct KptSet {
+  hipStream_t stream;
+  const KptDev* dev;         // device array [nk]
+  int nk, nb, nproj, npw_max;
+  int N[3];
+  long ntot;
+  const FftPlan* plans;
+  int lds_class;             // kpt_lds_class of the grid
+  cplx<double>* z;           // [kchunk][nb][ntot] grids (lds_class 0)
+  int kchunk;
+  double* dpart;             // [nk][nchunk][ntot] density parts (lds_class > 0)
+  int nchunk;
+};
+// conj(a) . b into matrix out: 0 S, 1 H, 2 C, 3 P (a = W_BETA)
+struct KptProduct {
+  int a, b, out;
+};
+int kpt_lds_class(const int N[3], size_t lds_limit);
 void kpt_zero(hipStream_t s, cplx<double>* a, long n);
-void kpt_scatter_bands(hipStream_t s, cplx<double>* zk, const cplx<double>* X, const KptBands& kb, long ntot);
-void kpt_fft3(hipStream_t s, cplx<double>* zk, int nb, const int N[3], const FftPlan* plans, int sign);
-void kpt_hpsi(hipStream_t s, const KptBands& kb, const cplx<double>* X, cplx<double>* Y, cplx<double>* zk,
-              const double* veff, const int N[3], const FftPlan* plans, cplx<double>* P, const double* h);
-void kpt_zdot(hipStream_t s, const cplx<double>* A, int na, const cplx<double>* B, int nbb, int npw,
-              cplx<double>* C, int ldc, const double* q, int qa);
-void kpt_zgemm(hipStream_t s, const cplx<double>* X, int nx, const cplx<double>* M, int ldm, cplx<double>* Y,
-               int ny, int npw, double alpha, double beta, const double* h);
-void kpt_copy(hipStream_t s, cplx<double>* dst, const cplx<double>* src, long n);
-void kpt_beta(hipStream_t s, const KptBands& kb, const int* patom, const int* plm, const double* pr,
-              const double* pos, double omega);
-void kpt_subspace(hipStream_t s, cplx<double>* S, cplx<double>* H, cplx<double>* W, cplx<double>* V,
-                  cplx<double>* M, double* eps, int n, int mode, int* fail);
-void kpt_cg_dir(hipStream_t s, const KptBands& kb, const cplx<double>* X, const cplx<double>* HX,
-                cplx<double>* D, const double* eps, double* gam, int first);
-void kpt_linemin(hipStream_t s, const KptBands& kb, cplx<double>* X, cplx<double>* HX,
-                 const cplx<double>* D, const cplx<double>* HD);
-void kpt_init(hipStream_t s, const KptBands& kb, cplx<double>* X, unsigned seed, int kidx);
+void kpt_hpsi(const KptSet& K, int src, int dst, const double* veff, const double* h);
+void kpt_zdot(const KptSet& K, int nprod, KptProduct p0, KptProduct p1);
+// dst <- beta dst + alpha src . mat (0 M, 1 C, 2 P) for the narr arrays `which`
+// (four bits each); src < 0: the array itself
+void kpt_zgemm(const KptSet& K, int src, int which, int narr, int mat, double alpha, double beta,
+               const double* h);
+void kpt_beta(const KptSet& K, const int* patom, const int* plm, const double* pr, const double* pos,
+              double omega);
+void kpt_subspace(const KptSet& K, int* fail);
+void kpt_cg_dir(const KptSet& K, int first);
+void kpt_linemin(const KptSet& K);
+void kpt_init(const KptSet& K, unsigned seed);
 void kpt_occupations(hipStream_t s, const double* eps, const double* wk, int nk, int nb, double nelec,
                      int kind, double sigma, double* occ, double* scal);
-void kpt_band_kinetic(hipStream_t s, const KptBands& kb, const cplx<double>* X, double* out);
-void kpt_kinetic_total(hipStream_t s, const double* bandw_k, const double* occ_k, const double* wk, int nk,
-                       int nb, double* occ_s, double* bandw_s, int nb_s);
-void kpt_density(hipStream_t s, const cplx<double>* zk, const double* occ, double wk, int nb, long ntot,
-                 double* dens, int first);
-void kpt_force_nl(hipStream_t s, const cplx<double>* P, const cplx<double>* dP, int nproj, int nb,
-                  const double* h, const int* patom, const double* occ, double wk, int nat, double* fnl,
-                  int first);
-void kpt_force_total(hipStream_t s, const double* floc, int nblk, const double* fnl, const double* few,
-                     int nat, double* force, double* fnl_part);
+void kpt_kinetic(const KptSet& K, const double* bandw_k, const double* occ_k, const double* wk, double* occ_s,
+                 double* bandw_s, int nb_s);
+void kpt_density(const KptSet& K, double* dens);
+void kpt_force(const KptSet& K, const double* h, const int* patom, const double* floc, int nblk,
+               const double* few, int nat, double* force, double* fnl_part);
 void configure_kpt_kernels();
 // BF16-input projector products (FP32_BF16PROJ form).
 void launch_beta_bf16(const LaunchCtx& L);
