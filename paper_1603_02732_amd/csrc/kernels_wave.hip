@@ -699,72 +699,149 @@ __device__ __forceinline__ double tpa(double x) {
   return p / (p + 16.0 * x * x * x * x);
 }
 
+// The kernels below hold a band per block.  With few bands (4 clusters of 24) a
+// launch is the latency of one block, so a block is as wide as it can be and a
+// thread has kPairs coefficients (16-byte loads in FP64) of every array in flight;
+// a band read twice comes from the L2 the second time.  24 bands x 4 of 12,100
+// values in FP64, direction / line minimisation / kinetic energy: 52 / 49 /
+// 16 us with 256 threads and one value a thread and step, 18 / 20 / 5 us so.
+constexpr int kWideNT = 1024, kPairs = 4;
+// 256 threads where one step of them covers a band: 16 wavefronts' partial sums
+// cost more than they save (20 bands of 1,168 values: line minimisation 8.3 us
+// with 1,024 threads, 5.1 us with 256).
+static int band_threads(const BatchGeom& g) { return g.K_max <= 2 * 256 * kPairs ? 256 : kWideNT; }
+template <typename T>
+struct Pair;
+template <>
+struct Pair<double> { typedef double2 type; };
+template <>
+struct Pair<float> { typedef float2 type; };
+// r[u] = the coefficient p0 + blockDim.x u of a band (0 past the end)
+template <typename T>
+__device__ __forceinline__ void load_pairs(const T* __restrict__ a, int p0, int npwh, double2 (&r)[kPairs]) {
+  typename Pair<T>::type v[kPairs];
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u)
+    v[u] = reinterpret_cast<const typename Pair<T>::type*>(a)[min(p0 + (int)blockDim.x * u, npwh - 1)];
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    const bool in = p0 + (int)blockDim.x * u < npwh;
+    r[u] = make_double2(in ? (double)v[u].x : 0.0, in ? (double)v[u].y : 0.0);
+  }
+}
+template <typename T>
+__device__ __forceinline__ void store_pairs(T* __restrict__ a, int p0, int npwh, const double2 (&r)[kPairs]) {
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u)
+    if (p0 + (int)blockDim.x * u < npwh) {
+      typename Pair<T>::type v;
+      v.x = (T)r[u].x;
+      v.y = (T)r[u].y;
+      reinterpret_cast<typename Pair<T>::type*>(a)[p0 + (int)blockDim.x * u] = v;
+    }
+}
+__device__ __forceinline__ void load_kin(const double* __restrict__ kin, int p0, int npwh, double (&r)[kPairs]) {
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) r[u] = kin[min(p0 + (int)blockDim.x * u, npwh - 1)];
+}
+
 // Residual R = H psi - eps psi, preconditioned g = K R, CG direction
 // D = g + beta D_prev with beta = <g,R>_k / <g,R>_{k-1} (first step: D = g).
 template <typename T>
-__global__ void __launch_bounds__(kNT) k_cg_direction(const CandDesc* __restrict__ cds, int first) {
+__global__ void __launch_bounds__(kWideNT) k_cg_direction(const CandDesc* __restrict__ cds, int first) {
   const CandDesc& cd = cds[blockIdx.z];
   if (!cd.active) return;
   const int i = blockIdx.x;
   if (i >= cd.nb) return;
   __shared__ double sh[16 * 2];
-  const int K = cd.K;
+  const int n = cd.npwh;
   const T* x = (const T*)cd.X + (size_t)i * cd.Kp;
   const T* hx = (const T*)cd.HX + (size_t)i * cd.Kp;
   T* d = (T*)cd.D + (size_t)i * cd.Kp;
+  const double* kin = cd.kin;
+  const double e = cd.eps[i], gp = first ? 0.0 : cd.gam[i];
+  double2 X[kPairs], R[kPairs];
+  double kk[kPairs];
   double v1[1] = {0.0};
-  for (int k = threadIdx.x; k < K; k += blockDim.x) {
-    const double xv = (double)x[k];
-    v1[0] += cd.kin[k >> 1] * xv * xv;
+  for (int p = threadIdx.x; p < n; p += blockDim.x * kPairs) {
+    load_pairs<T>(x, p, n, X);
+    load_kin(kin, p, n, kk);
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) v1[0] += kk[u] * (X[u].x * X[u].x + X[u].y * X[u].y);
   }
   block_sum<1>(v1, sh);
   const double ek = fmax(v1[0], 1e-8);
-  const double e = cd.eps[i];
+  // R and the preconditioner's factors
+  auto residual = [&](int p) {
+    load_pairs<T>(x, p, n, X);
+    load_pairs<T>(hx, p, n, R);
+    load_kin(kin, p, n, kk);
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) {
+      R[u] = make_double2(R[u].x - e * X[u].x, R[u].y - e * X[u].y);
+      kk[u] = tpa(kk[u] / ek);
+    }
+  };
   double v2[2] = {0.0, 0.0};
-  for (int k = threadIdx.x; k < K; k += blockDim.x) {
-    const double r = (double)hx[k] - e * (double)x[k];
-    const double g = tpa(cd.kin[k >> 1] / ek) * r;
-    v2[0] += g * r;
-    v2[1] += r * r;
+  for (int p = threadIdx.x; p < n; p += blockDim.x * kPairs) {
+    residual(p);
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) {
+      const double r2 = R[u].x * R[u].x + R[u].y * R[u].y;
+      v2[0] += kk[u] * r2;
+      v2[1] += r2;
+    }
   }
   block_sum<2>(v2, sh);
   const double gam = v2[0];
-  if (threadIdx.x == 0) cd.resn[i] = v2[1];
-  double beta = 0.0;
-  if (!first) {
-    const double gp = cd.gam[i];
-    beta = gp > 0.0 ? gam / gp : 0.0;
+  const double beta = gp > 0.0 ? gam / gp : 0.0;
+  for (int p = threadIdx.x; p < n; p += blockDim.x * kPairs) {
+    if (n > (int)blockDim.x * kPairs) residual(p);  // else the registers still hold them
+    if (!first) load_pairs<T>(d, p, n, X);
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u)
+      R[u] = first ? make_double2(kk[u] * R[u].x, kk[u] * R[u].y)
+                   : make_double2(kk[u] * R[u].x + beta * X[u].x, kk[u] * R[u].y + beta * X[u].y);
+    store_pairs<T>(d, p, n, R);
   }
-  for (int k = threadIdx.x; k < K; k += blockDim.x) {
-    const double r = (double)hx[k] - e * (double)x[k];
-    const double g = tpa(cd.kin[k >> 1] / ek) * r;
-    d[k] = (T)(g + (first ? 0.0 : beta * (double)d[k]));
+  if (threadIdx.x == 0) {
+    cd.resn[i] = v2[1];
+    cd.gam[i] = gam;
   }
-  if (threadIdx.x == 0) cd.gam[i] = gam;
 }
 
 // Line minimisation of each band along its (projected) direction d:
 // psi(theta) = x cos(theta) + d/|d| sin(theta), exact minimiser of the 2x2
 // Rayleigh quotient at fixed H; H psi is updated with H d (no extra H apply).
 template <typename T>
-__global__ void __launch_bounds__(kNT) k_linemin(const CandDesc* __restrict__ cds) {
+__global__ void __launch_bounds__(kWideNT) k_linemin(const CandDesc* __restrict__ cds) {
   const CandDesc& cd = cds[blockIdx.z];
   if (!cd.active) return;
   const int i = blockIdx.x;
   if (i >= cd.nb) return;
   __shared__ double sh[16 * 4];
-  const int K = cd.K;
+  const int n = cd.npwh;
   T* x = (T*)cd.X + (size_t)i * cd.Kp;
   T* hx = (T*)cd.HX + (size_t)i * cd.Kp;
   const T* d = (const T*)cd.D + (size_t)i * cd.Kp;
   const T* hd = (const T*)cd.HD + (size_t)i * cd.Kp;
+  double2 X[kPairs], HX[kPairs], D[kPairs], HD[kPairs];
+  auto load = [&](int p) {
+    load_pairs<T>(x, p, n, X);
+    load_pairs<T>(d, p, n, D);
+    load_pairs<T>(hx, p, n, HX);
+    load_pairs<T>(hd, p, n, HD);
+  };
   double v[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int k = threadIdx.x; k < K; k += blockDim.x) {
-    const double xv = x[k], hxv = hx[k], dv = d[k], hdv = hd[k];
-    v[0] += xv * hxv;
-    v[1] += xv * hdv;
-    v[2] += dv * hdv;
-    v[3] += dv * dv;
+  for (int p = threadIdx.x; p < n; p += blockDim.x * kPairs) {
+    load(p);
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) {
+      v[0] += X[u].x * HX[u].x + X[u].y * HX[u].y;
+      v[1] += X[u].x * HD[u].x + X[u].y * HD[u].y;
+      v[2] += D[u].x * HD[u].x + D[u].y * HD[u].y;
+      v[3] += D[u].x * D[u].x + D[u].y * D[u].y;
+    }
   }
   block_sum<4>(v, sh);
   const double n2 = v[3];
@@ -775,9 +852,15 @@ __global__ void __launch_bounds__(kNT) k_linemin(const CandDesc* __restrict__ cd
   double sn, cs;
   sincos(theta, &sn, &cs);
   const double sd = sn * inv;
-  for (int k = threadIdx.x; k < K; k += blockDim.x) {
-    x[k] = (T)(cs * (double)x[k] + sd * (double)d[k]);
-    hx[k] = (T)(cs * (double)hx[k] + sd * (double)hd[k]);
+  for (int p = threadIdx.x; p < n; p += blockDim.x * kPairs) {
+    if (n > (int)blockDim.x * kPairs) load(p);
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) {
+      X[u] = make_double2(cs * X[u].x + sd * D[u].x, cs * X[u].y + sd * D[u].y);
+      HX[u] = make_double2(cs * HX[u].x + sd * HD[u].x, cs * HX[u].y + sd * HD[u].y);
+    }
+    store_pairs<T>(x, p, n, X);
+    store_pairs<T>(hx, p, n, HX);
   }
 }
 
@@ -915,17 +998,23 @@ __global__ void __launch_bounds__(kBandNT) k_cg_direction_r(const CandDesc* __re
 
 // Kinetic energy of each band: bandw[i] = sum_G |G|^2/2 |c_iG|^2.
 template <typename T>
-__global__ void __launch_bounds__(kNT) k_band_kinetic(const CandDesc* __restrict__ cds) {
+__global__ void __launch_bounds__(kWideNT) k_band_kinetic(const CandDesc* __restrict__ cds) {
   const CandDesc& cd = cds[blockIdx.z];
   if (!cd.active) return;
   const int i = blockIdx.x;
   if (i >= cd.nb) return;
   __shared__ double sh[16];
+  const int n = cd.npwh;
   const T* x = (const T*)cd.X + (size_t)i * cd.Kp;
+  const double* kin = cd.kin;
+  double2 X[kPairs];
+  double kk[kPairs];
   double v[1] = {0.0};
-  for (int k = threadIdx.x; k < cd.K; k += blockDim.x) {
-    const double xv = x[k];
-    v[0] += cd.kin[k >> 1] * xv * xv;
+  for (int p = threadIdx.x; p < n; p += blockDim.x * kPairs) {
+    load_pairs<T>(x, p, n, X);
+    load_kin(kin, p, n, kk);
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) v[0] += kk[u] * (X[u].x * X[u].x + X[u].y * X[u].y);
   }
   block_sum<1>(v, sh);
   if (threadIdx.x == 0) cd.bandw[i] = v[0];
@@ -1395,7 +1484,7 @@ void launch_cg_direction(const LaunchCtx& L, int first) {
     return;
   }
   prof_before("k_cg_direction", L.stream);
-  hipLaunchKernelGGL(k_cg_direction<T>, dim3(L.g.nb_max, 1, L.g.ncand), dim3(kNT), 0, L.stream,
+  hipLaunchKernelGGL(k_cg_direction<T>, dim3(L.g.nb_max, 1, L.g.ncand), dim3(band_threads(L.g)), 0, L.stream,
                      L.desc, first);
   check_launch("k_cg_direction");
   prof_after("k_cg_direction", L.stream);
@@ -1414,14 +1503,14 @@ void launch_linemin(const LaunchCtx& L) {
     return;
   }
   prof_before("k_linemin", L.stream);
-  hipLaunchKernelGGL(k_linemin<T>, dim3(L.g.nb_max, 1, L.g.ncand), dim3(kNT), 0, L.stream, L.desc);
+  hipLaunchKernelGGL(k_linemin<T>, dim3(L.g.nb_max, 1, L.g.ncand), dim3(band_threads(L.g)), 0, L.stream, L.desc);
   check_launch("k_linemin");
   prof_after("k_linemin", L.stream);
 }
 template <typename T>
 void launch_band_kinetic(const LaunchCtx& L) {
   prof_before("k_band_kinetic", L.stream);
-  hipLaunchKernelGGL(k_band_kinetic<T>, dim3(L.g.nb_max, 1, L.g.ncand), dim3(kNT), 0, L.stream,
+  hipLaunchKernelGGL(k_band_kinetic<T>, dim3(L.g.nb_max, 1, L.g.ncand), dim3(band_threads(L.g)), 0, L.stream,
                      L.desc);
   check_launch("k_band_kinetic");
   prof_after("k_band_kinetic", L.stream);
