@@ -24,7 +24,6 @@ template <typename T>
 __device__ __forceinline__ cplx<T> csub(cplx<T> a, cplx<T> b) { return {a.x - b.x, a.y - b.y}; }
 
 constexpr int kMaxFftN = 128;     // longest 1-D transform along any axis
-constexpr int kMaxStages = 8;
 constexpr int kMaxHist = 8;       // Pulay history slots
 constexpr int kNT = 256;          // threads of most kernels
 
@@ -39,9 +38,9 @@ enum Scal {
 
 // Radix plan of one transform length.
 struct FftPlan {
-  int n;
-  int nstage;
-  int radix[kMaxStages];
+  int n;     // line length
+  int nr;    // stages of the in-place LDS transform (fft_lds.hpp)
+  int r[3];  // their radices, descending
 };
 
 // Pointer of the descriptor: on the device it is a pointer to global memory

@@ -102,133 +102,6 @@ __device__ bool grid_sum_last(const double (&v)[N], double* part, unsigned* tick
   return true;
 }
 
-// ----------------------------------------------------------------------- FFT
-// Twiddle table tw[k] = exp(-2 pi i k / n), k < n, computed in FP64.
-template <typename T>
-__device__ __forceinline__ void fill_twiddles(cplx<T>* tw, int n, int tid, int nthr) {
-  for (int k = tid; k < n; k += nthr) {
-    double s, c;
-    sincospi(-2.0 * (double)k / (double)n, &s, &c);
-    tw[k] = {(T)c, (T)s};
-  }
-}
-
-// i * sign * z
-template <typename T>
-__device__ __forceinline__ cplx<T> imul(cplx<T> z, int sign) {
-  return sign > 0 ? cplx<T>{-z.y, z.x} : cplx<T>{z.y, -z.x};
-}
-
-template <typename T>
-__device__ __forceinline__ void bfly2(cplx<T>* v) {
-  cplx<T> a = v[0], b = v[1];
-  v[0] = cadd(a, b);
-  v[1] = csub(a, b);
-}
-template <typename T>
-__device__ __forceinline__ void bfly4(cplx<T>* v, int sign) {
-  cplx<T> a = cadd(v[0], v[2]), b = csub(v[0], v[2]);
-  cplx<T> c = cadd(v[1], v[3]), d = imul(csub(v[1], v[3]), sign);
-  v[0] = cadd(a, c);
-  v[2] = csub(a, c);
-  v[1] = cadd(b, d);
-  v[3] = csub(b, d);
-}
-template <typename T>
-__device__ __forceinline__ void bfly3(cplx<T>* v, int sign) {
-  const T h = (T)0.86602540378443864676;  // sqrt(3)/2
-  cplx<T> t = cadd(v[1], v[2]);
-  cplx<T> u = csub(v[1], v[2]);
-  cplx<T> m = {v[0].x - (T)0.5 * t.x, v[0].y - (T)0.5 * t.y};
-  cplx<T> iu = imul(cplx<T>{h * u.x, h * u.y}, sign);
-  v[0] = cadd(v[0], t);
-  v[1] = cadd(m, iu);
-  v[2] = csub(m, iu);
-}
-template <typename T>
-__device__ __forceinline__ void bfly5(cplx<T>* v, int sign) {
-  const T c1 = (T)0.30901699437494742410, c2 = (T)-0.80901699437494742410;
-  const T s1 = (T)0.95105651629515357212, s2 = (T)0.58778525229247312917;
-  cplx<T> t1 = cadd(v[1], v[4]), t2 = cadd(v[2], v[3]);
-  cplx<T> u1 = csub(v[1], v[4]), u2 = csub(v[2], v[3]);
-  cplx<T> r1 = {v[0].x + c1 * t1.x + c2 * t2.x, v[0].y + c1 * t1.y + c2 * t2.y};
-  cplx<T> r2 = {v[0].x + c2 * t1.x + c1 * t2.x, v[0].y + c2 * t1.y + c1 * t2.y};
-  cplx<T> q1 = imul(cplx<T>{s1 * u1.x + s2 * u2.x, s1 * u1.y + s2 * u2.y}, sign);
-  cplx<T> q2 = imul(cplx<T>{s2 * u1.x - s1 * u2.x, s2 * u1.y - s1 * u2.y}, sign);
-  v[0] = cadd(v[0], cadd(t1, t2));
-  v[1] = cadd(r1, q1);
-  v[4] = csub(r1, q1);
-  v[2] = cadd(r2, q2);
-  v[3] = csub(r2, q2);
-}
-
-// One radix-R Stockham stage over nseq sequences of length n stored at
-// element stride es and sequence stride ss, from `a` into `b`.
-template <typename T, int R>
-__device__ __forceinline__ void fft_stage(const cplx<T>* __restrict__ a, cplx<T>* __restrict__ b,
-                                          int n, int Ns, int nseq, int es, int ss,
-                                          const cplx<T>* __restrict__ tw, int sign, int tid,
-                                          int nthr) {
-  const int nbf = n / R;
-  const int tws = n / (Ns * R);
-  const int total = nbf * nseq;
-  for (int t = tid; t < total; t += nthr) {
-    // consecutive threads take consecutive elements when elements are
-    // contiguous (es == 1), else consecutive sequences: either way the LDS
-    // addresses of a wavefront are consecutive (no bank conflicts).
-    int seq, j;
-    if (es == 1) {
-      seq = t / nbf;
-      j = t - seq * nbf;
-    } else {
-      j = t / nseq;
-      seq = t - j * nseq;
-    }
-    const cplx<T>* src = a + seq * ss;
-    cplx<T>* dst = b + seq * ss;
-    const int jm = j % Ns;
-    cplx<T> v[R];
-    v[0] = src[j * es];
-#pragma unroll
-    for (int r = 1; r < R; ++r) {
-      cplx<T> x = src[(j + r * nbf) * es];
-      cplx<T> w = tw[jm * r * tws];
-      if (sign > 0) w.y = -w.y;
-      v[r] = cmul(x, w);
-    }
-    if (R == 2) bfly2(v);
-    if (R == 3) bfly3(v, sign);
-    if (R == 4) bfly4(v, sign);
-    if (R == 5) bfly5(v, sign);
-    const int base = (j - jm) * R + jm;
-#pragma unroll
-    for (int r = 0; r < R; ++r) dst[(base + r * Ns) * es] = v[r];
-  }
-}
-
-// Batched in-LDS FFT.  Data starts in `a`; `b` is scratch of the same
-// shape.  Returns the buffer holding the result (natural order).
-// sign = -1: forward  X_k = sum_j x_j e^{-2 pi i jk/n};  sign = +1: inverse
-// (unnormalised).  Ends with a barrier.
-template <typename T>
-__device__ cplx<T>* lds_fft(cplx<T>* a, cplx<T>* b, const FftPlan& P, int nseq, int es, int ss,
-                            const cplx<T>* tw, int sign, int tid, int nthr) {
-  int Ns = 1;
-  for (int st = 0; st < P.nstage; ++st) {
-    const int R = P.radix[st];
-    if (R == 4) fft_stage<T, 4>(a, b, P.n, Ns, nseq, es, ss, tw, sign, tid, nthr);
-    else if (R == 2) fft_stage<T, 2>(a, b, P.n, Ns, nseq, es, ss, tw, sign, tid, nthr);
-    else if (R == 3) fft_stage<T, 3>(a, b, P.n, Ns, nseq, es, ss, tw, sign, tid, nthr);
-    else fft_stage<T, 5>(a, b, P.n, Ns, nseq, es, ss, tw, sign, tid, nthr);
-    __syncthreads();
-    cplx<T>* t = a;
-    a = b;
-    b = t;
-    Ns *= R;
-  }
-  return a;
-}
-
 // Unpack Gamma-point storage of half-sphere coefficient g of a band:
 // c_G = (x[2g] + i x[2g+1]) / sqrt2 for G != 0, c_0 = x[0].
 template <typename T>

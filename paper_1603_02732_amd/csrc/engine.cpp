@@ -137,19 +137,38 @@ void check_launch(const char* name) {
 }
 
 // --------------------------------------------------------------- utilities
+// Radices of a line: the fewest (at most three, each at most 10), the largest as
+// small as possible, descending.
 static bool fft_plan(int n, FftPlan& p) {
   p.n = n;
-  p.nstage = 0;
-  int m = n;
-  const int order[4] = {4, 2, 3, 5};
-  for (int r : order) {
-    while (m % r == 0) {
-      if (p.nstage >= kMaxStages) return false;
-      p.radix[p.nstage++] = r;
-      m /= r;
+  p.nr = 0;
+  if (n < 1 || n > kMaxFftN) return false;
+  static const int radices[] = {1, 2, 3, 4, 5, 6, 8, 9, 10};
+  for (int a : radices)
+    if (a == n) {
+      p.nr = 1;
+      p.r[0] = a;
+      return true;
     }
-  }
-  return m == 1 && n >= 1 && n <= kMaxFftN;
+  for (int a : radices)
+    for (int b : radices)
+      if (b > 1 && b <= a && a * b == n) {
+        p.nr = 2;
+        p.r[0] = a;
+        p.r[1] = b;
+        return true;
+      }
+  for (int a : radices)
+    for (int b : radices)
+      for (int c : radices)
+        if (c > 1 && c <= b && b <= a && a * b * c == n) {
+          p.nr = 3;
+          p.r[0] = a;
+          p.r[1] = b;
+          p.r[2] = c;
+          return true;
+        }
+  return false;
 }
 
 static void inv3(const double* A, double* Ai, double* det) {

@@ -6,6 +6,7 @@
 // and the FP64 subspace solver (Cholesky orthonormalisation + Jacobi
 // diagonalisation: the orthogonalisation and subspace-diagonalisation steps
 // of Algorithm 1).
+#include "fft_lds.hpp"
 #include "jacobi.hpp"
 
 #include <algorithm>
@@ -101,14 +102,19 @@ __global__ void __launch_bounds__(kNT) k_grid_fft_x(const CandDesc* __restrict__
   extern __shared__ __align__(16) char smem[];
   cplx<double>* tw = (cplx<double>*)smem;
   cplx<double>* A = tw + kMaxFftN;
-  cplx<double>* Bf = A + rows_per_block * N1;
+  const int p = N1 | 1;
+  unsigned char* pos = (unsigned char*)(A + nr * p);
   const int tid = threadIdx.x, nthr = blockDim.x;
-  fill_twiddles(tw, N1, tid, nthr);
+  const float in1 = 1.0f / N1;
   cplx<double>* g = cd.zgrid + (size_t)r0 * N1;
-  for (int e = tid; e < nr * N1; e += nthr) A[e] = g[e];
+  for (int e = tid; e < nr * N1; e += nthr) A[e + (p - N1) * line_div(e, in1)] = g[e];
+  lds_tables<double>(tw, nullptr, pos, cd.plan[0], 192);
   __syncthreads();
-  cplx<double>* r = lds_fft(A, Bf, cd.plan[0], nr, 1, N1, tw, sign, tid, nthr);
-  for (int e = tid; e < nr * N1; e += nthr) g[e] = r[e];
+  lds_dif<double>(A, {nr, p, 1, nr, 0}, cd.plan[0], tw, (double)sign);
+  for (int e = tid; e < nr * N1; e += nthr) {
+    const int l = line_div(e, in1);
+    g[e] = A[l * p + pos[e - l * N1]];
+  }
 }
 
 // Columns along y (axis 1) or z (axis 2): each block takes a tile of TX
@@ -130,19 +136,21 @@ __global__ void __launch_bounds__(kNT) k_grid_fft_yz(const CandDesc* __restrict_
   extern __shared__ __align__(16) char smem[];
   cplx<double>* tw = (cplx<double>*)smem;
   cplx<double>* A = tw + kMaxFftN;
-  cplx<double>* Bf = A + kTX * n;
+  unsigned char* pos = (unsigned char*)(A + tx * n);
   const int tid = threadIdx.x, nthr = blockDim.x;
-  fill_twiddles(tw, n, tid, nthr);
   const FftPlan& P = cd.plan[axis];
-  for (int t = tid; t < tx * n; t += nthr) {
-    const int e = t / tx, c = t - e * tx;
-    A[c * n + e] = cd.zgrid[base + e * es + c];
+  const float itx = 1.0f / tx;
+  cplx<double>* g = cd.zgrid + base;
+  for (int t = tid; t < tx * n; t += nthr) {  // [n][tx], as in memory
+    const int e = line_div(t, itx);
+    A[t] = g[e * es + (t - e * tx)];
   }
+  lds_tables<double>(tw, nullptr, pos, P, 192);
   __syncthreads();
-  cplx<double>* r = lds_fft(A, Bf, P, tx, 1, n, tw, sign, tid, nthr);
+  lds_dif<double>(A, {tx, 1, tx, tx, 0}, P, tw, (double)sign);
   for (int t = tid; t < tx * n; t += nthr) {
-    const int e = t / tx, c = t - e * tx;
-    cd.zgrid[base + e * es + c] = r[c * n + e];
+    const int e = line_div(t, itx), c = t - e * tx;
+    g[e * es + c] = A[pos[e] * tx + c];
   }
 }
 
@@ -1530,20 +1538,20 @@ void launch_grid_fft(const LaunchCtx& L, int sign) {
   const BatchGeom& g = L.g;
   const int rpb = std::max(1, 1024 / g.N1max);
   const int rows = g.N2max * g.N3max;
-  size_t lds_x = sizeof(cplx<double>) * (kMaxFftN + 2 * (size_t)rpb * g.N1max);
+  size_t lds_x = sizeof(cplx<double>) * (kMaxFftN + (size_t)rpb * (g.N1max | 1)) + kMaxFftN;
   prof_before("k_grid_fft_x", L.stream);
   hipLaunchKernelGGL(k_grid_fft_x, dim3((rows + rpb - 1) / rpb, 1, g.ncand), dim3(kNT), lds_x,
                      L.stream, L.desc, sign, rpb);
   check_launch("k_grid_fft_x");
   prof_after("k_grid_fft_x", L.stream);
   const int ntx = (g.N1max + kTX - 1) / kTX;
-  size_t lds_y = sizeof(cplx<double>) * (kMaxFftN + 2 * (size_t)kTX * g.N2max);
+  size_t lds_y = sizeof(cplx<double>) * (kMaxFftN + (size_t)kTX * g.N2max) + kMaxFftN;
   prof_before("k_grid_fft_yz", L.stream);
   hipLaunchKernelGGL(k_grid_fft_yz, dim3(ntx * g.N3max, 1, g.ncand), dim3(kNT), lds_y, L.stream,
                      L.desc, 1, sign);
   check_launch("k_grid_fft_yz");
   prof_after("k_grid_fft_yz", L.stream);
-  size_t lds_z = sizeof(cplx<double>) * (kMaxFftN + 2 * (size_t)kTX * g.N3max);
+  size_t lds_z = sizeof(cplx<double>) * (kMaxFftN + (size_t)kTX * g.N3max) + kMaxFftN;
   prof_before("k_grid_fft_yz", L.stream);
   hipLaunchKernelGGL(k_grid_fft_yz, dim3(ntx * g.N2max, 1, g.ncand), dim3(kNT), lds_z, L.stream,
                      L.desc, 2, sign);

@@ -19,7 +19,7 @@
 // 256-thread workgroup walking the Jacobi pairs of a k in turn, 790 launches and
 // 11.1 ms this way.
 #include "device.hpp"
-#include "fft_reg.hpp"
+#include "fft_lds.hpp"
 #include "jacobi.hpp"
 #include "launch.hpp"
 
@@ -71,42 +71,44 @@ __global__ void k_kpt_scatter(const KptDev* __restrict__ kd, zc* __restrict__ z,
 
 // Batched line transforms along one axis of grids [nb][N3][N2][N1]: line l
 // starts at (l / A) * Bs + (l % A) * Cs and its elements are es apart.  L
-// lines per workgroup go through the LDS Stockham passes together.
+// lines per workgroup go through LDS together (fft_lds.hpp).
 __global__ void __launch_bounds__(256) k_kpt_lines(zc* __restrict__ data, FftPlan P, int A, long Bs,
                                                    long Cs, long es, long nlines, int L, int sign) {
   extern __shared__ __align__(16) char smem[];
-  const int n = P.n;
+  const int n = P.n, p = n | 1, tid = threadIdx.x, nthr = blockDim.x;
   zc* a = (zc*)smem;
-  zc* b = a + (size_t)L * n;
-  zc* tw = b + (size_t)L * n;
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  fill_twiddles(tw, n, tid, nthr);
+  zc* tw = a + (size_t)L * p;
+  unsigned char* pos = (unsigned char*)(tw + n);
+  lds_tables<double>(tw, nullptr, pos, P, 192);
   const long l0 = (long)blockIdx.x * L;
-  for (int t = tid; t < L * n; t += nthr) {
-    int li, j;
+  const int nl = (int)min((long)L, nlines - l0);
+  for (int t = tid; t < nl * n; t += nthr) {
+    // consecutive threads take consecutive memory: along the line (es == 1)
+    // or across lines
+    int l, e;
     if (es == 1) {
-      li = t / n;
-      j = t - li * n;
-    } else {  // consecutive threads on consecutive lines: consecutive addresses
-      j = t / L;
-      li = t - j * L;
+      l = t / n;
+      e = t - l * n;
+    } else {
+      e = t / nl;
+      l = t - e * nl;
     }
-    const long l = l0 + li;
-    a[li * n + j] = l < nlines ? data[(l / A) * Bs + (l % A) * Cs + j * es] : zc{0.0, 0.0};
+    const long line = l0 + l;
+    a[l * p + e] = data[(line / A) * Bs + (line % A) * Cs + e * es];
   }
   __syncthreads();
-  zc* r = lds_fft(a, b, P, L, 1, n, tw, sign, tid, nthr);
-  for (int t = tid; t < L * n; t += nthr) {
-    int li, j;
+  lds_dif<double>(a, {nl, p, 1, nl, 0}, P, tw, (double)sign);
+  for (int t = tid; t < nl * n; t += nthr) {
+    int l, e;
     if (es == 1) {
-      li = t / n;
-      j = t - li * n;
+      l = t / n;
+      e = t - l * n;
     } else {
-      j = t / L;
-      li = t - j * L;
+      e = t / nl;
+      l = t - e * nl;
     }
-    const long l = l0 + li;
-    if (l < nlines) data[(l / A) * Bs + (l % A) * Cs + j * es] = r[li * n + j];
+    const long line = l0 + l;
+    data[(line / A) * Bs + (line % A) * Cs + e * es] = a[l * p + pos[e]];
   }
 }
 
@@ -1144,7 +1146,7 @@ static void kpt_fft3(hipStream_t s, zc* zk, long nb, const int N[3], const FftPl
   for (const Ax& a : axes) {
     const int n = plans[a.ax].n;
     const int L = std::max(1, 512 / n);
-    const size_t lds = (size_t)(2 * L * n + n) * sizeof(zc);
+    const size_t lds = (size_t)(L * (n | 1) + n) * sizeof(zc) + n;
     hipLaunchKernelGGL(k_kpt_lines, dim3((unsigned)((a.nlines + L - 1) / L)), dim3(256), lds, s, zk,
                        plans[a.ax], a.A, a.Bs, a.Cs, a.es, a.nlines, L, sign);
     check_launch("k_kpt_lines");

@@ -13,6 +13,7 @@
 //  * the FP64 subspace solver: Cholesky orthonormalisation and Jacobi
 //    diagonalisation of the subspace Hamiltonian.
 #include "device.hpp"
+#include "fft_lds.hpp"
 #include "launch.hpp"
 
 #include <type_traits>
@@ -65,9 +66,10 @@ __global__ void __launch_bounds__(kNT) k_z_inverse(const CandDesc* __restrict__ 
   extern __shared__ __align__(16) char smem[];
   cplx<T>* tw = (cplx<T>*)smem;
   cplx<T>* A = tw + kMaxFftN;
-  cplx<T>* Bf = A + nloc * N3;
-  fill_twiddles(tw, N3, tid, nthr);
-  for (int e = tid; e < nloc * N3; e += nthr) A[e] = {(T)0, (T)0};
+  const int pz = N3 | 1;
+  unsigned char* pos = (unsigned char*)(A + nloc * pz);
+  for (int e = tid; e < nloc * pz; e += nthr) A[e] = {(T)0, (T)0};
+  lds_tables<T>(tw, nullptr, pos, cd.plan[2], 192);
   __syncthreads();
   const T* base = warr<T>(cd, src);
   const T* xa = base + (size_t)(2 * pair) * cd.Kp;
@@ -79,19 +81,20 @@ __global__ void __launch_bounds__(kNT) k_z_inverse(const CandDesc* __restrict__ 
     const int s = meta & 0xFFFFF, z = meta >> 20;
     cplx<T> ca = unpack_coef(xa, g);
     cplx<T> cb = hasb ? unpack_coef(xb, g) : cplx<T>{(T)0, (T)0};
-    A[(s - s0) * N3 + z] = {ca.x - cb.y, ca.y + cb.x};  // c_a + i c_b
+    A[(s - s0) * pz + z] = {ca.x - cb.y, ca.y + cb.x};  // c_a + i c_b
     if (g != 0) {
       const int sm = mirror_stick(s);
       const int zm = z == 0 ? 0 : N3 - z;
-      A[(sm - s0) * N3 + zm] = {ca.x + cb.y, cb.x - ca.y};  // conj c_a + i conj c_b
+      A[(sm - s0) * pz + zm] = {ca.x + cb.y, cb.x - ca.y};  // conj c_a + i conj c_b
     }
   }
   __syncthreads();
-  cplx<T>* r = lds_fft(A, Bf, cd.plan[2], nloc, 1, N3, tw, +1, tid, nthr);
+  lds_dif<T>(A, {nloc, pz, 1, nloc, 0}, cd.plan[2], tw, (T)1);
   cplx<T>* out = (cplx<T>*)cd.sticks + (size_t)pair * N3 * cd.nst;
+  const float inl = 1.0f / nloc;
   for (int t = tid; t < nloc * N3; t += nthr) {
-    const int z = t / nloc, s = t - z * nloc;
-    out[(size_t)z * cd.nst + s0 + s] = r[s * N3 + z];
+    const int z = line_div(t, inl), s = t - z * nloc;
+    out[(size_t)z * cd.nst + s0 + s] = A[s * pz + pos[z]];
   }
 }
 
@@ -115,15 +118,17 @@ __global__ void __launch_bounds__(kNT) k_z_forward(const CandDesc* __restrict__ 
   extern __shared__ __align__(16) char smem[];
   cplx<T>* tw = (cplx<T>*)smem;
   cplx<T>* A = tw + kMaxFftN;
-  cplx<T>* Bf = A + nloc * N3;
-  fill_twiddles(tw, N3, tid, nthr);
+  const int pz = N3 | 1;
+  unsigned char* pos = (unsigned char*)(A + nloc * pz);
+  lds_tables<T>(tw, nullptr, pos, cd.plan[2], 192);
   const cplx<T>* in = (const cplx<T>*)cd.sticks + (size_t)pair * N3 * cd.nst;
+  const float inl = 1.0f / nloc;
   for (int t = tid; t < nloc * N3; t += nthr) {
-    const int z = t / nloc, s = t - z * nloc;
-    A[s * N3 + z] = in[(size_t)z * cd.nst + s0 + s];
+    const int z = line_div(t, inl), s = t - z * nloc;
+    A[s * pz + z] = in[(size_t)z * cd.nst + s0 + s];
   }
   __syncthreads();
-  cplx<T>* r = lds_fft(A, Bf, cd.plan[2], nloc, 1, N3, tw, -1, tid, nthr);
+  lds_dif<T>(A, {nloc, pz, 1, nloc, 0}, cd.plan[2], tw, (T)-1);
   const T sc = (T)(1.0 / (double)cd.ntot);
   const T rt2 = (T)1.41421356237309504880;
   const T* xsrc = warr<T>(cd, src);
@@ -140,8 +145,8 @@ __global__ void __launch_bounds__(kNT) k_z_forward(const CandDesc* __restrict__ 
     const int s = meta & 0xFFFFF, z = meta >> 20;
     const int sm = mirror_stick(s);
     const int zm = z == 0 ? 0 : N3 - z;
-    cplx<T> W = r[(s - s0) * N3 + z];
-    cplx<T> Wm = r[(sm - s0) * N3 + zm];
+    cplx<T> W = A[(s - s0) * pz + pos[z]];
+    cplx<T> Wm = A[(sm - s0) * pz + pos[zm]];
     // (V psi_a)_G = (W_G + conj W_-G)/2 ; (V psi_b)_G = (W_G - conj W_-G)/(2i)
     cplx<T> va = {(T)0.5 * (W.x + Wm.x) * sc, (T)0.5 * (W.y - Wm.y) * sc};
     cplx<T> vb = {(T)0.5 * (W.y + Wm.y) * sc, (T)-0.5 * (W.x - Wm.x) * sc};
@@ -165,56 +170,144 @@ __global__ void __launch_bounds__(kNT) k_z_forward(const CandDesc* __restrict__ 
 }
 
 // ------------------------------------------------------------ plane kernels
+// A plane in LDS, rows at an odd pitch, with the axes' tables.
+template <typename T>
+struct Plane {
+  cplx<T>*tw1, *tw2, *A;
+  unsigned char *nat1, *nat2;  // x and y of a position
+  int p;
+  LdsLines cols, rows;         // active columns (the others are zero), rows
+};
+template <typename T>
+__device__ __forceinline__ Plane<T> plane_of_block(const CandDesc& cd, char* smem) {
+  Plane<T> P;
+  P.p = cd.N1 | 1;
+  P.tw1 = (cplx<T>*)smem;
+  P.tw2 = P.tw1 + cd.N1;
+  P.A = P.tw2 + cd.N2;
+  P.nat1 = (unsigned char*)(P.A + P.p * cd.N2);
+  P.nat2 = P.nat1 + cd.N1;
+  P.cols = {cd.pl_nx, 1, P.p, cd.pl_nxl, cd.N1 - cd.pl_nx};
+  P.rows = {cd.N2, P.p, 1, cd.N2, 0};
+  return P;
+}
+// The sticks of plane (pair, z), zeros elsewhere; the tables as well if `tables`,
+// while the first sticks are on their way.
+template <typename T>
+__device__ __forceinline__ void plane_fill(const CandDesc& cd, const Plane<T>& P, const cplx<T>* __restrict__ st,
+                                           bool tables) {
+  const int n = P.p * cd.N2, nthr = blockDim.x, nst = cd.nst;
+  const int* xy_of = cd.stick_xy;
+  const int sa = threadIdx.x, sb = sa + nthr;  // the first two of a thread
+  const int xya = xy_of[min(sa, nst - 1)], xyb = xy_of[min(sb, nst - 1)];
+  const T vax = st[min(sa, nst - 1)].x, vay = st[min(sa, nst - 1)].y;
+  const T vbx = st[min(sb, nst - 1)].x, vby = st[min(sb, nst - 1)].y;
+  for (int e = threadIdx.x; e < n; e += nthr) P.A[e] = {(T)0, (T)0};
+  if (tables) {
+    lds_tables<T>(P.tw1, P.nat1, nullptr, cd.plan[0]);
+    lds_tables<T>(P.tw2, P.nat2, nullptr, cd.plan[1], 128);
+  }
+  __syncthreads();
+  if (sa < nst) P.A[(xya >> 16) * P.p + (xya & 0xFFFF)] = {vax, vay};
+  if (sb < nst) P.A[(xyb >> 16) * P.p + (xyb & 0xFFFF)] = {vbx, vby};
+  for (int s0 = threadIdx.x + 2 * nthr; s0 < nst; s0 += 4 * nthr) {
+    int xy[4];
+    cplx<T> v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int s = min(s0 + nthr * u, nst - 1);
+      xy[u] = xy_of[s];
+      v[u] = {st[s].x, st[s].y};
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + nthr * u < nst) P.A[(xy[u] >> 16) * P.p + (xy[u] & 0xFFFF)] = v[u];
+  }
+  __syncthreads();
+}
+
+// Last inverse x stage, times V_eff, first forward x stage: the same elements, so
+// they stay in registers.  Consecutive lanes take consecutive butterflies of a
+// row: V's addresses are runs of N1 / R values.
+template <typename T, int R>
+__device__ __forceinline__ void plane_vmul(const Plane<T>& P, int N1, int N2, const T* __restrict__ V) {
+  const int nj = N1 / R;
+  const float inj = 1.0f / nj;
+  for (int t = threadIdx.x; t < nj * N2; t += blockDim.x) {
+    const int l = line_div(t, inj), j = t - l * nj;
+    cplx<T>* p = P.A + l * P.p + j * R;
+    const T* vp = V + (int)P.nat2[l] * N1 + P.nat1[j * R];
+    cplx<T> v[R], w[R];
+    T f[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      f[r] = vp[r * nj];
+      v[r] = p[r];
+    }
+    freg::fft<T, 1, R>(v, w);
+#pragma unroll
+    for (int r = 0; r < R; ++r) w[r] = {w[r].x * f[r], -w[r].y * f[r]};
+    freg::fft<T, 1, R>(w, v);
+#pragma unroll
+    for (int r = 0; r < R; ++r) p[r] = {v[r].x, -v[r].y};
+  }
+  __syncthreads();
+}
+
 // One z-plane of one band pair: gather the stick values, inverse 2-D FFT,
 // multiply by V_eff(r), forward 2-D FFT, scatter back to the sticks.
+//
+// Bound by the LDS passes and their index arithmetic: 7 passes in place for
+// lines of 12 to 100, where radix-4/2/3/5 passes between two buffers took 13.
+// 4 clusters of 24 FP64 bands, 40^3: 94 -> 48 us (density 73 -> 35); 164 FP32 bands,
+// planes of 80 x 50: 226 -> 84 us (137 -> 72); 20 bands, 24^3 (240 blocks, one a
+// CU: latency) 12.6 -> 12.5 us.  The z transforms likewise: 23 -> 12, 27 -> 19 and
+// 8.9 -> 7.5 us.
 template <typename T>
-__global__ void __launch_bounds__(kNT) k_plane_hpsi(const CandDesc* __restrict__ cds) {
+__global__ void __launch_bounds__(kNT, 4) k_plane_hpsi(const CandDesc* __restrict__ cds) {
   const CandDesc& cd = cds[blockIdx.z];
   if (!cd.active) return;
   const int z = blockIdx.x, pair = blockIdx.y;
   if (z >= cd.N3 || pair >= cd.npair) return;
-  const int N1 = cd.N1, N2 = cd.N2, NP = N1 * N2;
-  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int N1 = cd.N1, N2 = cd.N2;
   extern __shared__ __align__(16) char smem[];
-  cplx<T>* tw1 = (cplx<T>*)smem;
-  cplx<T>* tw2 = tw1 + kMaxFftN;
-  cplx<T>* A = tw2 + kMaxFftN;
-  cplx<T>* Bf = A + NP;
-  fill_twiddles(tw1, N1, tid, nthr);
-  fill_twiddles(tw2, N2, tid, nthr);
-  for (int e = tid; e < NP; e += nthr) A[e] = {(T)0, (T)0};
-  __syncthreads();
+  const Plane<T> P = plane_of_block<T>(cd, smem);
   cplx<T>* st = (cplx<T>*)cd.sticks + ((size_t)pair * cd.N3 + z) * cd.nst;
-  for (int s = tid; s < cd.nst; s += nthr) {
-    const int xy = cd.stick_xy[s];
-    A[(xy >> 16) * N1 + (xy & 0xFFFF)] = st[s];
+  const T* V = (const T*)cd.veff_t + (size_t)z * N1 * N2;
+  // a value of every cache line of V, read here so that the plane is near when
+  // it is needed
+  const T ahead = V[min((int)(threadIdx.x * (128 / sizeof(T))), N1 * N2 - 1)];
+  plane_fill<T>(cd, P, st, true);
+  const int n1 = cd.plan[0].nr;
+  for (int pass = 0; pass < 4; ++pass) {  // y, x, (x, V, x), x, y: one copy of the stages
+    if (pass == 2) {
+      asm volatile("" ::"v"(ahead));
+      switch (cd.plan[0].r[n1 - 1]) {
+#define SGO_RADIX(r)                      \
+  case r:                                 \
+    plane_vmul<T, r>(P, N1, N2, V);       \
+    break;
+        SGO_LDS_RADICES(SGO_RADIX)
+#undef SGO_RADIX
+      }
+    }
+    const bool y = pass == 0 || pass == 3;
+    lds_stages<T>(P.A, y ? P.cols : P.rows, cd.plan[y ? 1 : 0], y ? P.tw2 : P.tw1, pass >= 2,
+                  pass >= 2 ? (T)-1 : (T)1, 0, y ? cd.plan[1].nr : n1 - 1);
   }
-  __syncthreads();
-  cplx<T>* r = lds_fft(A, Bf, cd.plan[1], N1, N1, 1, tw2, +1, tid, nthr);  // along y
-  cplx<T>* o = r == A ? Bf : A;
-  r = lds_fft(r, o, cd.plan[0], N2, 1, N1, tw1, +1, tid, nthr);            // along x
-  const T* V = (const T*)cd.veff_t + (size_t)z * NP;
-  for (int e = tid; e < NP; e += nthr) {
-    const T v = V[e];
-    r[e].x *= v;
-    r[e].y *= v;
-  }
-  __syncthreads();
-  o = r == A ? Bf : A;
-  r = lds_fft(r, o, cd.plan[0], N2, 1, N1, tw1, -1, tid, nthr);
-  o = r == A ? Bf : A;
-  r = lds_fft(r, o, cd.plan[1], N1, N1, 1, tw2, -1, tid, nthr);
-  for (int s = tid; s < cd.nst; s += nthr) {
-    const int xy = cd.stick_xy[s];
-    st[s] = r[(xy >> 16) * N1 + (xy & 0xFFFF)];
+  const int* xy_of = cd.stick_xy;
+  for (int s = threadIdx.x; s < cd.nst; s += blockDim.x) {
+    const int xy = xy_of[s];
+    st[s] = P.A[(xy >> 16) * P.p + (xy & 0xFFFF)];
   }
 }
 
 // Density of one z-plane summed over a chunk of band pairs:
 // part[chunk][z][y][x] = sum_pairs f_a Re(u)^2 + f_b Im(u)^2, u = psi_a + i psi_b
 // (unnormalised transforms; the 1/Omega is applied when chunks are summed).
+// DR values a thread in registers: DR kNT >= N1 N2.
 constexpr int kDensRegs = 48;
-template <typename T>
+template <typename T, int DR>
 __global__ void __launch_bounds__(kNT) k_plane_density(const CandDesc* __restrict__ cds) {
   const CandDesc& cd = cds[blockIdx.z];
   if (!cd.active) return;
@@ -223,46 +316,43 @@ __global__ void __launch_bounds__(kNT) k_plane_density(const CandDesc* __restric
   const int N1 = cd.N1, N2 = cd.N2, NP = N1 * N2;
   const int tid = threadIdx.x, nthr = blockDim.x;
   extern __shared__ __align__(16) char smem[];
-  cplx<T>* tw1 = (cplx<T>*)smem;
-  cplx<T>* tw2 = tw1 + kMaxFftN;
-  cplx<T>* A = tw2 + kMaxFftN;
-  cplx<T>* Bf = A + NP;
-  fill_twiddles(tw1, N1, tid, nthr);
-  fill_twiddles(tw2, N2, tid, nthr);
-  double acc[kDensRegs];
+  const Plane<T> P = plane_of_block<T>(cd, smem);
+  const float in1 = 1.0f / N1;
+  double acc[DR];
 #pragma unroll
-  for (int k = 0; k < kDensRegs; ++k) acc[k] = 0.0;
+  for (int k = 0; k < DR; ++k) acc[k] = 0.0;
   const int per = (cd.npair + cd.ndens_chunk - 1) / cd.ndens_chunk;
   const int p0 = chunk * per, p1 = min(cd.npair, p0 + per);
   for (int pair = p0; pair < p1; ++pair) {
-    for (int e = tid; e < NP; e += nthr) A[e] = {(T)0, (T)0};
-    __syncthreads();
-    const cplx<T>* st = (const cplx<T>*)cd.sticks + ((size_t)pair * cd.N3 + z) * cd.nst;
-    for (int s = tid; s < cd.nst; s += nthr) {
-      const int xy = cd.stick_xy[s];
-      A[(xy >> 16) * N1 + (xy & 0xFFFF)] = st[s];
-    }
-    __syncthreads();
-    cplx<T>* r = lds_fft(A, Bf, cd.plan[1], N1, N1, 1, tw2, +1, tid, nthr);
-    cplx<T>* o = r == A ? Bf : A;
-    r = lds_fft(r, o, cd.plan[0], N2, 1, N1, tw1, +1, tid, nthr);
+    plane_fill<T>(cd, P, (const cplx<T>*)cd.sticks + ((size_t)pair * cd.N3 + z) * cd.nst, pair == p0);
+    for (int ax = 1; ax >= 0; --ax)
+      lds_stages<T>(P.A, ax ? P.cols : P.rows, cd.plan[ax], ax ? P.tw2 : P.tw1, false, (T)1, 0, cd.plan[ax].nr);
     const double fa = cd.occ[2 * pair];
     const double fb = 2 * pair + 1 < cd.nb ? cd.occ[2 * pair + 1] : 0.0;
 #pragma unroll
-    for (int k = 0; k < kDensRegs; ++k) {
+    for (int k = 0; k < DR; ++k) {
       const int e = tid + k * nthr;
       if (e < NP) {
-        const double ux = (double)r[e].x, uy = (double)r[e].y;
+        const cplx<T> u = P.A[e + (P.p - N1) * line_div(e, in1)];
+        const double ux = (double)u.x, uy = (double)u.y;
         acc[k] += fa * ux * ux + fb * uy * uy;
       }
     }
     __syncthreads();
   }
+  if (p0 >= p1) {  // no pair, no tables: zeros
+    double* o = cd.dens_part + (size_t)chunk * cd.ntot + (size_t)z * NP;
+    for (int e = tid; e < NP; e += nthr) o[e] = 0.0;
+    return;
+  }
   double* out = cd.dens_part + (size_t)chunk * cd.ntot + (size_t)z * NP;
 #pragma unroll
-  for (int k = 0; k < kDensRegs; ++k) {
+  for (int k = 0; k < DR; ++k) {
     const int e = tid + k * nthr;
-    if (e < NP) out[e] = acc[k];
+    if (e < NP) {
+      const int l = line_div(e, in1);
+      out[(int)P.nat2[l] * N1 + P.nat1[e - l * N1]] = acc[k];
+    }
   }
 }
 
@@ -1258,11 +1348,11 @@ __global__ void k_potential_finalize(const CandDesc* __restrict__ cds) {
 template <typename T>
 static size_t z_lds(const BatchGeom& g) {
   const int nloc = 2 * g.sp_chunk;
-  return sizeof(cplx<T>) * (kMaxFftN + 2 * (size_t)nloc * g.N3max);
+  return sizeof(cplx<T>) * (kMaxFftN + (size_t)nloc * (g.N3max | 1)) + kMaxFftN;
 }
 template <typename T>
 static size_t plane_lds(const BatchGeom& g) {
-  return sizeof(cplx<T>) * (2 * kMaxFftN + 2 * (size_t)g.plane_max);
+  return sizeof(cplx<T>) * (2 * kMaxFftN + (size_t)g.plane_max + g.N2max) + 2 * kMaxFftN;
 }
 
 template <typename T>
@@ -1326,7 +1416,12 @@ void launch_density(const LaunchCtx& L) {
   } else {
     dim3 gp(g.N3max, g.dens_chunks, g.ncand);
     prof_before("k_plane_density", L.stream);
-    hipLaunchKernelGGL(k_plane_density<T>, gp, dim3(kNT), plane_lds<T>(g), L.stream, L.desc);
+    if (g.plane_max <= 8 * kNT)
+      hipLaunchKernelGGL((k_plane_density<T, 8>), gp, dim3(kNT), plane_lds<T>(g), L.stream, L.desc);
+    else if (g.plane_max <= 16 * kNT)
+      hipLaunchKernelGGL((k_plane_density<T, 16>), gp, dim3(kNT), plane_lds<T>(g), L.stream, L.desc);
+    else
+      hipLaunchKernelGGL((k_plane_density<T, kDensRegs>), gp, dim3(kNT), plane_lds<T>(g), L.stream, L.desc);
     check_launch("k_plane_density");
     prof_after("k_plane_density", L.stream);
   }
@@ -1572,7 +1667,9 @@ static void configure_t() {
   allow_lds((const void*)k_z_inverse<T>);
   allow_lds((const void*)k_z_forward<T>);
   allow_lds((const void*)k_plane_hpsi<T>);
-  allow_lds((const void*)k_plane_density<T>);
+  allow_lds((const void*)k_plane_density<T, 8>);
+  allow_lds((const void*)k_plane_density<T, 16>);
+  allow_lds((const void*)k_plane_density<T, kDensRegs>);
   allow_lds((const void*)k_gemm_acc<T, 1>);
   allow_lds((const void*)k_gemm_acc<T, 2>);
   allow_lds((const void*)k_gemm_acc<T, 5>);
