@@ -901,15 +901,15 @@ class Engine {
   }
 
   // Orthonormalise (Cholesky) and rotate to the Ritz vectors of the band
-  // subspace.  Intermediate calls within an SCF iteration may stop after
+  // subspace the first `narr` of X, HX and D.  Intermediate calls within an SCF iteration may stop after
   // `sweeps` Jacobi sweeps; the last one converges fully.
   template <typename T>
-  void subspace_rotate(const LaunchCtx& L, bool with_d, int sweeps) {
+  void subspace_rotate(const LaunchCtx& L, int narr, int sweeps) {
     int a[2] = {W_X, W_X}, b[2] = {W_X, W_HX}, o[2] = {M_S, M_H};
     launch_gram<T>(L, 2, a, b, o);
     launch_subspace(L, 3, sweeps);
     int y[3] = {W_X, W_HX, W_D};
-    launch_gemm_acc<T>(L, with_d ? 3 : 2, y, y, M_M, 0.0, 1.0, 0);
+    launch_gemm_acc<T>(L, narr, y, y, M_M, 0.0, 1.0, 0);
   }
 
   // All-band CG of Algorithm 1: at most ncg steps; with cg_tol > 0 a
@@ -919,7 +919,7 @@ class Engine {
   void eigensolver(const LaunchCtx& L, int ncg, double cg_tol) {
     const int inter = tune("SGO_RR_SWEEPS", 1);
     launch_hpsi<T>(L, W_X);
-    subspace_rotate<T>(L, false, inter);
+    subspace_rotate<T>(L, 2, inter);
     for (int k = 0; k < ncg; ++k) {
       launch_cg_direction<T>(L, k == 0 ? 1 : 0);
       if (cg_tol > 0.0) launch_cg_gate(L, cg_tol);
@@ -929,11 +929,14 @@ class Engine {
       launch_gemm_acc<T>(L, 1, y, aa, M_C, 1.0, -1.0, 0);
       launch_hpsi<T>(L, W_D);
       launch_linemin<T>(L);
-      subspace_rotate<T>(L, true, k + 1 == ncg ? 40 : inter);
+      // after the last step only the bands are read again (H X and D start anew
+      // with the next potential), except by the gated diagonalisation below
+      const bool last = k + 1 == ncg;
+      subspace_rotate<T>(L, last && !(cg_tol > 0.0) ? 1 : 3, last ? 40 : inter);
     }
     if (cg_tol > 0.0) {
       launch_cg_release(L, 0);
-      subspace_rotate<T>(L, false, 40);
+      subspace_rotate<T>(L, 2, 40);
       launch_cg_release(L, 1);
     }
   }
@@ -1339,11 +1342,11 @@ class Engine {
   }
 
   // Rayleigh-Ritz: S = X^H X, H = X^H HX, Cholesky and complex Jacobi, then X,
-  // HX (and D) <- . M, at every k
-  void k_rr(bool with_d) {
+  // HX and D (the first narr) <- . M, at every k
+  void k_rr(int narr) {
     kpt_zdot(kset_, 2, {W_X, W_X, 0}, {W_X, W_HX, 1});
     kpt_subspace(kset_, kfail_);
-    kpt_zgemm(kset_, -1, W_X | W_HX << 4 | W_D << 8, with_d ? 3 : 2, 0, 1.0, 0.0, nullptr);
+    kpt_zgemm(kset_, -1, W_X | W_HX << 4 | W_D << 8, narr, 0, 1.0, 0.0, nullptr);
   }
 
   // Algorithm 1 at every k: H psi, subspace diagonalisation, then ncg steps
@@ -1351,14 +1354,14 @@ class Engine {
   // Rayleigh-Ritz.
   void k_eigensolve(const HostCand& c, int ncg) {
     kpt_hpsi(kset_, W_X, W_HX, c.d.veff_r, c.d.hproj);
-    k_rr(false);
+    k_rr(2);
     for (int st = 0; st < ncg; ++st) {
       kpt_cg_dir(kset_, st == 0 ? 1 : 0);
       kpt_zdot(kset_, 1, {W_X, W_D, 2}, {});
       kpt_zgemm(kset_, W_X, W_D, 1, 1, -1.0, 1.0, nullptr);
       kpt_hpsi(kset_, W_D, W_HD, c.d.veff_r, c.d.hproj);
       kpt_linemin(kset_);
-      k_rr(true);
+      k_rr(st + 1 == ncg ? 1 : 3);  // H X and D start anew with the next potential
     }
   }
 
