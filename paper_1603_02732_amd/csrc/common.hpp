@@ -73,7 +73,8 @@ struct CandDesc {
   int Kp, pad_kp;   // Kp: row stride of band arrays (K rounded up to 32, zero padded)
   int nsp, nst, nproj, nat;
   int occ_kind, nocc, active, ncand_index;
-  int pl_nx, pl_nxl, pl_sx, pl_pad;  // active x columns of the planes (register FFT kernels)
+  int pl_nx, pl_nxl, pl_sx;  // active x columns of the planes (register FFT kernels)
+  int pos_off;               // start of this candidate in arrays [all atoms][3]
   int np16, pad_np;     // nproj rounded up to 16 (BF16 projector tiles)
   double sigma, nelec, omega, pad0;
   double A[9];

@@ -254,7 +254,9 @@ class Engine {
     k_free();
     for (auto& c : cands_) free_cand(c);
     if (d_species_) (void)hipFree(d_species_);
-    if (d_desc_) (void)hipFree(d_desc_);
+    if (stage_d_) (void)hipFree(stage_d_);
+    if (stage_h_) (void)hipHostFree(stage_h_);
+    if (stage_done_) (void)hipEventDestroy(stage_done_);
     if (d_desc_act_) (void)hipFree(d_desc_act_);
     if (d_iter_) (void)hipFree(d_iter_);
     if (d_scal_all_) (void)hipFree(d_scal_all_);
@@ -583,11 +585,13 @@ class Engine {
         {(void**)&d.beta, (size_t)c.nproj * K * ts + 256},
         {(void**)&d.beta16, prec_ == SGO_FP32_BF16PROJ ? (size_t)2 * np16 * K * 2 + 256 : 0},
         {(void**)&d.betaT16, prec_ == SGO_FP32_BF16PROJ ? (size_t)2 * np16 * K * 2 + 256 : 0},
+        // the arrays that upload_static fills, one after another from kin to agroup
         {(void**)&d.kin, c.npwh * sizeof(double)}, {(void**)&d.gmeta, c.npwh * sizeof(int)},
         {(void**)&d.sp_off, (c.nsp + 1) * sizeof(int)}, {(void**)&d.stick_xy, c.nst * sizeof(int)},
         {(void**)&d.gmill, 3 * c.npwh * sizeof(int)},
         {(void**)&d.hproj, c.nproj * sizeof(double) + 8}, {(void**)&d.proj_atom, c.nproj * sizeof(int) + 8},
         {(void**)&d.proj_lm, c.nproj * sizeof(int) + 8}, {(void**)&d.proj_r, c.nproj * sizeof(double) + 8},
+        {(void**)&d.spec, (size_t)c.nat * sizeof(int)}, {(void**)&d.agroup, c.agroup.size() * sizeof(int)},
         {(void**)&d.S, nb * nb * 8}, {(void**)&d.Hs, nb * nb * 8}, {(void**)&d.M, nb * nb * 8},
         {(void**)&d.C, nbm * nb * 8}, {(void**)&d.eps, nb * 8}, {(void**)&d.occ, nb * 8},
         {(void**)&d.gam, nb * 8}, {(void**)&d.bandw, nb * 8}, {(void**)&d.resn, nb * 8},
@@ -596,8 +600,7 @@ class Engine {
         {(void**)&d.rho_out_G, nt * 16}, {(void**)&d.hist_in, kMaxHist * nt * hist_bytes()},
         {(void**)&d.hist_res, kMaxHist * nt * hist_bytes()}, {(void**)&d.pulay, kMaxHist * kMaxHist * 8},
         {(void**)&d.coef, kMaxHist * 8}, {(void**)&d.dens_part, (size_t)c.dens_chunks * nt * 8},
-        {(void**)&d.pos, (size_t)3 * c.nat * 8}, {(void**)&d.spec, (size_t)c.nat * sizeof(int)},
-        {(void**)&d.phase, (size_t)3 * c.nat * c.phase_m * 16}, {(void**)&d.agroup, c.agroup.size() * sizeof(int)},
+        {(void**)&d.pos, (size_t)3 * c.nat * 8}, {(void**)&d.phase, (size_t)3 * c.nat * c.phase_m * 16},
         {(void**)&d.force, (size_t)3 * c.nat * 8}, {(void**)&d.force_ew, (size_t)3 * c.nat * 8},
         {(void**)&d.force_part, (size_t)6 * c.nat * 8}, {(void**)&d.nlwork, (size_t)c.nproj * nb * 4 * 8 + 8},
         {(void**)&d.stwork, stress_layout(c.nb, c.nproj, c.nat).total * 8},
@@ -619,7 +622,6 @@ class Engine {
     // stream-ordered (the legacy null stream would wait on every blocking
     // stream, and fail while another batch's thread captures a graph)
     HIPCHK(hipMemsetAsync(c.mem, 0, total, stream_));
-    HIPCHK(hipStreamSynchronize(stream_));
     size_t off = 0;
     for (auto& it : items) {
       *it.p = c.mem + off;
@@ -671,24 +673,25 @@ class Engine {
     d.ew_nimg = c.ew_nimg;
     d.phase_m = c.phase_m;
     d.nagroup = (int)c.agroup.size() / kAtomGroup;
-    auto up = [&](const void* dst, const void* src, size_t bytes) {
-      if (bytes) {
-        HIPCHK(hipMemcpyAsync((void*)dst, src, bytes, hipMemcpyHostToDevice, stream_));
-        HIPCHK(hipStreamSynchronize(stream_));
-      }
+    // one copy of the adjacent arrays
+    char* const first = (char*)(double*)d.kin;
+    std::vector<char> blob((char*)(int*)d.agroup + c.agroup.size() * 4 - first, 0);
+    auto put = [&](const void* dst, const void* src, size_t bytes) {
+      if (bytes) std::memcpy(blob.data() + ((const char*)dst - first), src, bytes);
     };
-    up(d.kin, c.kin.data(), c.npwh * 8);
-    up(d.gmeta, c.gmeta.data(), c.npwh * 4);
-    up(d.sp_off, c.sp_off.data(), (c.nsp + 1) * 4);
-    up(d.stick_xy, c.stick_xy.data(), c.nst * 4);
-    up(d.gmill, c.gmill.data(), 3 * c.npwh * 4);
-    up(d.hproj, c.hproj.data(), c.nproj * 8);
-    up(d.proj_atom, c.proj_atom.data(), c.nproj * 4);
-    up(d.proj_lm, c.proj_lm.data(), c.nproj * 4);
-    up(d.proj_r, c.proj_r.data(), c.nproj * 8);
-    up(d.spec, c.spec.data(), c.nat * 4);
-    up(d.agroup, c.agroup.data(), c.agroup.size() * 4);
-    up(d.pos, c.pos.data(), 3 * c.nat * 8);
+    put(d.kin, c.kin.data(), c.npwh * 8);
+    put(d.gmeta, c.gmeta.data(), c.npwh * 4);
+    put(d.sp_off, c.sp_off.data(), (c.nsp + 1) * 4);
+    put(d.stick_xy, c.stick_xy.data(), c.nst * 4);
+    put(d.gmill, c.gmill.data(), 3 * c.npwh * 4);
+    put(d.hproj, c.hproj.data(), c.nproj * 8);
+    put(d.proj_atom, c.proj_atom.data(), c.nproj * 4);
+    put(d.proj_lm, c.proj_lm.data(), c.nproj * 4);
+    put(d.proj_r, c.proj_r.data(), c.nproj * 8);
+    put(d.spec, c.spec.data(), c.nat * 4);
+    put(d.agroup, c.agroup.data(), c.agroup.size() * 4);
+    HIPCHK(hipMemcpyAsync(first, blob.data(), blob.size(), hipMemcpyHostToDevice, stream_));
+    HIPCHK(hipStreamSynchronize(stream_));
   }
 
   void free_cand(HostCand& c) {
@@ -781,23 +784,41 @@ class Engine {
     if (std::max(g.nb_max, g.nproj_max) > 600) throw Error(SGO_EINVAL, "too many projectors");
   }
 
-  void upload_desc() {
-    std::vector<CandDesc> h(cands_.size());
-    int nact = 0;
-    for (size_t i = 0; i < cands_.size(); ++i) {
+  // The descriptors, and the positions behind them with `positions`, from one
+  // pinned buffer by one copy in stream order.  The buffer is not written
+  // again before its last copy is done.
+  void upload_desc(bool positions = false) {
+    const size_t n = cands_.size(), nd = (sizeof(CandDesc) * n + 255) / 256 * 256;
+    size_t np = 0;
+    for (auto& c : cands_) np += 3 * (size_t)c.nat;
+    if (stage_done_) HIPCHK(hipEventSynchronize(stage_done_));
+    else HIPCHK(hipEventCreateWithFlags(&stage_done_, hipEventDisableTiming));
+    if (stage_cap_ < nd + 8 * np) {
+      if (stage_d_) (void)hipFree(stage_d_);
+      if (stage_h_) (void)hipHostFree(stage_h_);
+      stage_d_ = stage_h_ = nullptr;
+      stage_cap_ = 0;
+      HIPCHK(hipMalloc(&stage_d_, nd + 8 * np));
+      HIPCHK(hipHostMalloc((void**)&stage_h_, nd + 8 * np, hipHostMallocDefault));
+      stage_cap_ = nd + 8 * np;
+    }
+    d_desc_ = (CandDesc*)stage_d_;
+    stage_pos_ = (const double*)(stage_d_ + nd);
+    CandDesc* h = (CandDesc*)stage_h_;
+    double* hp = (double*)(stage_h_ + nd);
+    int nact = 0, off = 0;
+    for (size_t i = 0; i < n; ++i) {
       h[i] = cands_[i].d;
       h[i].ncand_index = (int)i;
+      h[i].pos_off = off;
+      if (positions) std::memcpy(hp + off, cands_[i].pos.data(), 3 * cands_[i].nat * 8);
+      off += 3 * cands_[i].nat;
       nact += h[i].active ? 1 : 0;
     }
     t_active = nact;
-    if (!d_desc_ || desc_cap_ < cands_.size()) {
-      if (d_desc_) (void)hipFree(d_desc_);
-      HIPCHK(hipMalloc(&d_desc_, sizeof(CandDesc) * cands_.size()));
-      desc_cap_ = cands_.size();
-    }
-    HIPCHK(hipMemcpyAsync(d_desc_, h.data(), sizeof(CandDesc) * h.size(), hipMemcpyHostToDevice,
+    HIPCHK(hipMemcpyAsync(stage_d_, stage_h_, positions ? nd + 8 * np : sizeof(CandDesc) * n, hipMemcpyHostToDevice,
                           stream_));
-    HIPCHK(hipStreamSynchronize(stream_));
+    HIPCHK(hipEventRecord(stage_done_, stream_));
   }
 
   LaunchCtx ctx(const BatchGeom& g) {
@@ -878,18 +899,15 @@ class Engine {
       } else {
         c.d.hist_len = hist;
         c.d.ndens_chunk = c.dens_chunks;
-        HIPCHK(hipMemcpyAsync((void*)c.d.pos, c.pos.data(), 3 * c.nat * 8, hipMemcpyHostToDevice,
-                              stream_));
-        HIPCHK(hipStreamSynchronize(stream_));
       }
       c.d.seed = seed;
       c.d.active = 1;
       c.d.iter_state = d_iter_;
       c.status = SGO_OK;
       c.info = sgo_scf_info{};
-      HIPCHK(hipMemsetAsync(c.d.scal, 0, S_COUNT * 8, stream_));
     }
-    upload_desc();
+    upload_desc(true);
+    launch_scatter_state(ctx(g), stage_pos_);
     return g;
   }
 
@@ -951,27 +969,64 @@ class Engine {
     launch_gemm_acc<T>(L, 1, y, y, M_M, 0.0, 1.0, 0);
   }
 
+  // Device buffer and pinned copy of n doubles for gathered results.
+  void ensure_gather(size_t n) {
+    if (scal_cap_ >= n) return;
+    if (d_scal_all_) (void)hipFree(d_scal_all_);
+    if (h_scal_all_) (void)hipHostFree(h_scal_all_);
+    d_scal_all_ = nullptr;
+    h_scal_all_ = nullptr;
+    scal_cap_ = 0;
+    HIPCHK(hipMalloc(&d_scal_all_, n * 8));
+    HIPCHK(hipHostMalloc((void**)&h_scal_all_, n * 8, hipHostMallocDefault));
+    scal_cap_ = n;
+  }
+
   // Status scalars of every candidate: one gather kernel and one copy into
   // pinned host memory.
   void read_scal(std::vector<std::array<double, S_COUNT>>& out) {
     const size_t n = cands_.size();
     out.resize(n);
-    if (scal_cap_ < n) {
-      if (d_scal_all_) (void)hipFree(d_scal_all_);
-      if (h_scal_all_) (void)hipHostFree(h_scal_all_);
-      d_scal_all_ = nullptr;
-      h_scal_all_ = nullptr;
-      scal_cap_ = 0;
-      HIPCHK(hipMalloc(&d_scal_all_, n * S_COUNT * 8));
-      HIPCHK(hipHostMalloc((void**)&h_scal_all_, n * S_COUNT * 8, hipHostMallocDefault));
-      scal_cap_ = n;
-    }
+    ensure_gather(n * S_COUNT);
     LaunchCtx L = ctx(BatchGeom{});
     L.g.ncand = (int)n;
     launch_gather_scal(L, d_scal_all_);
     HIPCHK(hipMemcpyAsync(h_scal_all_, d_scal_all_, n * S_COUNT * 8, hipMemcpyDeviceToHost, stream_));
     HIPCHK(hipStreamSynchronize(stream_));
     for (size_t i = 0; i < n; ++i) std::memcpy(out[i].data(), h_scal_all_ + i * S_COUNT, S_COUNT * 8);
+  }
+
+  // Energies [ncand] and forces [all atoms][3] of a finished scf() the same way.
+  // Either may be null.
+  void read_results(double* energies, double* forces) {
+    if (!energies && !forces) return;
+    HIPCHK(hipSetDevice(device_));
+    const size_t n = cands_.size();
+    size_t m = n;
+    for (auto& c : cands_) m += 3 * (size_t)c.nat;
+    ensure_gather(m);
+    LaunchCtx L = ctx(BatchGeom{});
+    L.g.ncand = (int)n;
+    launch_gather_results(L, d_scal_all_);
+    HIPCHK(hipMemcpyAsync(h_scal_all_, d_scal_all_, m * 8, hipMemcpyDeviceToHost, stream_));
+    HIPCHK(hipStreamSynchronize(stream_));
+    if (energies) std::memcpy(energies, h_scal_all_, n * 8);
+    if (forces) std::memcpy(forces, h_scal_all_ + n, (m - n) * 8);
+  }
+
+  // The same, a vector of forces per candidate.
+  void read_all(std::vector<std::vector<double>>& force, std::vector<double>* en) {
+    std::vector<double> f;
+    for (size_t i = 0; i < cands_.size(); ++i) {
+      force[i].resize(3 * cands_[i].nat);
+      f.resize(f.size() + 3 * cands_[i].nat);
+    }
+    read_results(en ? en->data() : nullptr, f.data());
+    size_t off = 0;
+    for (auto& v : force) {
+      std::memcpy(v.data(), f.data() + off, v.size() * 8);
+      off += v.size();
+    }
   }
 
   // One SCF iteration after the first: mix the previous output into the new
@@ -1038,6 +1093,7 @@ class Engine {
     // the K-iteration graphs, or the Jacobi sweeps over the GPU
     if ((o.use_graph || g.nb_max >= g.jac_grid) && !stream_) {
       if (!own_stream_) HIPCHK(hipStreamCreateWithFlags(&own_stream_, hipStreamNonBlocking));
+      HIPCHK(hipStreamSynchronize(stream_));  // what prepare() has queued
       stream_ = own_stream_;
     }
     struct Restore {
@@ -1485,15 +1541,9 @@ class Engine {
                         std::vector<double>* en) {
       for (int i = 0; i < n; ++i) move_atoms(i, pos[i].data());
       (void)scf(o);
+      read_all(force, en);
       for (int i = 0; i < n; ++i) {
         HostCand& c = cands_[i];
-        force[i].resize(3 * c.nat);
-        get(c.d.force, force[i].data(), 3 * c.nat * sizeof(double));
-        if (en) {
-          double sc[S_COUNT];
-          get_scal(c, sc);
-          (*en)[i] = sc[S_ETOT];
-        }
         if (c.status < status[i]) status[i] = c.status;
       }
     };
@@ -1647,15 +1697,9 @@ class Engine {
       for (int i = 0; i < n; ++i) move_atoms(i, pos[i].data());
       const int rc = scf(o);
       (void)rc;
+      read_all(force, en);
       for (int i = 0; i < n; ++i) {
         HostCand& c = cands_[i];
-        force[i].resize(3 * c.nat);
-        get(c.d.force, force[i].data(), 3 * c.nat * sizeof(double));
-        if (en) {
-          double s[S_COUNT];
-          get_scal(c, s);
-          (*en)[i] = s[S_ETOT];
-        }
         if (c.status < status[i]) status[i] = c.status;
       }
     };
@@ -1882,8 +1926,11 @@ class Engine {
   std::vector<SpeciesHost> species_;
   SpeciesDev* d_species_ = nullptr;
   std::vector<HostCand> cands_;
-  CandDesc* d_desc_ = nullptr;
-  size_t desc_cap_ = 0;
+  CandDesc* d_desc_ = nullptr;            // in stage_d_
+  char *stage_h_ = nullptr, *stage_d_ = nullptr;  // descriptors, positions: pinned, device
+  const double* stage_pos_ = nullptr;
+  size_t stage_cap_ = 0;
+  hipEvent_t stage_done_ = nullptr;       // the last copy out of stage_h_
   CandDesc* d_desc_act_ = nullptr;  // descriptors of the active candidates only
   size_t desc_act_cap_ = 0;
   int* d_iter_ = nullptr;             // SCF iteration counter (device)
@@ -2562,16 +2609,9 @@ int sgo_batch_scf(sgo_batch* b, const sgo_scf_opts* opts, double* energies, doub
     if (b->eng->size() == 0) throw Error(SGO_ESTATE, "empty batch");
     const sgo_scf_opts o = opts_or_default(opts);
     int rc = b->eng->scf(o);
-    size_t off = 0;
+    b->eng->read_results(energies, forces);
     for (int i = 0; i < b->eng->size(); ++i) {
       auto& hc = b->eng->cand(i);
-      if (energies) {
-        double s[sgo::S_COUNT];
-        b->eng->get_scal(hc, s);
-        energies[i] = s[sgo::S_ETOT];
-      }
-      if (forces) b->eng->get(hc.d.force, forces + off, 3 * hc.nat * sizeof(double));
-      off += 3 * hc.nat;
       if (status) status[i] = hc.status;
       b->status[i] = hc.status;
     }
@@ -2640,10 +2680,10 @@ int sgo_batch_relax_cg(sgo_batch* b, int nsteps, const sgo_scf_opts* opts, doubl
     if (nsteps < 0) throw Error(SGO_EINVAL, "nsteps must be >= 0");
     const sgo_scf_opts o = opts_or_default(opts);
     const int rc = b->eng->relax_cg(nsteps, o, energies);
+    b->eng->read_results(nullptr, forces);
     size_t off = 0;
     for (int i = 0; i < b->eng->size(); ++i) {
       auto& hc = b->eng->cand(i);
-      if (forces) b->eng->get(hc.d.force, forces + off, 3 * hc.nat * sizeof(double));
       if (positions) std::memcpy(positions + off, hc.pos.data(), 3 * hc.nat * sizeof(double));
       off += 3 * hc.nat;
       if (status) status[i] = hc.status;
@@ -2661,10 +2701,10 @@ int sgo_batch_relax_pcg(sgo_batch* b, int nsteps, int refit, const sgo_scf_opts*
     if (nsteps < 0 || refit < 0) throw Error(SGO_EINVAL, "nsteps and refit must be >= 0");
     const sgo_scf_opts o = opts_or_default(opts);
     const int rc = b->eng->relax_pcg(nsteps, o, energies, refit, params);
+    b->eng->read_results(nullptr, forces);
     size_t off = 0;
     for (int i = 0; i < b->eng->size(); ++i) {
       auto& hc = b->eng->cand(i);
-      if (forces) b->eng->get(hc.d.force, forces + off, 3 * hc.nat * sizeof(double));
       if (positions) std::memcpy(positions + off, hc.pos.data(), 3 * hc.nat * sizeof(double));
       off += 3 * hc.nat;
       if (status) status[i] = hc.status;
@@ -2681,10 +2721,10 @@ int sgo_batch_relax_cls(sgo_batch* b, int nsteps, const sgo_scf_opts* opts, doub
     if (nsteps < 0) throw Error(SGO_EINVAL, "nsteps must be >= 0");
     const sgo_scf_opts o = opts_or_default(opts);
     const int rc = b->eng->relax_cls(nsteps, o, energies, params);
+    b->eng->read_results(nullptr, forces);
     size_t off = 0;
     for (int i = 0; i < b->eng->size(); ++i) {
       auto& hc = b->eng->cand(i);
-      if (forces) b->eng->get(hc.d.force, forces + off, 3 * hc.nat * sizeof(double));
       if (positions) std::memcpy(positions + off, hc.pos.data(), 3 * hc.nat * sizeof(double));
       off += 3 * hc.nat;
       if (status) status[i] = hc.status;

@@ -1588,6 +1588,26 @@ void launch_gather_scal(const LaunchCtx& L, double* out) {
   hipLaunchKernelGGL(k_gather_scal, dim3(L.g.ncand), dim3(64), 0, L.stream, L.desc, out);
   check_launch("k_gather_scal");
 }
+__global__ void k_scatter_state(const CandDesc* __restrict__ cds, const double* __restrict__ pos) {
+  const CandDesc& cd = cds[blockIdx.x];
+  double* to = const_cast<double*>((const double*)cd.pos);
+  for (int k = threadIdx.x; k < 3 * cd.nat; k += blockDim.x) to[k] = pos[cd.pos_off + k];
+  for (int k = threadIdx.x; k < S_COUNT; k += blockDim.x) cd.scal[k] = 0.0;
+}
+void launch_scatter_state(const LaunchCtx& L, const double* pos) {
+  hipLaunchKernelGGL(k_scatter_state, dim3(L.g.ncand), dim3(64), 0, L.stream, L.desc, pos);
+  check_launch("k_scatter_state");
+}
+__global__ void k_gather_results(const CandDesc* __restrict__ cds, double* __restrict__ out) {
+  const CandDesc& cd = cds[blockIdx.x];
+  double* f = out + gridDim.x + cd.pos_off;
+  if (threadIdx.x == 0) out[blockIdx.x] = cd.scal[S_ETOT];
+  for (int k = threadIdx.x; k < 3 * cd.nat; k += blockDim.x) f[k] = cd.force[k];
+}
+void launch_gather_results(const LaunchCtx& L, double* out) {
+  hipLaunchKernelGGL(k_gather_results, dim3(L.g.ncand), dim3(64), 0, L.stream, L.desc, out);
+  check_launch("k_gather_results");
+}
 // Residual gate of the all-band CG steps.  Algorithm 1 repeats its CG steps
 // until the band residuals meet the convergence condition; here a candidate
 // leaves the remaining CG steps of the current SCF iteration once every band

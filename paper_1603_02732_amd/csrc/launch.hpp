@@ -122,6 +122,10 @@ void launch_force_local(const LaunchCtx& L);
 void launch_force_finalize(const LaunchCtx& L);
 void launch_stress_grid(const LaunchCtx& L);
 void launch_gather_scal(const LaunchCtx& L, double* out);  // [ncand][S_COUNT]  // grid, Ewald and finalize kernels
+// positions of every candidate from pos [all atoms][3], status scalars to zero
+void launch_scatter_state(const LaunchCtx& L, const double* pos);
+// total energies [ncand], then forces [all atoms][3]
+void launch_gather_results(const LaunchCtx& L, double* out);
 
 // Enable large dynamic LDS for every kernel (once per process per device).
 void configure_kernels();
