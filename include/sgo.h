@@ -313,7 +313,7 @@ int sgo_subspace_solve_noalloc(int device, int n, int mode, const double* S, con
 
 /* Launch-schedule tuning (process-wide; read when a solve starts).  Keys:
  * "SGO_GRAM_KC" (K range of one split-K Gram block, multiple of 32),
- * "SGO_SUB_THREADS" (threads of the subspace solver's workgroup above 128
+ * "SGO_SUB_THREADS" (threads of the subspace solver's workgroup above 198
  * bands, 64..512; the smaller problems' kernels have their own),
  * "SGO_SP_CHUNK" (stick pairs per block of the LDS z transforms, used by
  * FP64 and by lines longer than 64; the FP32 register z passes take 16),

@@ -15,9 +15,33 @@
 
 namespace sgo {
 
+// Addresses of the entry (u, v) = (v, u) among n2 (n2 + 1) / 2.
 __device__ __forceinline__ int jac_tri(int u, int v) {  // packed lower triangle
   const int a = u > v ? u : v, b = u > v ? v : u;
   return a * (a + 1) / 2 + b;
+}
+// By pairs: with P >= Q the pairs that hold u and v, the block number t = P (P +
+// 1) / 2 + Q within one of four triangles, (top P, top Q), (bottom P, top Q),
+// (bottom P, bottom Q) and (top P, bottom Q) without P = Q.  A wavefront handles
+// consecutive blocks, so its four reads are four runs of consecutive words, and
+// its writes as well but for the ends of a row; packed by (u, v) half of them are
+// strides of about n2, different from lane to lane.
+__device__ __forceinline__ int jac_quad(int u, int v, int n2) {
+  const int np = n2 / 2, M = np * (np + 1) / 2;
+  const bool bu = u >= np, bv = v >= np;
+  const int pu = bu ? n2 - 1 - u : u, pv = bv ? n2 - 1 - v : v;
+  const bool sw = pu < pv;
+  const int P = sw ? pv : pu, Q = sw ? pu : pv, t = P * (P + 1) / 2 + Q;
+  const bool bP = sw ? bv : bu, bQ = sw ? bu : bv;
+  if (bP == bQ) return bP ? 2 * M + t : t;
+  return bP || P == Q ? M + t : 3 * M + t - P;
+}
+// QUAD from 65 bands on: the rounds of 112 bands 449 -> 437 us, of 164 bands 1.19 ->
+// 1.00 ms a call of the engine (4 to 5 sweeps on average); up to 64 a round is a chain of latencies and the longer way to the addresses
+// costs more (32 bands: 104 -> 106 us).
+template <bool QUAD>
+__device__ __forceinline__ int jac_addr(int u, int v, int n2) {
+  return QUAD ? jac_quad(u, v, n2) : jac_tri(u, v);
 }
 // Where a round's results go: the contents of position u move to jac_next(u).
 __device__ __forceinline__ int jac_next(int u, int n2) { return u == 0 ? 0 : (u == 1 ? n2 - 1 : u - 1); }
@@ -114,15 +138,28 @@ __device__ __forceinline__ void jac_row_step(double& top, double& bot, double c,
 
 // Off-diagonal norm below 1e-13 of the diagonal norm (one wavefront a row at a
 // time; every thread of the block takes part).
+template <bool QUAD>
 __device__ __forceinline__ bool jac_converged(const double* T, int n2, double* sh) {
   const int w = threadIdx.x >> 6, W = blockDim.x >> 6, lane = threadIdx.x & 63;
+  const int np = n2 / 2, M = np * (np + 1) / 2;
   double v[2] = {0.0, 0.0};
-  for (int u = w; u < n2; u += W)
-    for (int q = lane; q <= u; q += 64) {
-      const double a = T[u * (u + 1) / 2 + q];
-      if (q == u) v[1] += a * a;
-      else v[0] += a * a;
-    }
+  if (QUAD) {
+    for (int P = w; P < np; P += W)
+      for (int Q = lane; Q <= P; Q += 64) {
+        const int t = P * (P + 1) / 2 + Q;
+        const double a = T[t], b = T[2 * M + t], c = T[M + t], d = P != Q ? T[3 * M + t - P] : 0.0;
+        if (P == Q) v[1] += a * a + b * b;
+        else v[0] += a * a + b * b + d * d;
+        v[0] += c * c;
+      }
+  } else {
+    for (int u = w; u < n2; u += W)
+      for (int q = lane; q <= u; q += 64) {
+        const double a = T[u * (u + 1) / 2 + q];
+        if (q == u) v[1] += a * a;
+        else v[0] += a * a;
+      }
+  }
   block_sum<2>(v, sh);
   return __builtin_amdgcn_readfirstlane((int)!(2.0 * v[0] > 1e-26 * v[1] + 1e-300)) != 0;
 }
@@ -132,6 +169,7 @@ __device__ __forceinline__ bool jac_converged(const double* T, int n2, double* s
 // round reads them (rd) and where it leaves them (wr).
 struct JacBlock {
   int P, Q, rd[4], wr[4];
+  template <bool QUAD>
   __device__ __forceinline__ void init(int t, int n2) {
     P = (int)((sqrtf(8.0f * t + 1.0f) - 1.0f) * 0.5f);
     while (P * (P + 1) / 2 > t) --P;
@@ -139,14 +177,14 @@ struct JacBlock {
     Q = t - P * (P + 1) / 2;
     const int bp = n2 - 1 - P, bq = n2 - 1 - Q;
     const int tpn = jac_next(P, n2), bpn = jac_next(bp, n2), tqn = jac_next(Q, n2), bqn = jac_next(bq, n2);
-    rd[0] = jac_tri(P, Q);
-    rd[1] = jac_tri(bp, Q);
-    rd[2] = jac_tri(P, bq);
-    rd[3] = jac_tri(bp, bq);
-    wr[0] = jac_tri(tpn, tqn);
-    wr[1] = jac_tri(bpn, tqn);
-    wr[2] = jac_tri(tpn, bqn);
-    wr[3] = jac_tri(bpn, bqn);
+    rd[0] = jac_addr<QUAD>(P, Q, n2);
+    rd[1] = jac_addr<QUAD>(bp, Q, n2);
+    rd[2] = jac_addr<QUAD>(P, bq, n2);
+    rd[3] = jac_addr<QUAD>(bp, bq, n2);
+    wr[0] = jac_addr<QUAD>(tpn, tqn, n2);
+    wr[1] = jac_addr<QUAD>(bpn, tqn, n2);
+    wr[2] = jac_addr<QUAD>(tpn, bqn, n2);
+    wr[3] = jac_addr<QUAD>(bpn, bqn, n2);
   }
 };
 // x: the entries in that order, rotated in place; the rotated entry of a

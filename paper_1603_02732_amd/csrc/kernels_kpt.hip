@@ -460,13 +460,13 @@ template <int R>
 constexpr int kpt_sub_threads() { return R == 4 ? 512 : 1024; }
 template <int R>
 constexpr size_t kpt_sub_lds() {
-  return sizeof(zc) * (2 * (size_t)(8 * R) * (8 * R + 1) + 2 * (R == 4 ? 64 : 128)) + 2 * 32 * 3 * sizeof(double);
+  return sizeof(zc) * (2 * (size_t)(8 * R) * (8 * R + 1) + 2 * 64) + 2 * 32 * 3 * sizeof(double);
 }
 template <int R>
 __global__ void __launch_bounds__(kpt_sub_threads<R>()) k_kpt_sub(const KptDev* __restrict__ kd, int max_sweeps,
                                                                   int* __restrict__ fail) {
   const KptDev& kp = kd[blockIdx.x];
-  constexpr int N = 8 * R, LD = N + 1, TRI = N * (N + 1) / 2, NV = R == 4 ? 1 : 2;
+  constexpr int N = 8 * R, LD = N + 1, TRI = N * (N + 1) / 2;
   constexpr int STR = R == 4 ? 16 : 32, RPW = 64 / STR, SETS = R == 4 ? 2 : 5;
   const int n = kp.nb, n2 = n + (n & 1), np = n2 / 2, m = n2 - 1;
   const int tid = threadIdx.x, lane = tid & 63, W = blockDim.x >> 6;
@@ -475,7 +475,7 @@ __global__ void __launch_bounds__(kpt_sub_threads<R>()) k_kpt_sub(const KptDev* 
   zc* Hl = (zc*)smem;
   zc* Wl = Hl + N * LD;
   zc* prow = Wl + N * LD;
-  double* cs = (double*)(prow + 2 * NV * 64);  // [2][32][3]: c, t of two rounds
+  double* cs = (double*)(prow + 2 * 64);  // [2][32][3]: c, t of two rounds
   __shared__ double sh[16 * 2];
   __shared__ int rank[N];
   for (int u = w; u < n; u += W)
@@ -483,24 +483,16 @@ __global__ void __launch_bounds__(kpt_sub_threads<R>()) k_kpt_sub(const KptDev* 
       const zc a = kp.H[u * n + lane], b = kp.H[lane * n + u];
       Hl[u * LD + lane] = {0.5 * (a.x + b.x), 0.5 * (a.y - b.y)};
     }
-  zc v[R][NV];
-  double piv[R];
-  const int col = NV == 1 ? lane & 31 : lane;
+  // rows of S, then of W, as in the real step
+  zc v[R];
+  double dc = 1.0;  // the pivot of this lane's column
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int i = w + 8 * r;
-    const bool in = w < 8 && i < n && col < n;
-    zc s = in ? kp.S[max(i, col) * n + min(i, col)] : zc{0.0, 0.0};
-    if (col > i) s.y = -s.y;
-    if (col == i) s.y = 0.0;
-    const zc one = {in && i == col ? 1.0 : 0.0, 0.0};
-    if (NV == 1) {
-      v[r][0] = lane < 32 ? s : one;
-    } else {
-      v[r][0] = s;
-      v[r][NV - 1] = one;
-    }
-    piv[r] = 1.0;
+    const bool in = w < 8 && i < n && lane < n;
+    v[r] = in ? zc(kp.S[max(i, lane) * n + min(i, lane)]) : zc{0.0, 0.0};
+    if (lane > i) v[r].y = -v[r].y;
+    if (lane == i) v[r].y = 0.0;
   }
   bool ok = true;
 #pragma unroll
@@ -508,29 +500,26 @@ __global__ void __launch_bounds__(kpt_sub_threads<R>()) k_kpt_sub(const KptDev* 
     for (int kk = 0; kk < 8; ++kk) {
       const int k = r0 * 8 + kk;
       if (k >= n || !ok) break;
-      zc* row = prow + (k & 1) * NV * 64;
-      if (w == kk) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q) row[q * 64 + lane] = v[r0][q];
-      }
+      zc* row = prow + (k & 1) * 64;
+      if (w == kk) row[lane] = v[r0];
       __syncthreads();
-      zc p[NV];
-#pragma unroll
-      for (int q = 0; q < NV; ++q) p[q] = row[q * 64 + lane];
-      const double d = readlane_d(p[0].x, k);
+      zc p = row[lane];
+      const double d = readlane_d(p.x, k);
       if (!(d > 0.0)) {
         ok = false;
         break;
       }
       double inv = rcp_nr(d);
       inv = fma(inv, fma(-d, inv, 1.0), inv);
-      if (w == kk) piv[r0] = d;
+      if (lane == k) {
+        dc = d;
+        p = {0.0, 0.0};
+      }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (r < r0 || (r == r0 && w <= kk)) continue;
-        const zc f = zscale(zreadlane(v[r][0], k), -inv);
-#pragma unroll
-        for (int q = 0; q < NV; ++q) v[r][q] = zfma(f, p[q], v[r][q]);
+        const zc f = zscale(zreadlane(v[r], k), -inv);
+        v[r] = zfma(f, p, v[r]);
       }
     }
   }
@@ -538,12 +527,13 @@ __global__ void __launch_bounds__(kpt_sub_threads<R>()) k_kpt_sub(const KptDev* 
     kpt_sub_failed(kp, fail);
     return;
   }
-  constexpr int w0 = NV == 1 ? 32 : 0;
+  const double dinv = -1.0 / dc;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int i = w + 8 * r;
-    v[r][NV - 1] = zscale(v[r][NV - 1], 1.0 / sqrt(piv[r]));
-    if (w < 8 && i < n && lane >= w0 && col < n) Wl[i * LD + col] = v[r][NV - 1];
+    const double f = 1.0 / sqrt(readlane_d(dc, i & 63));
+    v[r] = lane < i ? zscale(v[r], f * dinv) : zc{lane == i ? f : 0.0, 0.0};
+    if (w < 8 && i < n && lane < n) Wl[i * LD + lane] = v[r];
   }
   __syncthreads();
   // H' = W H W^H
@@ -552,12 +542,12 @@ __global__ void __launch_bounds__(kpt_sub_threads<R>()) k_kpt_sub(const KptDev* 
   for (int r = 0; r < R; ++r) t[r] = hh[r] = {0.0, 0.0};
   if (w < 8) {
     for (int k = 0; k < n; ++k) {
-      const zc x = Hl[k * LD + col];
+      const zc x = Hl[k * LD + min(lane, N - 1)];
 #pragma unroll
-      for (int r = 0; r < R; ++r) t[r] = zfma(zreadlane(v[r][NV - 1], w0 + k), x, t[r]);
+      for (int r = 0; r < R; ++r) t[r] = zfma(zreadlane(v[r], k), x, t[r]);
     }
     for (int k = 0; k < n; ++k) {
-      const zc x = zconj(Wl[col * LD + k]);
+      const zc x = zconj(Wl[min(lane, N - 1) * LD + k]);
 #pragma unroll
       for (int r = 0; r < R; ++r) hh[r] = zfma(zreadlane(t[r], k), x, hh[r]);
     }
@@ -574,7 +564,7 @@ __global__ void __launch_bounds__(kpt_sub_threads<R>()) k_kpt_sub(const KptDev* 
   const int nblk = np * (np + 1) / 2, NH = (nblk + 63) / 64;
   JacBlock blk;
   const bool on = w * 64 + lane < nblk;
-  blk.init(min(w * 64 + lane, nblk - 1), n2);
+  blk.init<false>(min(w * 64 + lane, nblk - 1), n2);
   // sign of the stored imaginary parts: entry (u, v) at its next positions
   double sg[4];
   {

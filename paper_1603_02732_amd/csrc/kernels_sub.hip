@@ -8,9 +8,10 @@
 // Jacobi rounds per sweep, each a few hundred cycles of dependent loads and
 // FP64 operations on one compute unit.  So each step is laid out for few
 // instructions, one barrier (two above 64 bands), and no index arithmetic:
-//  - Cholesky and W = L^-1 are one elimination on [S | I] with the rows in
-//    registers (row i in wavefront i mod NW, a column a lane); a step publishes
-//    the pivot row in LDS and takes the row multipliers by scalar lane reads;
+//  - Cholesky and W = L^-1 are one elimination on [S | I], in place (a column of
+//    W takes the place of the finished column of S), with the rows in registers
+//    (row i in wavefront i mod NW, a column a lane); a step publishes the pivot
+//    row in LDS and takes the row multipliers by scalar lane reads;
 //  - the Jacobi rounds update one triangle of H', stored by position
 //    (jacobi.hpp);
 //  - M's rows (those of W^T, rotated along with H') need each round's
@@ -30,48 +31,65 @@
 
 namespace sgo {
 
-// Elimination on [S | I]: row i = w + NW r of wavefront w in v[r][0 .. NV-1],
-// column c of S in register c / 64 (lane c mod 64), of I in register NV/2 +
-// c / 64; NV = 1 packs both into one register (lanes 0 .. 31 and 32 .. 63).  S
-// is full (both triangles).  On return the I part is the unit-lower factor's
-// inverse and piv[r] the row's pivot, so W's row is its I part / sqrt(piv).
-// prow: 2 x NV x 64 doubles of LDS.  False (everywhere) at a pivot <= 0.
-template <int NV, int NR, int NW>
-__device__ __forceinline__ bool eliminate(double (&v)[NR][NV], double (&piv)[NR], int n, int w, int lane,
-                                          double* prow) {
-  constexpr int HV = NV / 2;
+// Elimination on [S | I] in place: row i = w + NW r of wavefront w in v[r], column c
+// in register c / 64, lane c mod 64.  A row below the step's k holds S in the
+// columns past k and, in column c <= k, the entry of the unit-lower factor's
+// inverse times -d_c (d_c: the pivot), which is what S left there: no step writes
+// its own column.  S is full (both triangles).  On return v is W = L^-1.  prow:
+// 2 x NQ x 64 doubles of LDS.  False (everywhere) at a pivot <= 0.
+template <int NQ, int NR, int NW>
+__device__ __forceinline__ bool eliminate_steps(double (&v)[NR][NQ], double (&dc)[NQ], int n, int w, int lane,
+                                                double* prow) {
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) dc[q] = 1.0;
 #pragma unroll
   for (int r0 = 0; r0 < NR; ++r0) {
-    constexpr int kLanes = NV == 1 ? 32 : 64;
-    const int ka = r0 * NW / kLanes;  // register of the step's column
+    const int ka = r0 * NW / 64;  // register of the step's column
     for (int kk = 0; kk < NW; ++kk) {
       const int k = r0 * NW + kk;
       if (k >= n) return true;
-      double* row = prow + (k & 1) * NV * 64;
+      double* row = prow + (k & 1) * NQ * 64;
       if (w == kk) {
 #pragma unroll
-        for (int q = 0; q < NV; ++q) row[q * 64 + lane] = v[r0][q];
+        for (int q = 0; q < NQ; ++q) row[q * 64 + lane] = v[r0][q];
       }
       __syncthreads();
-      double p[NV];
+      double p[NQ];
 #pragma unroll
-      for (int q = 0; q < NV; ++q) p[q] = row[q * 64 + lane];
-      const double d = readlane_d(p[NV == 1 ? 0 : ka], k & (kLanes - 1));
+      for (int q = 0; q < NQ; ++q) p[q] = row[q * 64 + lane];
+      const int kl = k & 63;
+      const double d = readlane_d(p[ka], kl);
       if (!(d > 0.0)) return false;
       double inv = rcp_nr(d);
       inv = fma(inv, fma(-d, inv, 1.0), inv);
-      if (w == kk) piv[r0] = d;
+      dc[ka] = lane == kl ? d : dc[ka];
+      p[ka] = lane == kl ? 0.0 : p[ka];
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
         if (r < r0 || (r == r0 && w <= kk)) continue;
-        const double f = readlane_d(v[r][NV == 1 ? 0 : ka], k & (kLanes - 1)) * inv;
+        const double f = readlane_d(v[r][ka], kl) * inv;
 #pragma unroll
-        for (int q = 0; q < NV; ++q) {
-          // finished columns of S and columns of I past the step are left out
-          if (NV == 4 && ((q < HV && q < ka) || (q >= HV && q - HV > ka))) continue;
-          v[r][q] = fma(-f, p[q], v[r][q]);
-        }
+        for (int q = 0; q < NQ; ++q) v[r][q] = fma(-f, p[q], v[r][q]);
       }
+    }
+  }
+  return true;
+}
+template <int NQ, int NR, int NW>
+__device__ __forceinline__ bool eliminate(double (&v)[NR][NQ], int n, int w, int lane, double* prow) {
+  double dc[NQ];  // pivots of this lane's columns
+  if (!eliminate_steps<NQ, NR, NW>(v, dc, n, w, lane, prow)) return false;
+  double dinv[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) dinv[q] = -1.0 / dc[q];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int i = w + NW * r;
+    const double f = 1.0 / sqrt(readlane_d(dc[r * NW / 64], i & 63));
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int c = q * 64 + lane;
+      v[r][q] = c < i ? v[r][q] * dinv[q] * f : (c == i ? f : 0.0);
     }
   }
   return true;
@@ -84,13 +102,14 @@ __device__ __forceinline__ void sub_failed(const CandDesc& cd) {
 }
 
 // Sorted eps and the ranks (ascending, ties by index) from H's diagonal.
+template <bool QUAD>
 __device__ __forceinline__ void jac_ranks(const CandDesc& cd, const double* T, int* rank) {
-  const int n = cd.nb;
+  const int n = cd.nb, n2 = n + (n & 1);
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const double li = T[jac_tri(i, i)];
+    const double li = T[jac_addr<QUAD>(i, i, n2)];
     int rnk = 0;
     for (int j = 0; j < n; ++j) {
-      const double lj = T[jac_tri(j, j)];
+      const double lj = T[jac_addr<QUAD>(j, j, n2)];
       if (lj < li || (lj == li && j < i)) ++rnk;
     }
     rank[i] = rnk;
@@ -108,14 +127,14 @@ template <int R>
 constexpr int sub_small_threads() { return R == 4 ? 512 : 576; }  // 9 wavefronts hold 64 bands' blocks
 template <int R>
 constexpr size_t sub_small_lds() {
-  return sizeof(double) * (2 * (size_t)(8 * R) * (8 * R + 1) + 2 * (R == 4 ? 64 : 128) + 64);
+  return sizeof(double) * (2 * (size_t)(8 * R) * (8 * R + 1) + 2 * 64 + 64);
 }
 template <int R>
 __global__ void __launch_bounds__(sub_small_threads<R>()) k_sub_small(const CandDesc* __restrict__ cds, int mode,
                                                                       int max_sweeps) {
   const CandDesc& cd = cds[blockIdx.x];
   if (!cd.active) return;
-  constexpr int N = 8 * R, LD = N + 1, TRI = N * (N + 1) / 2, NV = R == 4 ? 1 : 2;
+  constexpr int N = 8 * R, LD = N + 1, TRI = N * (N + 1) / 2;
   constexpr bool inl = R == 4;  // M's rows rotated here
   const int n = cd.nb, n2 = n + (n & 1), np = n2 / 2, m = n2 - 1;
   const int tid = threadIdx.x, lane = tid & 63, W = blockDim.x >> 6;
@@ -124,7 +143,7 @@ __global__ void __launch_bounds__(sub_small_threads<R>()) k_sub_small(const Cand
   double* Hl = (double*)smem;      // H, then the two triangles of H'
   double* Wl = Hl + N * LD;        // W = L^-1
   double* prow = Wl + N * LD;      // pivot rows
-  double2* cs = (double2*)(prow + 2 * NV * 64);  // rotations of two rounds (R = 4)
+  double2* cs = (double2*)(prow + 2 * 64);  // rotations of two rounds (R = 4)
   __shared__ double sh[16 * 2];
   __shared__ int rank_l[N];
   long long* clk = cd.dbg_clk;
@@ -132,33 +151,22 @@ __global__ void __launch_bounds__(sub_small_threads<R>()) k_sub_small(const Cand
   if (mode == 3)
     for (int u = w; u < n; u += W)
       if (lane < n) Hl[u * LD + lane] = 0.5 * (cd.Hs[u * n + lane] + cd.Hs[lane * n + u]);
-  // rows of [S | I] (S from its lower triangle)
-  double v[R][NV], piv[R];
-  const int col = inl ? lane & 31 : lane;
+  // rows of S (from its lower triangle), then of W
+  double v[R][1];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int i = w + 8 * r;
-    const bool in = w < 8 && i < n && col < n;
-    const double s = in ? cd.S[max(i, col) * n + min(i, col)] : 0.0;
-    const double one = in && i == col ? 1.0 : 0.0;
-    if (inl) {
-      v[r][0] = lane < 32 ? s : one;
-    } else {
-      v[r][0] = s;
-      v[r][NV - 1] = one;
-    }
-    piv[r] = 1.0;
+    const bool in = w < 8 && i < n && lane < n;
+    v[r][0] = in ? cd.S[max(i, lane) * n + min(i, lane)] : 0.0;
   }
-  if (!eliminate<NV, R, 8>(v, piv, n, w, lane, prow)) {
+  if (!eliminate<1, R, 8>(v, n, w, lane, prow)) {
     sub_failed(cd);
     return;
   }
-  constexpr int w0 = inl ? 32 : 0;  // lane of W's column 0
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int i = w + 8 * r;
-    v[r][NV - 1] *= 1.0 / sqrt(piv[r]);
-    if (w < 8 && i < n && lane >= w0 && col < n) Wl[i * LD + col] = v[r][NV - 1];
+    if (w < 8 && i < n && lane < n) Wl[i * LD + lane] = v[r][0];
   }
   __syncthreads();
   if (clk && tid == 0) clk[1] = clock64();
@@ -173,12 +181,12 @@ __global__ void __launch_bounds__(sub_small_threads<R>()) k_sub_small(const Cand
   for (int r = 0; r < R; ++r) t[r] = h[r] = 0.0;
   if (w < 8) {
     for (int k = 0; k < n; ++k) {
-      const double hk = Hl[k * LD + col];
+      const double hk = Hl[k * LD + min(lane, N - 1)];
 #pragma unroll
-      for (int r = 0; r < R; ++r) t[r] = fma(readlane_d(v[r][NV - 1], w0 + k), hk, t[r]);
+      for (int r = 0; r < R; ++r) t[r] = fma(readlane_d(v[r][0], k), hk, t[r]);
     }
     for (int k = 0; k < n; ++k) {
-      const double wk = Wl[col * LD + k];
+      const double wk = Wl[min(lane, N - 1) * LD + k];
 #pragma unroll
       for (int r = 0; r < R; ++r) h[r] = fma(readlane_d(t[r], k), wk, h[r]);
     }
@@ -188,18 +196,18 @@ __global__ void __launch_bounds__(sub_small_threads<R>()) k_sub_small(const Cand
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int i = w + 8 * r;
-    if (w < 8 && i < n && lane <= i) T[i * (i + 1) / 2 + lane] = h[r];
+    if (w < 8 && i < n && lane <= i) T[jac_addr<false>(i, lane, n2)] = h[r];
   }
-  if (n2 > n && w == 0 && lane <= n) T[n * (n + 1) / 2 + lane] = 0.0;
+  if (n2 > n && w == 0 && lane <= n) T[jac_addr<false>(n, lane, n2)] = 0.0;
   __syncthreads();
   if (clk && tid == 0) clk[2] = clock64();
   const int nblk = np * (np + 1) / 2, NH = (nblk + 63) / 64;
   // this lane's block
   JacBlock blk;
   const bool on = w * 64 + lane < nblk;
-  blk.init(min(w * 64 + lane, nblk - 1), n2);
+  blk.init<false>(min(w * 64 + lane, nblk - 1), n2);
   const int k = min(lane, np - 1);
-  const int ia = jac_tri(k, k), ib = jac_tri(n2 - 1 - k, n2 - 1 - k), ic = jac_tri(n2 - 1 - k, k);
+  const int ia = jac_addr<false>(k, k, n2), ib = jac_addr<false>(n2 - 1 - k, n2 - 1 - k, n2), ic = jac_addr<false>(n2 - 1 - k, k, n2);
   const int pP = 4 * blk.P, pQ = 4 * blk.Q;
   const bool diag = blk.P == blk.Q;
   // this lane's entries of M's rows: row j starts as row j of W^T
@@ -223,7 +231,7 @@ __global__ void __launch_bounds__(sub_small_threads<R>()) k_sub_small(const Cand
   bool pending = false;
   const int limit = n > 1 ? max_sweeps : 0;
   for (int sweep = 0; sweep < limit; ++sweep) {
-    if (jac_converged(T + par * TRI, n2, sh)) break;
+    if (jac_converged<false>(T + par * TRI, n2, sh)) break;
     ++nsweep;
     for (int r = 0; r < m; ++r) {
       if (w < NH) {
@@ -265,7 +273,7 @@ __global__ void __launch_bounds__(sub_small_threads<R>()) k_sub_small(const Cand
     clk[5] = nsweep;
   }
   int* rank = inl ? rank_l : (int*)(cd.red_part + kJacRanks);
-  jac_ranks(cd, T + par * TRI, rank);
+  jac_ranks<false>(cd, T + par * TRI, rank);
   if (inl) {
     __syncthreads();
     const int wv = w - NH, Wv = W - NH, ibot = n2 - 1 - kv;
@@ -285,43 +293,41 @@ __global__ void __launch_bounds__(sub_small_threads<R>()) k_sub_small(const Cand
   if (clk && tid == 0) clk[4] = clock64();
 }
 
-// Cholesky and W = L^-1 (into C) of 65 to 128 bands: the same elimination, 16
-// wavefronts, two columns a lane.
-constexpr int kSubCholMax = 128;
+// Cholesky and W = L^-1 (into C) above 64 bands: the same elimination, 16
+// wavefronts, NR rows and NQ columns a lane (<2, 8>: 128, <3, 12>: 192, <4, 13>:
+// 208).  112 bands 56 us; 164 bands 119 us, 435 us by blocks of rows in global
+// memory.
+template <int NQ, int NR>
 __global__ void __launch_bounds__(1024) k_sub_chol(const CandDesc* __restrict__ cds) {
   const CandDesc& cd = cds[blockIdx.x];
   if (!cd.active) return;
-  constexpr int NR = 8, NW = 16;
+  constexpr int NW = 16;
   const int n = cd.nb, lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  __shared__ double prow[2 * 4 * 64];
+  __shared__ double prow[2 * NQ * 64];
   long long* clk = cd.dbg_clk;
   if (clk && threadIdx.x == 0) clk[0] = clock64();
-  double v[NR][4], piv[NR];
+  double v[NR][NQ];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     const int i = w + NW * r;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+    for (int q = 0; q < NQ; ++q) {
       const int c = q * 64 + lane;
-      const bool in = i < n && c < n;
-      v[r][q] = in ? cd.S[(size_t)max(i, c) * n + min(i, c)] : 0.0;
-      v[r][2 + q] = in && i == c ? 1.0 : 0.0;
+      v[r][q] = i < n && c < n ? cd.S[(size_t)max(i, c) * n + min(i, c)] : 0.0;
     }
-    piv[r] = 1.0;
   }
-  if (!eliminate<4, NR, NW>(v, piv, n, w, lane, prow)) {
+  if (!eliminate<NQ, NR, NW>(v, n, w, lane, prow)) {
     sub_failed(cd);
     return;
   }
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     const int i = w + NW * r;
-    const double f = 1.0 / sqrt(piv[r]);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+    for (int q = 0; q < NQ; ++q) {
       const int c = q * 64 + lane;
-      if (i < n && c < n) cd.C[(size_t)i * n + c] = v[r][2 + q] * f;
+      if (i < n && c < n) cd.C[(size_t)i * n + c] = v[r][q];
     }
   }
   if (clk && threadIdx.x == 0) clk[1] = clock64();
@@ -353,14 +359,14 @@ __global__ void __launch_bounds__(1024) k_sub_jacobi(const CandDesc* __restrict_
   double* T = (double*)(cs + np);    // [nt], then a slot for the idle lanes' writes
   __shared__ double sh[16 * 2];
   for (int u = tid >> 6; u < n2; u += nthr >> 6)
-    for (int v = lane; v <= u; v += 64) T[u * (u + 1) / 2 + v] = u < n ? cd.Hs[(size_t)u * n + v] : 0.0;
+    for (int v = lane; v <= u; v += 64) T[jac_addr<true>(u, v, n2)] = u < n ? cd.Hs[(size_t)u * n + v] : 0.0;
   if (cd.dbg_clk && tid == 0) cd.dbg_clk[2] = clock64();
   int rd[ITEMS][4], wr[ITEMS][4], P[ITEMS], Q[ITEMS];
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
     const int t = tid + i * nthr;
     JacBlock b;
-    b.init(min(t, nblk - 1), n2);
+    b.init<true>(min(t, nblk - 1), n2);
     P[i] = b.P;
     Q[i] = b.Q;
 #pragma unroll
@@ -370,13 +376,13 @@ __global__ void __launch_bounds__(1024) k_sub_jacobi(const CandDesc* __restrict_
     }
   }
   const int k = min(tid, np - 1);
-  const int ia = jac_tri(k, k), ib = jac_tri(n2 - 1 - k, n2 - 1 - k), ic = jac_tri(n2 - 1 - k, k);
+  const int ia = jac_addr<true>(k, k, n2), ib = jac_addr<true>(n2 - 1 - k, n2 - 1 - k, n2), ic = jac_addr<true>(n2 - 1 - k, k, n2);
   double2* log = (double2*)(cd.red_part + kJacLog);
   __syncthreads();
   int nsweep = 0;
   const int limit = n > 1 ? max_sweeps : 0;
   for (int sweep = 0; sweep < limit; ++sweep) {
-    if (jac_converged(T, n2, sh)) break;
+    if (jac_converged<true>(T, n2, sh)) break;
     ++nsweep;
     for (int r = 0; r < m; ++r) {
       if ((tid & ~63) < np) {  // uniform per wavefront
@@ -404,7 +410,7 @@ __global__ void __launch_bounds__(1024) k_sub_jacobi(const CandDesc* __restrict_
       __syncthreads();
     }
   }
-  jac_ranks(cd, T, (int*)(cd.red_part + kJacRanks));
+  jac_ranks<true>(cd, T, (int*)(cd.red_part + kJacRanks));
   if (tid == 0) {
     cd.red_part[kJacSweeps] = nsweep;
     if (cd.dbg_clk) {
@@ -504,8 +510,7 @@ static void launch_rounds(hipStream_t st, const CandDesc* desc, int ncand, int n
 
 // No host sync and no allocation: this serves graph capture and the
 // allocation-free entry point too.
-void launch_sub_block(hipStream_t st, const CandDesc* desc, int ncand, int n, int mode, int max_sweeps,
-                      int nthr) {
+void launch_sub_block(hipStream_t st, const CandDesc* desc, int ncand, int n, int mode, int max_sweeps) {
   if (n <= 32) {
     hipLaunchKernelGGL(k_sub_small<4>, dim3(ncand), dim3(sub_small_threads<4>()), sub_small_lds<4>(), st, desc,
                        mode, max_sweeps);
@@ -519,17 +524,14 @@ void launch_sub_block(hipStream_t st, const CandDesc* desc, int ncand, int n, in
     if (mode == 3) launch_vapply(st, desc, ncand, n);
     return;
   }
-  if (n <= kSubCholMax) {
-    hipLaunchKernelGGL(k_sub_chol, dim3(ncand), dim3(1024), 0, st, desc);
-    check_launch("k_sub_chol");
-    if (mode == 1) {
-      hipLaunchKernelGGL(k_sub_wt, dim3((n * n + kNT - 1) / kNT, ncand), dim3(kNT), 0, st, desc);
-      check_launch("k_sub_wt");
-      return;
-    }
-  } else {
-    launch_sub_chol_blocked(st, desc, ncand, n, mode, nthr);
-    if (mode == 1) return;
+  if (n <= 128) hipLaunchKernelGGL((k_sub_chol<2, 8>), dim3(ncand), dim3(1024), 0, st, desc);
+  else if (n <= 192) hipLaunchKernelGGL((k_sub_chol<3, 12>), dim3(ncand), dim3(1024), 0, st, desc);
+  else hipLaunchKernelGGL((k_sub_chol<4, 13>), dim3(ncand), dim3(1024), 0, st, desc);
+  check_launch("k_sub_chol");
+  if (mode == 1) {
+    hipLaunchKernelGGL(k_sub_wt, dim3((n * n + kNT - 1) / kNT, ncand), dim3(kNT), 0, st, desc);
+    check_launch("k_sub_wt");
+    return;
   }
   launch_sub_congruence(st, desc, ncand, n);
   const int np = (n + 1) / 2, nblk = np * (np + 1) / 2;
