@@ -588,11 +588,17 @@ __global__ void __launch_bounds__(kNT) k_gram_reduce(const CandDesc* __restrict_
 // Band-space product on 64-column slices:
 //   Y[i][k] = alpha Y[i][k] + beta sum_j w_j M[j][i] A[j][k]   (i < nout, j < nin)
 // w_j = h_j (projector energies) when use_h, else 1.  Each block owns all
-// rows of its 64 columns, so Y may alias A (in-place rotation): the block
-// reads every A row of its slice (through LDS, 32 rows at a time) before it
-// writes.  Wave w holds the output rows 16 (w + 4 m) .. +16, m < IBW.
+// rows of its 64 columns, so Y may alias A (in-place rotation, alpha = 0): the
+// block reads every A row of its slice (through LDS, 32 rows at a time) before it
+// writes.  Wavefront w holds columns 16 w .. +16 of every 16-row output tile.
+//
+// A cell's bands (20 x 600 to 1,200 values) make some ten blocks, so the kernel is
+// the latency of one: the slice, M and, up to two tiles, Y are loaded from
+// clamped addresses all at once (behind a bounds test each they went one after
+// another), and the tiles' MFMAs go to all four wavefronts whatever their
+// number.  20 x 1,168 values 5.6 us (11.0 before), 4 x 24 x 12,100 13.6 us (19.2).
 constexpr int kJC = 32;
-template <typename T, int IBW>
+template <typename T, int NIB>
 __global__ void __launch_bounds__(kNT) k_gemm_acc(const CandDesc* __restrict__ cds, int y0, int y1,
                                                   int y2, int a0, int a1, int a2, int mat,
                                                   double alpha, double beta, int use_h) {
@@ -609,6 +615,7 @@ __global__ void __launch_bounds__(kNT) k_gemm_acc(const CandDesc* __restrict__ c
   const T* A = warr<T>(cd, wa);
   T* Y = warr<T>(cd, wy);
   const double* M = marr(cd, mat);
+  const double* hp = cd.hproj;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, g = lane >> 4;
   const int nib = (nout + 15) / 16;
@@ -616,64 +623,70 @@ __global__ void __launch_bounds__(kNT) k_gemm_acc(const CandDesc* __restrict__ c
   double* As = (double*)smem;            // [kJC][64]
   double* Ms = As + kJC * 64;            // [kJC][nib*16]
   const int ldm = nib * 16;
-  dbl4 acc[IBW][4];
+  const float ildm = 1.0f / ldm;
+  const int k = kbase + wave * 16 + r16;  // this lane's column
+  constexpr bool ahead = NIB <= 2;
+  T yo[ahead ? NIB : 1][4];
+  if (ahead && alpha != 0.0) {
 #pragma unroll
-  for (int m = 0; m < IBW; ++m)
+    for (int m = 0; m < NIB; ++m)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[m][v] = dbl4{0.0, 0.0, 0.0, 0.0};
+      for (int r = 0; r < 4; ++r) yo[m][r] = Y[(size_t)min(m * 16 + 4 * r + g, nout - 1) * Kp + min(k, Kp - 1)];
+  }
+  dbl4 acc[NIB];
+#pragma unroll
+  for (int m = 0; m < NIB; ++m) acc[m] = dbl4{0.0, 0.0, 0.0, 0.0};
   for (int j0 = 0; j0 < nin; j0 += kJC) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < kJC * 64; e += blockDim.x) {
-      const int jj = e >> 6, kk = e & 63;
-      const int j = j0 + jj, k = kbase + kk;
-      As[e] = (j < nin && k < Kp) ? (double)A[(size_t)j * Kp + k] : 0.0;
-    }
-    for (int e = threadIdx.x; e < kJC * ldm; e += blockDim.x) {
-      const int jj = e / ldm, i = e - jj * ldm;
-      const int j = j0 + jj;
-      double m = 0.0;
-      if (j < nin && i < nout) {
-        m = M[(size_t)j * nout + i];
-        if (use_h) m *= cd.hproj[j];
+    T av[kJC / 4];
+#pragma unroll
+    for (int q = 0; q < kJC / 4; ++q)
+      av[q] = A[(size_t)min(j0 + wave + 4 * q, nin - 1) * Kp + min(kbase + lane, Kp - 1)];
+    // M's rows, four of this thread's elements at a time
+    bool staged = false;
+    for (int e0 = threadIdx.x; e0 < kJC * ldm || !staged; e0 += 4 * kNT) {
+      double mv[4], hv[4];
+      int jj[4], i[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int e = e0 + q * kNT;
+        jj[q] = line_div(e, ildm);
+        i[q] = e - jj[q] * ldm;
+        const int j = min(j0 + jj[q], nin - 1);
+        mv[q] = M[(size_t)j * nout + min(i[q], nout - 1)];
+        hv[q] = use_h ? hp[j] : 1.0;
       }
-      Ms[e] = m;
+      if (!staged) {
+        __syncthreads();  // the tile before is read
+#pragma unroll
+        for (int q = 0; q < kJC / 4; ++q)
+          As[(wave + 4 * q) * 64 + lane] =
+              j0 + wave + 4 * q < nin && kbase + lane < Kp ? (double)av[q] : 0.0;
+        staged = true;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (jj[q] < kJC) Ms[e0 + q * kNT] = j0 + jj[q] < nin && i[q] < nout ? mv[q] * hv[q] : 0.0;
     }
     __syncthreads();
 #pragma unroll
     for (int j4 = 0; j4 < kJC / 4; ++j4) {
       const int jr = 4 * j4 + g;
-      double bop[4];
+      const double bop = As[jr * 64 + wave * 16 + r16];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) bop[v] = As[jr * 64 + v * 16 + r16];
-#pragma unroll
-      for (int m = 0; m < IBW; ++m) {
-        const int ib = wave + 4 * m;
-        if (ib < nib) {
-          const double aop = Ms[jr * ldm + ib * 16 + r16];
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            acc[m][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(aop, bop[v], acc[m][v], 0, 0, 0);
-        }
-      }
+      for (int m = 0; m < NIB; ++m)
+        if (m < nib) acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(Ms[jr * ldm + m * 16 + r16], bop, acc[m], 0, 0, 0);
     }
   }
-  __syncthreads();  // every read of A in this slice precedes the writes
+  if (k >= cd.K) return;  // every read of A in this slice is done
 #pragma unroll
-  for (int m = 0; m < IBW; ++m) {
-    const int ib = wave + 4 * m;
-    if (ib >= nib) continue;
+  for (int m = 0; m < NIB; ++m) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int k = kbase + v * 16 + r16;
-      if (k >= cd.K) continue;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = ib * 16 + 4 * r + g;
-        if (i >= nout) continue;
-        const size_t idx = (size_t)i * Kp + k;
-        const double yo = alpha != 0.0 ? (double)Y[idx] : 0.0;
-        Y[idx] = (T)(alpha * yo + beta * acc[m][v][r]);
-      }
+    for (int r = 0; r < 4; ++r) {
+      const int i = m * 16 + 4 * r + g;
+      if (i >= nout) continue;
+      const size_t idx = (size_t)i * Kp + k;
+      const double y = alpha == 0.0 ? 0.0 : (ahead ? (double)yo[ahead ? m : 0][r] : (double)Y[idx]);
+      Y[idx] = (T)(alpha * y + beta * acc[m][r]);
     }
   }
 }
@@ -1547,14 +1560,20 @@ void launch_gemm_acc(const LaunchCtx& L, int narr, const int* y, const int* a, i
     return;
   }
   prof_before("k_gemm_acc", L.stream);
-  if (nib <= 4)
+  if (nib <= 1)
     hipLaunchKernelGGL((k_gemm_acc<T, 1>), grid, dim3(kNT), lds, L.stream, L.desc, y[0], y1, y2,
                        a[0], a1, a2, mat, alpha, beta, use_h);
-  else if (nib <= 8)
+  else if (nib <= 2)
     hipLaunchKernelGGL((k_gemm_acc<T, 2>), grid, dim3(kNT), lds, L.stream, L.desc, y[0], y1, y2,
                        a[0], a1, a2, mat, alpha, beta, use_h);
+  else if (nib <= 4)
+    hipLaunchKernelGGL((k_gemm_acc<T, 4>), grid, dim3(kNT), lds, L.stream, L.desc, y[0], y1, y2,
+                       a[0], a1, a2, mat, alpha, beta, use_h);
+  else if (nib <= 8)
+    hipLaunchKernelGGL((k_gemm_acc<T, 8>), grid, dim3(kNT), lds, L.stream, L.desc, y[0], y1, y2,
+                       a[0], a1, a2, mat, alpha, beta, use_h);
   else if (nib <= 20)
-    hipLaunchKernelGGL((k_gemm_acc<T, 5>), grid, dim3(kNT), lds, L.stream, L.desc, y[0], y1, y2,
+    hipLaunchKernelGGL((k_gemm_acc<T, 20>), grid, dim3(kNT), lds, L.stream, L.desc, y[0], y1, y2,
                        a[0], a1, a2, mat, alpha, beta, use_h);
   else
     throw_unsupported("more than 320 bands in the rotation kernel");
@@ -1680,7 +1699,9 @@ static void configure_t() {
   allow_lds((const void*)k_plane_density<T, kDensRegs>);
   allow_lds((const void*)k_gemm_acc<T, 1>);
   allow_lds((const void*)k_gemm_acc<T, 2>);
-  allow_lds((const void*)k_gemm_acc<T, 5>);
+  allow_lds((const void*)k_gemm_acc<T, 4>);
+  allow_lds((const void*)k_gemm_acc<T, 8>);
+  allow_lds((const void*)k_gemm_acc<T, 20>);
 }
 void configure_wave() {
   allow_lds((const void*)k_gemm_f32<2, 1>);
