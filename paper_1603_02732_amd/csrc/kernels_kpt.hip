@@ -941,7 +941,7 @@ __global__ void k_kpt_init(const KptDev* __restrict__ kd, unsigned seed) {
 // doubly occupied); writes occ[k][n] and the band energy, entropy and mu
 // into the structure's status block (slots as at Gamma).  One workgroup; the
 // bracket of mu is narrowed by one point per wavefront and round, as at Gamma
-// (2 x 20 levels: 30 us; 1,665 us with one thread's bisection).
+// (2 x 20 levels: 23 us; 1,665 us with one thread's bisection).
 constexpr int kKptOccWaves = 16;
 __global__ void __launch_bounds__(64 * kKptOccWaves) k_kpt_occupations(const double* __restrict__ eps,
                                                                        const double* __restrict__ wk, int nk,
@@ -987,17 +987,18 @@ __global__ void __launch_bounds__(64 * kKptOccWaves) k_kpt_occupations(const dou
     lo -= 40.0 * sigma;
     hi += 40.0 * sigma;
     __shared__ int over[2][kKptOccWaves];
+    const double e0 = lane < n ? eps[lane] : 0.0, w0 = lane < n ? 2.0 * wk[lane / nb] : 0.0;
     for (int it = 0; it < 80; ++it) {
       const double mid = 0.5 * (lo + hi);
       if (mid <= lo || mid >= hi) break;
       const double at = fmin(fmax(lo + (hi - lo) * ((w + 1) / (kKptOccWaves + 1.0)), lo), hi);
-      double s = 0.0;
-      for (int e = lane; e < n; e += 64) s += wk[e / nb] * 2.0 / (1.0 + exp((eps[e] - at) / sigma));
+      double s = lane < n ? w0 / (1.0 + exp((e0 - at) / sigma)) : 0.0;
+      for (int e = lane + 64; e < n; e += 64) s += wk[e / nb] * 2.0 / (1.0 + exp((eps[e] - at) / sigma));
       s = wave_sum(s);
       if (lane == 0) over[it & 1][w] = s > nelec;
       __syncthreads();
-      int k = 0;
-      while (k < kKptOccWaves && !over[it & 1][k]) ++k;
+      const unsigned long long many = __ballot(lane < kKptOccWaves && over[it & 1][lane & (kKptOccWaves - 1)]);
+      const int k = many ? __ffsll((long long)many) - 1 : kKptOccWaves;
       const double a = lo, d = hi - lo;
       if (k > 0) lo = fmin(fmax(a + d * (k / (kKptOccWaves + 1.0)), a), hi);
       if (k < kKptOccWaves) hi = fmin(fmax(a + d * ((k + 1) / (kKptOccWaves + 1.0)), a), hi);
