@@ -321,7 +321,7 @@ int sgo_subspace_solve_noalloc(int device, int n, int mode, const double* S, con
  * "SGO_RR_SWEEPS" (Jacobi sweeps of the intermediate subspace steps),
  * "SGO_PLANE_KERNEL" (FP32 plane transforms: 1 = register-resident line
  * FFTs, the default where every line length is 2^a 3^b 5^c <= 64;
- * 2 = LDS Stockham passes, used for FP64 and longer lines),
+ * 2 = staged line transforms in LDS, used for FP64 and longer lines),
  * "SGO_GEMM_KERNEL" (FP32 band products X M: 1 = FP32 MFMA with FP32
  * accumulation, the default; 2 = FP64 MFMA on the FP32 data),
  * "SGO_GEMM_WAVES" (wavefronts that share one staged 64-column slice of the

@@ -1,5 +1,5 @@
-// Device helpers: wavefront/block/grid reductions and the LDS-resident
-// mixed-radix Stockham FFT used by every transform of the engine.
+// Device helpers: wavefront/block/grid reductions, packed coefficients and the
+// local-density functional.
 #pragma once
 #include "common.hpp"
 

@@ -19,9 +19,9 @@
 //    registers, a round behind; above that they are logged and applied over
 //    the whole GPU afterwards (k_sub_vapply).  V and W^T V are never formed.
 // Converged solves, against the same rounds on the square matrix with V in the
-// loop and a Cholesky of two barriers a column: 32 bands 206 -> 104 us (a round
-// 2,500 -> 1,250 cycles, the elimination 70k -> 22k cycles), 64 bands 918 -> 371
-// us, 112 bands 3.27 -> 0.78 ms, 164 bands 4.58 -> 2.26 ms (a launch per round
+// loop and a Cholesky of two barriers a column: 32 bands 206 -> 103 us (a round
+// 2,500 -> 1,250 cycles, the elimination 70k -> 22k cycles), 64 bands 918 -> 370
+// us, 112 bands 3.27 -> 0.74 ms, 164 bands 4.58 -> 1.67 ms (a launch per round
 // before); |M^T S M - 1| at 164 bands 4.8e-14 -> 5.7e-15.
 #include "jacobi.hpp"
 #include "launch.hpp"
