@@ -950,11 +950,11 @@ class Engine {
       // after the last step only the bands are read again (H X and D start anew
       // with the next potential), except by the gated diagonalisation below
       const bool last = k + 1 == ncg;
-      subspace_rotate<T>(L, last && !(cg_tol > 0.0) ? 1 : 3, last ? 40 : inter);
+      subspace_rotate<T>(L, last && !(cg_tol > 0.0) ? 1 : 3, last ? kJacMaxSweeps : inter);
     }
     if (cg_tol > 0.0) {
       launch_cg_release(L, 0);
-      subspace_rotate<T>(L, 2, 40);
+      subspace_rotate<T>(L, 2, kJacMaxSweeps);
       launch_cg_release(L, 1);
     }
   }

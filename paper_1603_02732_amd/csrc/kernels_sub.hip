@@ -511,6 +511,7 @@ static void launch_rounds(hipStream_t st, const CandDesc* desc, int ncand, int n
 // No host sync and no allocation: this serves graph capture and the
 // allocation-free entry point too.
 void launch_sub_block(hipStream_t st, const CandDesc* desc, int ncand, int n, int mode, int max_sweeps) {
+  max_sweeps = std::min(max_sweeps, kJacMaxSweeps);  // the log holds no more
   if (n <= 32) {
     hipLaunchKernelGGL(k_sub_small<4>, dim3(ncand), dim3(sub_small_threads<4>()), sub_small_lds<4>(), st, desc,
                        mode, max_sweeps);
