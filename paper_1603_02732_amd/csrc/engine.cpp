@@ -1313,11 +1313,10 @@ class Engine {
     for (int a = 0; a < 3; ++a) K.N[a] = c.N[a];
     K.plans = c.plan;
     K.lds_class = kpt_lds_class(c.N, (size_t)g_lds_limit);
-    // grids of as many k-points at a time as 4 GB hold (at least one); partial
-    // densities of enough blocks to fill the chip
     const size_t grids = (size_t)nb * c.ntot * zc;
-    K.kchunk = (int)std::max<size_t>(1, std::min<size_t>(nk, (size_t)4e9 / grids));
+    // partial densities of enough blocks to fill the chip, or grids
     K.nchunk = std::max(1, std::min(nb, 512 / nk));
+    K.kchunk = K.lds_class ? std::min(nk, 512) : kpt_grid_chunk(nk, grids);
     // the arena: what the host fills first (copied in one piece), then the rest
     std::vector<KptDev> dev(nk);
     std::vector<char> up;
@@ -1364,22 +1363,33 @@ class Engine {
         k.HD = (cplx<double>*)take(nb * n * zc);
         k.S = (cplx<double>*)take(nbb * zc);
         k.H = (cplx<double>*)take(nbb * zc);
-        k.W = (cplx<double>*)take(nbb * zc);
-        k.V = (cplx<double>*)take(nbb * zc);
+        k.W = (cplx<double>*)take(nb > kKptLdsBands ? nbb * zc : 0);
+        k.V = (cplx<double>*)take(nb > kKptLdsBands ? nbb * zc : 0);
         k.M = (cplx<double>*)take(nbb * zc);
         k.C = (cplx<double>*)take(nbb * zc);
         k.P = (cplx<double>*)take(pw * zc);
         k.dP = (cplx<double>*)take(3 * pw * zc);
       }
-      if (K.lds_class) K.dpart = (double*)take((size_t)nk * K.nchunk * c.ntot * 8);
+      if (K.lds_class) K.dpart = (double*)take((size_t)K.kchunk * K.nchunk * c.ntot * 8);
       else K.z = (cplx<double>*)take(K.kchunk * grids);
     };
-    layout();
-    if (kmem_bytes_ < at) {
-      k_free();
-      HIPCHK(hipMalloc(&kmem_, at));
-      kmem_bytes_ = at;
-    }
+    hipError_t rc = hipSuccess;
+    K.kchunk = largest_chunk(
+        K.kchunk,
+        [&](int chunk) {
+          K.kchunk = chunk;
+          layout();
+          return at;
+        },
+        [&](size_t bytes) {
+          if (kmem_bytes_ >= bytes) return true;
+          k_free();
+          rc = hipMalloc(&kmem_, bytes);
+          if (rc == hipSuccess) kmem_bytes_ = bytes;
+          else kmem_ = nullptr, (void)hipGetLastError();
+          return rc == hipSuccess;
+        });
+    if (K.kchunk == 0) HIPCHK(rc);
     base = kmem_;
     layout();
     up.assign(nup, 0);  // the failure flag starts at 0

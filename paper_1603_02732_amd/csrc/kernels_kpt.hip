@@ -248,9 +248,10 @@ __global__ void __launch_bounds__(256) k_kpt_dens_lds(const KptDev* __restrict__
     __syncthreads();
   }
 }
-__global__ void k_kpt_dens_sum(const double* __restrict__ part, int n, long ntot, double* __restrict__ dens) {
+__global__ void k_kpt_dens_sum(const double* __restrict__ part, int n, long ntot, double* __restrict__ dens,
+                               int first) {
   for (long r = (long)blockIdx.x * blockDim.x + threadIdx.x; r < ntot; r += (long)gridDim.x * blockDim.x) {
-    double s = 0.0;
+    double s = first ? 0.0 : dens[r];
     for (int c = 0; c < n; ++c) s += part[(size_t)c * ntot + r];
     dens[r] = s;
   }
@@ -1223,7 +1224,7 @@ void kpt_subspace(const KptSet& K, int* fail) {
   if (K.nb <= 32)
     hipLaunchKernelGGL(k_kpt_sub<4>, dim3(K.nk), dim3(kpt_sub_threads<4>()), kpt_sub_lds<4>(), K.stream, K.dev, 60,
                        fail);
-  else if (K.nb <= 64)
+  else if (K.nb <= kKptLdsBands)
     hipLaunchKernelGGL(k_kpt_sub<8>, dim3(K.nk), dim3(kpt_sub_threads<8>()), kpt_sub_lds<8>(), K.stream, K.dev, 60,
                        fail);
   else
@@ -1265,18 +1266,22 @@ void kpt_kinetic(const KptSet& K, const double* bandw_k, const double* occ_k, co
 void kpt_density(const KptSet& K, double* dens) {
   if (K.lds_class) {
     const KGrid G{K.N[0], K.N[1], K.N[2]};
-    const dim3 grid(K.nchunk, K.nk);
     const size_t lds = kpt_grid_lds(K.N);
-    if (K.lds_class == 16)
-      hipLaunchKernelGGL(k_kpt_dens_lds<16>, grid, dim3(256), lds, K.stream, K.dev, G, K.nchunk, K.dpart);
-    else if (K.lds_class == 20)
-      hipLaunchKernelGGL(k_kpt_dens_lds<20>, grid, dim3(256), lds, K.stream, K.dev, G, K.nchunk, K.dpart);
-    else
-      hipLaunchKernelGGL(k_kpt_dens_lds<32>, grid, dim3(256), lds, K.stream, K.dev, G, K.nchunk, K.dpart);
-    check_launch("k_kpt_dens_lds");
-    hipLaunchKernelGGL(k_kpt_dens_sum, dim3(nblocks(K.ntot)), dim3(256), 0, K.stream, K.dpart, K.nk * K.nchunk,
-                       K.ntot, dens);
-    check_launch("k_kpt_dens_sum");
+    for (int k0 = 0; k0 < K.nk; k0 += K.kchunk) {
+      const int kc = std::min(K.kchunk, K.nk - k0);
+      const dim3 grid(K.nchunk, kc);
+      const KptDev* kd = K.dev + k0;
+      if (K.lds_class == 16)
+        hipLaunchKernelGGL(k_kpt_dens_lds<16>, grid, dim3(256), lds, K.stream, kd, G, K.nchunk, K.dpart);
+      else if (K.lds_class == 20)
+        hipLaunchKernelGGL(k_kpt_dens_lds<20>, grid, dim3(256), lds, K.stream, kd, G, K.nchunk, K.dpart);
+      else
+        hipLaunchKernelGGL(k_kpt_dens_lds<32>, grid, dim3(256), lds, K.stream, kd, G, K.nchunk, K.dpart);
+      check_launch("k_kpt_dens_lds");
+      hipLaunchKernelGGL(k_kpt_dens_sum, dim3(nblocks(K.ntot)), dim3(256), 0, K.stream, K.dpart, kc * K.nchunk,
+                         K.ntot, dens, k0 == 0 ? 1 : 0);
+      check_launch("k_kpt_dens_sum");
+    }
     return;
   }
   for (int k0 = 0; k0 < K.nk; k0 += K.kchunk) {

@@ -154,7 +154,7 @@ struct KptDev {
   GPtr<cplx<double>> HD;
   GPtr<cplx<double>> S;      // [nb][nb] subspace matrices
   GPtr<cplx<double>> H;
-  GPtr<cplx<double>> W;
+  GPtr<cplx<double>> W;      // above kKptLdsBands
   GPtr<cplx<double>> V;
   GPtr<cplx<double>> M;
   GPtr<cplx<double>> C;
@@ -175,14 +175,31 @@ struct KptSet {
   const FftPlan* plans;
   int lds_class;             // kpt_lds_class of the grid
   cplx<double>* z;           // [kchunk][nb][ntot] grids (lds_class 0)
-  int kchunk;
-  double* dpart;             // [nk][nchunk][ntot] density parts (lds_class > 0)
+  int kchunk;                // k-points at a time: grids, or density parts
+  double* dpart;             // [kchunk][nchunk][ntot] density parts (lds_class > 0)
   int nchunk;
 };
+// k-points whose grids (of `bytes` each) are held at a time, at least one: 256 MB
+// of them fill the chip and stay in its last cache.  32 k-points of 24 bands on
+// 48^3: 114 ms for three iterations with 6 at a time, 129 ms with all (1.36 GB).
+inline int kpt_grid_chunk(int nk, size_t bytes) {
+  const size_t c = (size_t)256000000 / (bytes ? bytes : 1);
+  return c < 1 ? 1 : (c < (size_t)nk ? (int)c : nk);
+}
+// The largest of want, want / 2, ... 1 for which alloc(size(chunk)) succeeds; 0 if
+// none does.
+template <class Size, class Alloc>
+int largest_chunk(int want, Size size, Alloc alloc) {
+  for (int c = want;; c = (c + 1) / 2) {
+    if (alloc(size(c))) return c;
+    if (c == 1) return 0;
+  }
+}
 // conj(a) . b into matrix out: 0 S, 1 H, 2 C, 3 P (a = W_BETA)
 struct KptProduct {
   int a, b, out;
 };
+constexpr int kKptLdsBands = 64;  // subspace matrices in LDS up to here, above in W and V
 int kpt_lds_class(const int N[3], size_t lds_limit);
 void kpt_zero(hipStream_t s, cplx<double>* a, long n);
 void kpt_hpsi(const KptSet& K, int src, int dst, const double* veff, const double* h);

@@ -54,3 +54,35 @@ def test_grids(grid):
 def test_no_projectors():
     say("k-points, local potential only, fixed occupations")
     _check(workloads.tiny_system("si", ecut=3.0, grid=(12, 12, 12)))
+
+
+def _solve(s, K, W):
+    import paper_1603_02732_amd as sgo
+    ctx = sgo.context_from_system(s, sgo.SGO_FP64)
+    ctx.set_kpoints(K, W)
+    assert ctx.scf(tol_e=1e-10, tol_rho=1e-8, max_iter=200)["converged"]
+    return ctx
+
+
+@pytest.mark.parametrize("grid,copies", [(48, 16), (12, 260)])
+def test_many_k_points_in_chunks(grid, copies):
+    """More k-points than one chunk of grids (48^3: 14 k-points of 256 MB) or of
+    density parts (512 k-points) holds: two k-points, each `copies` times over,
+    against the two alone; and the device memory that the chunk allows: 256 MB
+    of grids and each k-point's own arrays (10 bands, fewer than 300
+    coefficients: under 1 MB), 16 MB for the allocations' granularity."""
+    import torch
+    s = workloads.tiny_system("c", ecut=3.0, grid=(grid,) * 3)
+    _solve(workloads.tiny_system("c", ecut=3.0, grid=(12, 12, 36)), K, W)  # one-time allocations
+    free = [torch.cuda.mem_get_info()[0]]
+    few = _solve(s, K, W)
+    free.append(torch.cuda.mem_get_info()[0])
+    many = _solve(s, K * copies, W * copies)
+    free.append(torch.cuda.mem_get_info()[0])
+    more = (free[1] - free[2]) - (free[0] - free[1])
+    dE = many.energy()[0] - few.energy()[0]
+    dF = np.abs(many.forces() - few.forces()).max()
+    say("k-points %d on %d^3: dE %.2e dF %.2e, %.1f MB more" % (2 * copies, grid, dE, dF, more / 1e6))
+    assert abs(dE) < 1e-6 * 4 and dF < 1e-4
+    if grid == 48:
+        assert more < 256e6 + 2 * copies * 1e6 + 16e6
