@@ -597,9 +597,15 @@ __global__ void __launch_bounds__(kNT) k_gram_reduce(const CandDesc* __restrict_
 // clamped addresses all at once (behind a bounds test each they went one after
 // another), and the tiles' MFMAs go to all four wavefronts whatever their
 // number.  20 x 1,168 values 5.6 us (11.0 before), 4 x 24 x 12,100 13.6 us (19.2).
+// 33 to 64 rows (NIB = 4) are held to 128 registers, four wavefronts a SIMD: the
+// compiler takes 203 by itself, two, which many blocks cannot make up for (16
+// structures of 64 bands x 12,100 values 177 -> 77 us, 135 with a 16-row tile a
+// wavefront; one of 64 x 2,976 20.8 -> 13.8 us, 20.0).  More rows run at three and
+// (129 to 320, 160 accumulators) one wavefront a SIMD: 128 x 2,976 41 -> 28 us, 16
+// x 128 x 12,100 410 -> 235 us, 320 x 2,976 170 -> 102 us against such tiles.
 constexpr int kJC = 32;
 template <typename T, int NIB>
-__global__ void __launch_bounds__(kNT) k_gemm_acc(const CandDesc* __restrict__ cds, int y0, int y1,
+__global__ void __launch_bounds__(kNT, NIB == 4 ? 4 : 1) k_gemm_acc(const CandDesc* __restrict__ cds, int y0, int y1,
                                                   int y2, int a0, int a1, int a2, int mat,
                                                   double alpha, double beta, int use_h) {
   const CandDesc& cd = cds[blockIdx.z];
