@@ -823,10 +823,16 @@ __device__ __forceinline__ double tpa(double x) {
 // values in FP64, direction / line minimisation / kinetic energy: 52 / 49 /
 // 16 us with 256 threads and one value a thread and step, 18 / 20 / 5 us so.
 constexpr int kWideNT = 1024, kPairs = 4;
-// 256 threads where one step of them covers a band: 16 wavefronts' partial sums
-// cost more than they save (20 bands of 1,168 values: line minimisation 8.3 us
-// with 1,024 threads, 5.1 us with 256).
-static int band_threads(const BatchGeom& g) { return g.K_max <= 2 * 256 * kPairs ? 256 : kWideNT; }
+// As many threads as hold a band in one step (a band of K values has K / 2
+// coefficients), 256 to 1,024: wavefronts without a value only cost residency and
+// a partial sum.  16 structures of 128 bands x 2,976 values, direction / line
+// minimisation / kinetic energy: 37 / 52 / 13 us with the 384 threads that hold
+// them, 70 / 88 / 20 us with 1,024; 20 bands of 1,168 values: line minimisation 5.1
+// us with 256, 8.3 us with 1,024.
+static int band_threads(const BatchGeom& g) {
+  const int waves = (g.K_max / 2 + 64 * kPairs - 1) / (64 * kPairs);
+  return 64 * std::max(4, std::min(kWideNT / 64, waves));
+}
 template <typename T>
 struct Pair;
 template <>
