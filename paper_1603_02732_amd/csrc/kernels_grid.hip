@@ -1616,9 +1616,13 @@ void launch_grid_fft(const LaunchCtx& L, int sign) {
   const BatchGeom& g = L.g;
   const int ntx = (g.N1max + kTX - 1) / kTX;
   const size_t lds_xy = sizeof(cplx<double>) * (2 * kMaxFftN + (size_t)g.plane_max + g.N2max) + 2 * kMaxFftN;
-  // whole planes where they fit the LDS and either are small or fill the chip: 40
-  // planes of 80 x 50 take 17.8 us this way, 13.1 us as rows and columns
-  if (lds_xy <= g.lds_limit && (g.plane_max <= 2048 || g.N3max * g.ncand >= 256)) {
+  // Whole planes up to what leaves two blocks a compute unit (about 4,600 points):
+  // 64 planes of 16 structures, 64 x 64: 86 us a transform this way, 105 us as rows
+  // and columns; 40 planes of 16, 72 x 64: 75 against 86 us, but 72 x 72: 98 against
+  // 94 us, 96 planes of four, 96 x 96: 109 against 97 us.  Few large planes leave
+  // more of the chip idle than rows and columns do: 48 of 48 x 48 24 against 27 us,
+  // 40 of 80 x 50 29 against 28 us.
+  if (2 * lds_xy <= g.lds_limit && (g.plane_max <= 2048 || g.N3max * g.ncand >= 48)) {
     prof_before("k_grid_fft_xy", L.stream);
     hipLaunchKernelGGL(k_grid_fft_xy, dim3(g.N3max, 1, g.ncand), dim3(kNT), lds_xy, L.stream, L.desc, sign);
     check_launch("k_grid_fft_xy");

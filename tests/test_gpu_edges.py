@@ -134,3 +134,25 @@ def test_batch_results_match_single_solves():
             say("candidate %d of %s: dE %.2e" % (i, sizes, e[i] - one.energy()[0]))
             assert abs(e[i] - one.energy()[0]) < 1e-7
             assert np.abs(f[i] - one.forces()).max() < 1e-5
+
+
+@pytest.mark.parametrize("grid,count", [((72, 64, 10), 5), ((64, 72, 12), 4), ((125, 27, 10), 5), ((45, 50, 16), 3)])
+def test_grid_transforms_of_planes_and_lines(grid, count):
+    """Grid transforms of whole planes (enough planes to fill the chip, here
+    `count` copies) against rows and columns (the structure alone): two
+    iterations from the same start, so they differ by FP64 rounding (1e-16 of 20
+    Ha, of densities and forces of order one) and what two iterations make of
+    it: some 20 steps that divide by level spacings of 0.01 to 0.1 Ha, a factor
+    of 1e6 at most, and ten more for the forces' sums over G."""
+    import paper_1603_02732_amd as sgo
+    s = workloads.tiny_system("c", ecut=2.0, grid=grid)
+    r = {}
+    for n in (1, count):
+        b = sgo.Batch(n, precision=sgo.SGO_FP64)
+        for _ in range(n):
+            b.add_system(s)
+        e, f, _ = b.scf(sgo.default_opts(max_iter=2, tol_e=1e-12, tol_rho=1e-12))
+        r[n] = (e[0], f[0], b.state(0)["rho"])
+    say("grid", grid, "dE %.2e dF %.2e" % (r[1][0] - r[count][0], np.abs(r[1][1] - r[count][1]).max()))
+    assert abs(r[1][0] - r[count][0]) < 2e-9 and np.abs(r[1][1] - r[count][1]).max() < 1e-9
+    assert np.abs(r[1][2] - r[count][2]).max() < 1e-10
