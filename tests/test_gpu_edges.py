@@ -156,3 +156,29 @@ def test_grid_transforms_of_planes_and_lines(grid, count):
     say("grid", grid, "dE %.2e dF %.2e" % (r[1][0] - r[count][0], np.abs(r[1][1] - r[count][1]).max()))
     assert abs(r[1][0] - r[count][0]) < 2e-9 and np.abs(r[1][1] - r[count][1]).max() < 1e-9
     assert np.abs(r[1][2] - r[count][2]).max() < 1e-10
+
+
+@pytest.mark.parametrize("nb", [16, 17, 31, 32, 33, 48, 64, 65, 128, 129, 193, 199])
+def test_bands_are_ritz_vectors(nb):
+    """The bands of one pass are the Ritz vectors of their own span: psi H psi^T
+    with H applied anew, in the potential that they were solved in, is diagonal
+    and holds their eigenvalues (a wrong H product, congruence, rotation or
+    order shows here; orthonormality alone would not).  The occupations add up
+    under Fermi filling.  H psi is within 1e-11 of its largest element (the
+    operator's bound), below 10 Ha for |k| <= 4 Ha and this potential: 1e-10."""
+    import paper_1603_02732_amd as sgo
+    s = workloads.tiny_system("sip", ecut=4.0, grid=(15, 15, 16), nbands=nb,
+                              occupation=configs.FIXED if nb == 16 else configs.FERMI)
+    b = sgo.Batch(1, precision=sgo.SGO_FP64)
+    b.add_system(s)
+    b.scf(sgo.default_opts(max_iter=1, ncg_first=2, tol_e=1e-10, tol_rho=1e-8))
+    st = b.state(0)
+    psi = st["psi"]
+    ctx = sgo.context_from_system(s, sgo.SGO_FP64)
+    H = psi @ ctx.apply_h(st["veff"], psi).T
+    dev = np.abs(H - np.diag(st["eig"])).max()
+    say("bands %d: |psi H psi^T - eig| %.2e, charge %.12f" % (nb, dev, st["occ"].sum()))
+    assert dev < 1e-10
+    assert np.abs(psi @ psi.T - np.eye(nb)).max() < 1e-11
+    assert np.all(np.diff(st["eig"]) >= 0)
+    assert abs(st["occ"].sum() - 32.0) < 1e-9
