@@ -67,3 +67,32 @@ def test_equal_diagonals(n):
     S, H = _problem(n, "ties")
     M, e = _noalloc(S, H, 3)
     _check(S, H, M, e)
+
+
+@pytest.mark.parametrize("mode", [1, 3])
+@pytest.mark.parametrize("n", [20, 40, 100, 150, 198, 200])
+def test_not_positive_definite(n, mode):
+    """Every Cholesky: up to 32, 64, 128, 192 and 198 bands in registers, above
+    in panels; the bad pivot first, in the middle and last.  The status says so,
+    M is the identity, the inputs stay, and the next call is not affected."""
+    import torch
+    S, H = _problem(n, "random")
+    tH = torch.from_numpy(H).cuda()
+    e = torch.zeros(n, dtype=torch.float64, device="cuda")
+    for bad in (0, n // 2, n - 1):
+        print("n=%d mode=%d bad pivot %d" % (n, mode, bad), flush=True)
+        B = S.copy()
+        B[bad, bad] = -1.0
+        tS = torch.from_numpy(B).cuda()
+        M = torch.full((n, n), float("nan"), dtype=torch.float64, device="cuda")
+        st = torch.zeros(1, dtype=torch.int32, device="cuda")
+        sgo.subspace_solve_noalloc(tS.data_ptr(), tH.data_ptr(), M.data_ptr(), e.data_ptr(), n, mode,
+                                   status=st.data_ptr(), stream=torch.cuda.current_stream().cuda_stream)
+        assert int(st.item()) == sgo.SGO_ENUMERIC
+        assert np.array_equal(M.cpu().numpy(), np.eye(n))
+        assert np.array_equal(tS.cpu().numpy(), B) and np.array_equal(tH.cpu().numpy(), H)
+        with pytest.raises(sgo.SgoError) as err:
+            sgo.subspace_solve(B, H, mode=mode)
+        assert err.value.code == sgo.SGO_ENUMERIC
+        M, _ = _noalloc(S, H, mode)
+        assert np.abs(M.T @ S @ M - np.eye(n)).max() < TOL
