@@ -731,7 +731,7 @@ class Engine {
       g.pl_sx_max = std::max(g.pl_sx_max, c.pl_sx);
     }
     g.sp_chunk = std::max(1, tune("SGO_SP_CHUNK", std::max(1, 640 / std::max(1, g.N3max))));
-    {  // the z kernels hold 2 x (2 sp_chunk) sticks of N3 complex values in LDS
+    {  // the z kernels hold 2 sp_chunk sticks of N3 complex values in LDS, twice within reach
       const size_t cplx_bytes = 2 * tsize();
       const int cap = (int)(((size_t)g_lds_limit / cplx_bytes - kMaxFftN) / (4 * (size_t)std::max(1, g.N3max)));
       g.sp_chunk = std::max(1, std::min(g.sp_chunk, cap));
@@ -774,6 +774,8 @@ class Engine {
     return g;
   }
 
+  // What is accepted: planes of which two fit the LDS (the FP64 and long-line
+  // kernels need one), 12,288 points, 320 bands.
   void check_lds(const BatchGeom& g) {
     const size_t ts = tsize();
     const size_t plane = 2 * ts * (2 * kMaxFftN + 2 * (size_t)g.plane_max);

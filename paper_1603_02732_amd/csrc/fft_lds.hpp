@@ -1,17 +1,17 @@
 // Batched line transforms in LDS, in place.
 //
 // N = r0 r1 (r2) with radices up to 10 whose butterflies sit in a thread's
-// registers (fft_reg.hpp), so a line of up to 100 takes two passes over the LDS and
-// one buffer, where radix-2/3/4/5 passes between two buffers take three or four.  The
-// results are not put in order: lds_dif takes natural order to digit-reversed
-// positions, lds_dit digit-reversed positions back to natural order, and what
-// lies between (V_eff, the density, a store) looks positions up in a table of N
-// bytes.  Lines are at an odd pitch and consecutive lanes take consecutive
+// registers (fft_reg.hpp), so most lines up to 100 (all but 75 and 96, which take
+// three) take two passes over the LDS and one buffer, where radix-2/3/4/5 passes
+// between two buffers take three or four.  The results are not put in order: lds_dif
+// takes natural order to digit-reversed positions, the stages backwards (dit) take
+// those back to natural order, and what lies between (V_eff, the density, a
+// store) looks positions up in a table of N bytes.  Lines are at an odd pitch and consecutive lanes take consecutive
 // lines, so the wavefront's addresses fall into different banks in every pass.
 //
 // With n2 = the index within a stride and L the length left to a stage,
 //   lds_dif: butterfly over r at stride L / R, then times w_L^(n2 k);
-//   lds_dit: the stages backwards, times w_L^(n2 r), then the butterfly.
+//   dit:     the stages backwards, times w_L^(n2 r), then the butterfly.
 // The sign is a conjugation on the way in and out (sg = +-1).
 #pragma once
 #include "device.hpp"
@@ -114,10 +114,6 @@ __device__ __forceinline__ void lds_stages(cplx<T>* A, const LdsLines& ln, const
 template <typename T>
 __device__ __forceinline__ void lds_dif(cplx<T>* A, const LdsLines& ln, const FftPlan& P, const cplx<T>* tw, T sg) {
   lds_stages<T>(A, ln, P, tw, false, sg, 0, P.nr);
-}
-template <typename T>
-__device__ __forceinline__ void lds_dit(cplx<T>* A, const LdsLines& ln, const FftPlan& P, const cplx<T>* tw, T sg) {
-  lds_stages<T>(A, ln, P, tw, true, sg, 0, P.nr);
 }
 
 }  // namespace sgo

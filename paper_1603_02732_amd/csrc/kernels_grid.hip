@@ -2,10 +2,11 @@
 // sums, density residual and Pulay/Kerker mixing (the step of the SCF loop of
 // Section 2.4 that combines the output density with the input one),
 // potentials, per-geometry setup (local potential and starting density from
-// structure factors, Ewald sum), Hellmann-Feynman force sums, occupations,
-// and the FP64 subspace solver (Cholesky orthonormalisation + Jacobi
-// diagonalisation: the orthogonalisation and subspace-diagonalisation steps
-// of Algorithm 1).
+// structure factors, Ewald sum), Hellmann-Feynman force sums, occupations;
+// and of the FP64 subspace solver (the orthogonalisation and
+// subspace-diagonalisation steps of Algorithm 1) the problems above kJacWideMax
+// bands, the congruence that the smaller ones share, and the allocation-free
+// entry point (kernels_sub.hip has the solver up to kJacWideMax).
 #include "fft_lds.hpp"
 #include "jacobi.hpp"
 
@@ -1488,7 +1489,7 @@ __global__ void __launch_bounds__(kNT) k_sub_twt(const CandDesc* __restrict__ cd
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n * n) return;
   const int i = e / n, j = e - i * n;
-  cd.M[e] = i == j ? 1.0 : 0.0;  // V^T = I
+  cd.M[e] = i == j ? 1.0 : 0.0;  // V^T = I (up to kJacWideMax bands k_sub_vapply writes M anew)
   if (i > j) return;
   const double* W = cd.C;
   const double* T = cd.S;
@@ -1867,9 +1868,9 @@ void launch_sub_congruence(hipStream_t st, const CandDesc* desc, int ncand, int 
   check_launch("k_sub_twt");
 }
 
-// One Jacobi sweep over the GPU (n2 - 1 rounds of two launches each),
+// One Jacobi sweep over the GPU (n2 - 1 rounds of a launch each, and a copy),
 // replayed from a graph captured once per (device, descriptor array,
-// candidates, bands, stream): a sweep of 282 bands is 562 short launches, and
+// candidates, bands, stream): a sweep of 282 bands is 282 short launches, and
 // the host's launch rate, not the kernels, set its pace.  The graphs live
 // until the process ends (at most kSweepGraphs; past that, and on the legacy
 // null stream, sweeps launch eagerly); the kernels read every size from the descriptors, so a graph
@@ -1973,9 +1974,10 @@ void launch_subspace(const LaunchCtx& L, int mode, int max_sweeps) {
 // ------------------------------------------------ allocation-free subspace
 // Workspace of the allocation-free form of the subspace step (for callers
 // that cannot allocate device memory: code under HIP graph capture, serving
-// loops): one fixed device array per GPU holding the solver's descriptor,
-// its status block and working copies of S and H plus the third matrix of
-// the global-memory solver, for up to kNoAllocMaxN bands.  The array lives
+// loops): one fixed device array per GPU (13.4 MiB) holding the solver's descriptor,
+// its status block, working copies of S and H and a third matrix for up to
+// kNoAllocMaxN bands, and the rotation log of kJacWideMax bands (12 MiB; more
+// bands are solved in global memory by one workgroup, without a log).  It lives
 // until the process ends; host code reaches it only through the address that
 // hipGetSymbolAddress returns on each device (the array's name is a
 // host-side stand-in, not a device address).  Every call on a GPU shares

@@ -456,7 +456,10 @@ __device__ __forceinline__ void kpt_sub_failed(const KptDev& k, int* fail) {
 // M's rows rotated by the wavefronts without blocks, a round behind.  Bound by
 // the dependent chain of a round (LDS read, rotation, exchange, update, barrier),
 // (n - 1) rounds a sweep: 2 k-points of 20 bands take 58.6 us together, where the
-// pairs in turn, with the matrices in global memory, took 604 us each.
+// pairs in turn, with the matrices in global memory, took 604 us each.  R = 8 keeps
+// 84 bytes a lane in scratch memory (16 wavefronts leave 128 registers): a solve at
+// 64 bands is 3.8 times as fast as at 65, in global memory (2 k-points, 24^3, three
+// iterations: 14.8 and 55.7 ms).
 template <int R>
 constexpr int kpt_sub_threads() { return R == 4 ? 512 : 1024; }
 template <int R>

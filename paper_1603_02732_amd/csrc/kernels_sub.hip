@@ -295,8 +295,9 @@ __global__ void __launch_bounds__(sub_small_threads<R>()) k_sub_small(const Cand
 
 // Cholesky and W = L^-1 (into C) above 64 bands: the same elimination, 16
 // wavefronts, NR rows and NQ columns a lane (<2, 8>: 128, <3, 12>: 192, <4, 13>:
-// 208).  112 bands 56 us; 164 bands 119 us, 435 us by blocks of rows in global
-// memory.
+// 208; the last keeps 13 registers in scratch memory).  112 bands 56 us; 164 bands
+// 119 us, 435 us by blocks of rows in global memory; 198 bands with M = W^T 192 us,
+// 539 us.
 template <int NQ, int NR>
 __global__ void __launch_bounds__(1024) k_sub_chol(const CandDesc* __restrict__ cds) {
   const CandDesc& cd = cds[blockIdx.x];
@@ -350,7 +351,7 @@ __global__ void __launch_bounds__(kNT) k_sub_wt(const CandDesc* __restrict__ cds
 template <int ITEMS>
 __global__ void __launch_bounds__(1024) k_sub_jacobi(const CandDesc* __restrict__ cds, int max_sweeps) {
   const CandDesc& cd = cds[blockIdx.x];
-  if (!cd.active || cd.scal[S_ERR] == 2.0) return;  // inactive, or this call's Cholesky failed
+  if (!cd.active || cd.scal[S_ERR] == 2.0) return;  // inactive, or a Cholesky failed
   const int n = cd.nb, n2 = n + (n & 1), np = n2 / 2, m = n2 - 1;
   const int nblk = np * (np + 1) / 2, nt = n2 * (n2 + 1) / 2;
   const int tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;

@@ -10,8 +10,7 @@
 //    projection steps of Algorithm 1), FP64 accumulation.
 //  * per-band CG kernels: residual + preconditioning + CG direction, and the
 //    line minimisation over the angle theta.
-//  * the FP64 subspace solver: Cholesky orthonormalisation and Jacobi
-//    diagonalisation of the subspace Hamiltonian.
+// (The FP64 subspace solver is in kernels_sub.hip and kernels_grid.hip.)
 #include "device.hpp"
 #include "fft_lds.hpp"
 #include "launch.hpp"
@@ -257,8 +256,9 @@ __device__ __forceinline__ void plane_vmul(const Plane<T>& P, int N1, int N2, co
 // One z-plane of one band pair: gather the stick values, inverse 2-D FFT,
 // multiply by V_eff(r), forward 2-D FFT, scatter back to the sticks.
 //
-// Bound by the LDS passes and their index arithmetic: 7 passes in place for
-// lines of 12 to 100, where radix-4/2/3/5 passes between two buffers took 13.
+// Bound by the LDS passes and their index arithmetic: 7 passes in place where both
+// axes have two stages (most lengths of 12 to 100; 75 and 96 have three), where
+// radix-4/2/3/5 passes between two buffers took 13.
 // 4 clusters of 24 FP64 bands, 40^3: 94 -> 48 us (density 73 -> 35); 164 FP32 bands,
 // planes of 80 x 50: 226 -> 84 us (137 -> 72); 20 bands, 24^3 (240 blocks, one a
 // CU: latency) 12.6 -> 12.5 us.  The z transforms likewise: 23 -> 12, 27 -> 19 and
@@ -274,8 +274,8 @@ __global__ void __launch_bounds__(kNT, 4) k_plane_hpsi(const CandDesc* __restric
   const Plane<T> P = plane_of_block<T>(cd, smem);
   cplx<T>* st = (cplx<T>*)cd.sticks + ((size_t)pair * cd.N3 + z) * cd.nst;
   const T* V = (const T*)cd.veff_t + (size_t)z * N1 * N2;
-  // a value of every cache line of V, read here so that the plane is near when
-  // it is needed
+  // a value of every cache line of V's first 32 KB (a whole plane up to 4,096 FP64
+  // points), read here so that the plane is near when it is needed
   const T ahead = V[min((int)(threadIdx.x * (128 / sizeof(T))), N1 * N2 - 1)];
   plane_fill<T>(cd, P, st, true);
   const int n1 = cd.plan[0].nr;
