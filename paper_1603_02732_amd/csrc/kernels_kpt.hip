@@ -17,7 +17,7 @@
 // one workgroup per k.  8 silicon atoms, 15^3, 20 bands, 2 k-points: 3,130
 // launches and 110 ms per solve with a launch per k, pass and array and one
 // 256-thread workgroup walking the Jacobi pairs of a k in turn, 790 launches and
-// 11.1 ms this way.
+// 10.1 ms this way (other positions take 8 to 13 ms, by their iterations).
 #include "device.hpp"
 #include "fft_lds.hpp"
 #include "jacobi.hpp"

@@ -86,7 +86,8 @@ template <typename T> void launch_stress_waves(const LaunchCtx& L);
 template <typename T> void launch_potential_finalize(const LaunchCtx& L);
 void launch_subspace(const LaunchCtx& L, int mode, int max_sweeps = kJacMaxSweeps);
 // Its parts: the one-workgroup step up to kJacWideMax bands (kernels_sub.hip; at
-// most kJacMaxSweeps sweeps, whatever is asked for) and the products that it shares with the larger problems.
+// most kJacMaxSweeps sweeps, whatever is asked for) and the products that it
+// shares with the larger problems.
 void launch_sub_block(hipStream_t st, const CandDesc* desc, int ncand, int n, int mode, int max_sweeps);
 void launch_sub_congruence(hipStream_t st, const CandDesc* desc, int ncand, int n);
 void configure_sub_kernels();
