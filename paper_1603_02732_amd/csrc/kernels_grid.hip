@@ -1273,84 +1273,40 @@ __device__ __forceinline__ bool chol_inv_blocked(double* __restrict__ A, double*
   return true;
 }
 
-// In global memory (above kJacWideMax bands; the
-// smaller problems' kernels are in kernels_sub.hip).  phase 0: the whole solve;
-// 1: Cholesky and W = L^-1 only (the congruence, the Jacobi rounds from
-// g.jac_grid bands and M = W^T V then run over the whole GPU: k_sub_*, k_jac_*);
-// 3: the Jacobi rounds of the H' that k_sub_wh/k_sub_twt formed; 2: eigenvalue
-// order and the sorted M, eps from the converged H' and the product W^T V
-// already in S.
+// In global memory, one workgroup a candidate (above kJacWideMax bands; the
+// smaller problems' kernels are in kernels_sub.hip):
+//   1: Cholesky and W = L^-1, for mode 1 M = W^T (the congruence and M = W^T V run
+//      over the GPU, k_sub_*, and from g.jac_grid bands the Jacobi rounds, k_jac_*);
+//   3: the Jacobi rounds of the H' that k_sub_wh/k_sub_twt formed (in Hs; V^T = I in M);
+//   2: eigenvalue order and the sorted M, eps from the converged H' and the
+//      product W^T V in S (max_sweeps: the sweeps that the rounds took).
+template <int PHASE>
 __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict__ cds, int mode,
-                                                     int max_sweeps, int phase) {
+                                                     int max_sweeps) {
   const CandDesc& cd = cds[blockIdx.x];
   if (!cd.active) return;
   const int n = cd.nb;
   const int tid = threadIdx.x, nthr = blockDim.x;
-  const int ld = n;
   extern __shared__ __align__(16) char smem[];
-  double *P0 = cd.S, *P1 = cd.Hs, *P2 = cd.C, *P3 = cd.M;  // L, H / H', W = L^-1, scratch / V
-  double* H1 = P1;
-  const int ldh = ld;
-  __shared__ double sh[16 * 2];
-  __shared__ int rank[640];
-  __shared__ double rc[320], rs[320];
-  __shared__ int rp[320], rq[320];
+  double *S = cd.S, *H1 = cd.Hs, *W = cd.C, *Vt = cd.M;
+  const int ld = n, ldh = n;
   long long* clk = cd.dbg_clk;
-  if (phase == 2 && clk && tid == 0) {
-    clk[3] = clock64();
-    clk[5] = max_sweeps;  // the sweeps the grid rounds took
-  }
-  if (phase == 2 && cd.scal[S_ERR] == 2.0) {
-    // this call's Cholesky failed: the rotation stays the identity
-    for (int e = tid; e < n * n; e += nthr) cd.M[e] = (e / n == e % n) ? 1.0 : 0.0;
-    return;
-  }
-  if (phase == 3) {
-    // Jacobi of the H' that the products over the GPU formed (in Hs; V^T = I
-    // in M), unless this call's Cholesky failed
-    if (cd.scal[S_ERR] == 2.0) return;
-  }
-  if (phase != 2) {
-   if (phase != 3) {
+  if constexpr (PHASE == 1) {
     if (clk && tid == 0) clk[0] = clock64();
-    __syncthreads();
-    if (!chol_inv_blocked(P0, P2, n, ld, (double*)smem, tid, nthr)) {
+    if (!chol_inv_blocked(S, W, n, ld, (double*)smem, tid, nthr)) {
       if (tid == 0) cd.scal[S_ERR] = 2.0;
       for (int e = tid; e < n * n; e += nthr) cd.M[e] = (e / n == e % n) ? 1.0 : 0.0;
       return;
     }
     if (clk && tid == 0) clk[1] = clock64();
-    if (mode == 1) {
-      for (int e = tid; e < n * n; e += nthr) cd.M[e] = P2[(e % n) * ld + e / n];
-      return;
-    }
-    if (phase == 1) return;  // W is ready; the products run over the GPU
-    // H' = W H W^T (symmetrised)
-    for (int e = tid; e < n * n; e += nthr) {
-      const int i = e / n, j = e % n;
-      double s = 0.0;
-      for (int k = 0; k <= i; ++k) s = fma(P2[i * ld + k], P1[k * ld + j], s);
-      P3[i * ld + j] = s;
-    }
-    __syncthreads();
-    for (int e = tid; e < n * n; e += nthr) {
-      const int i = e / n, j = e % n;
-      double s = 0.0;
-      for (int k = 0; k <= j; ++k) s = fma(P3[i * ld + k], P2[j * ld + k], s);
-      H1[i * ldh + j] = s;
-    }
-    __syncthreads();
-    for (int e = tid; e < n * n; e += nthr) {
-      const int i = e / n, j = e % n;
-      if (i < j) {
-        const double a = 0.5 * (H1[i * ldh + j] + H1[j * ldh + i]);
-        H1[i * ldh + j] = a;
-        H1[j * ldh + i] = a;
-      }
-      P3[i * ld + j] = (i == j) ? 1.0 : 0.0;
-    }
-    __syncthreads();
-   }
+    if (mode == 1)
+      for (int e = tid; e < n * n; e += nthr) cd.M[e] = W[(e % n) * ld + e / n];
+  }
+  if constexpr (PHASE == 3) {
+    if (cd.scal[S_ERR] == 2.0) return;  // a Cholesky failed
+    __shared__ double sh[16 * 2];
+    __shared__ double rc[320], rs[320];
+    __shared__ int rp[320], rq[320];
     // Cyclic Jacobi with the round-robin ordering of disjoint index pairs.
     // Phase A computes the rotations of a round; in phase B the threads take
     // the (row pair, column pair) 2x2 blocks, rotating them in place, then
@@ -1411,17 +1367,17 @@ __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict_
             if (p2v && q2v) H1[p2 * ldh + q2] = sQ * b21 + cQ * b22;
           }
         } else {
-          // V is stored transposed (P3[q][i] = V[i][q]): the column rotation of
-          // pair P updates rows p1, p2 of P3 (consecutive threads, consecutive i)
+          // V is stored transposed (Vt[q][i] = V[i][q]): the column rotation of
+          // pair P updates rows p1, p2 of Vt (consecutive threads, consecutive i)
           for (int t = tid - half; t < npair * n; t += half) {
             const int P = t / n, i = t - P * n;
             const double sP = rs[P];
             const int p1 = rp[P], p2 = rq[P];
             if (sP == 0.0 || p2 >= n) continue;
             const double cP = rc[P];
-            const double vp = P3[p1 * ld + i], vq = P3[p2 * ld + i];
-            P3[p1 * ld + i] = cP * vp - sP * vq;
-            P3[p2 * ld + i] = sP * vp + cP * vq;
+            const double vp = Vt[p1 * ld + i], vq = Vt[p2 * ld + i];
+            Vt[p1 * ld + i] = cP * vp - sP * vq;
+            Vt[p2 * ld + i] = sP * vp + cP * vq;
           }
         }
         __syncthreads();
@@ -1431,35 +1387,36 @@ __global__ void __launch_bounds__(kSubNT) k_subspace(const CandDesc* __restrict_
       clk[3] = clock64();
       clk[5] = nsweep;
     }
-    if (phase == 3) return;  // M = W^T V and the sort (phase 2) follow
   }
-  // ranks of the eigenvalues (ascending, ties by index)
-  for (int i = tid; i < n; i += nthr) {
-    const double li = H1[i * ldh + i];
-    int rnk = 0;
-    for (int j = 0; j < n; ++j) {
-      const double lj = H1[j * ldh + j];
-      if (lj < li || (lj == li && j < i)) ++rnk;
+  if constexpr (PHASE == 2) {
+    __shared__ int rank[640];
+    if (clk && tid == 0) {
+      clk[3] = clock64();
+      clk[5] = max_sweeps;
     }
-    rank[i] = rnk;
-  }
-  // M = W^T V into P0 (L is no longer needed); P3 holds V^T.  In phase 2
-  // the product has already been formed over the GPU (k_sub_compose).
-  if (phase != 2) {
+    if (cd.scal[S_ERR] == 2.0) {
+      // a Cholesky failed: the rotation stays the identity
+      for (int e = tid; e < n * n; e += nthr) cd.M[e] = (e / n == e % n) ? 1.0 : 0.0;
+      return;
+    }
+    // ranks of the eigenvalues (ascending, ties by index)
+    for (int i = tid; i < n; i += nthr) {
+      const double li = H1[i * ldh + i];
+      int rnk = 0;
+      for (int j = 0; j < n; ++j) {
+        const double lj = H1[j * ldh + j];
+        if (lj < li || (lj == li && j < i)) ++rnk;
+      }
+      rank[i] = rnk;
+    }
+    __syncthreads();
     for (int e = tid; e < n * n; e += nthr) {
       const int j = e / n, i = e % n;
-      double s = 0.0;
-      for (int k = j; k < n; ++k) s = fma(P2[k * ld + j], P3[i * ld + k], s);
-      P0[j * ld + i] = s;
+      cd.M[j * n + rank[i]] = S[j * ld + i];
     }
+    for (int i = tid; i < n; i += nthr) cd.eps[rank[i]] = H1[i * ldh + i];
+    if (clk && tid == 0) clk[4] = clock64();
   }
-  __syncthreads();
-  for (int e = tid; e < n * n; e += nthr) {
-    const int j = e / n, i = e % n;
-    cd.M[j * n + rank[i]] = P0[j * ld + i];
-  }
-  for (int i = tid; i < n; i += nthr) cd.eps[rank[i]] = H1[i * ldh + i];
-  if (clk && tid == 0) clk[4] = clock64();
 }
 
 // ------------------------------------- subspace products over the GPU
@@ -1855,10 +1812,11 @@ void launch_occupations(const LaunchCtx& L) {
   check_launch("k_occupations");
   prof_after("k_occupations", L.stream);
 }
+template <int PHASE>
 static void launch_k_subspace(int ncand, int n, int nthr, hipStream_t st, const CandDesc* desc, int mode,
-                              int max_sweeps, int phase) {
-  const size_t lds = phase < 2 ? sizeof(double) * (size_t)chol_inv_lds_doubles(n) : 0;
-  hipLaunchKernelGGL(k_subspace, dim3(ncand), dim3(nthr), lds, st, desc, mode, max_sweeps, phase);
+                              int max_sweeps) {
+  const size_t lds = PHASE == 1 ? sizeof(double) * (size_t)chol_inv_lds_doubles(n) : 0;
+  hipLaunchKernelGGL(k_subspace<PHASE>, dim3(ncand), dim3(nthr), lds, st, desc, mode, max_sweeps);
   check_launch("k_subspace");
 }
 void launch_sub_congruence(hipStream_t st, const CandDesc* desc, int ncand, int n) {
@@ -1866,6 +1824,23 @@ void launch_sub_congruence(hipStream_t st, const CandDesc* desc, int ncand, int 
   hipLaunchKernelGGL(k_sub_wh, ge, dim3(kNT), 0, st, desc);
   hipLaunchKernelGGL(k_sub_twt, ge, dim3(kNT), 0, st, desc);
   check_launch("k_sub_twt");
+}
+static void launch_sub_compose(hipStream_t st, const CandDesc* desc, int ncand, int n) {
+  hipLaunchKernelGGL(k_sub_compose, dim3((n * n + kNT - 1) / kNT, ncand), dim3(kNT), 0, st, desc);
+  check_launch("k_sub_compose");
+}
+// Above kJacWideMax bands with the rounds in one workgroup, in global memory: no host
+// read and no allocation (graph capture, the allocation-free entry point, mode 1).
+// 199 bands 30 ms, 256 bands 67 ms without allocation, nearly all of it the rounds;
+// 34 and 77 ms with the congruence and M = W^T V in the workgroup too.
+static void launch_sub_large(hipStream_t st, const CandDesc* desc, int ncand, int n, int nthr, int mode,
+                             int max_sweeps) {
+  launch_k_subspace<1>(ncand, n, nthr, st, desc, mode, max_sweeps);
+  if (mode == 1) return;
+  launch_sub_congruence(st, desc, ncand, n);
+  launch_k_subspace<3>(ncand, n, nthr, st, desc, mode, max_sweeps);
+  launch_sub_compose(st, desc, ncand, n);
+  launch_k_subspace<2>(ncand, n, nthr, st, desc, mode, max_sweeps);
 }
 
 // One Jacobi sweep over the GPU (n2 - 1 rounds of a launch each, and a copy),
@@ -1934,7 +1909,7 @@ void launch_subspace(const LaunchCtx& L, int mode, int max_sweeps) {
   const int nthr = L.g.sub_threads;
   prof_before("k_subspace", L.stream);
   if (mode == 3 && n >= L.g.jac_grid && L.jac_done && host_sync_allowed()) {
-    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 1);
+    launch_k_subspace<1>(nc, n, nthr, L.stream, L.desc, mode, max_sweeps);
     launch_sub_congruence(L.stream, L.desc, nc, n);
     const int n2 = n + (n & 1), npair = n2 / 2;
     const dim3 ga((npair * npair + npair * n + kNT - 1) / kNT, nc);
@@ -1952,21 +1927,12 @@ void launch_subspace(const LaunchCtx& L, int mode, int max_sweeps) {
       jacobi_sweep(L, n, n2, ga);
       ++done_sweeps;
     }
-    hipLaunchKernelGGL(k_sub_compose, dim3((n * n + kNT - 1) / kNT, nc), dim3(kNT), 0, L.stream, L.desc);
-    check_launch("k_sub_compose");
-    // phase 2 takes the sweep count in place of the sweep limit (debug clocks)
-    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, done_sweeps, 2);
+    launch_sub_compose(L.stream, L.desc, nc, n);
+    launch_k_subspace<2>(nc, n, nthr, L.stream, L.desc, mode, done_sweeps);
   } else if (n <= kJacWideMax) {
     launch_sub_block(L.stream, L.desc, nc, n, mode, max_sweeps);
-  } else if (mode == 3) {
-    // under graph capture: the rounds in one workgroup, in global memory
-    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 1);
-    launch_sub_congruence(L.stream, L.desc, nc, n);
-    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 3);
-    hipLaunchKernelGGL(k_sub_compose, dim3((n * n + kNT - 1) / kNT, nc), dim3(kNT), 0, L.stream, L.desc);
-    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 2);
   } else {
-    launch_k_subspace(nc, n, nthr, L.stream, L.desc, mode, max_sweeps, 0);
+    launch_sub_large(L.stream, L.desc, nc, n, nthr, mode, max_sweeps);
   }
   prof_after("k_subspace", L.stream);
 }
@@ -2051,7 +2017,7 @@ int subspace_noalloc(int device, int n, int mode, const double* S, const double*
                      mode == 3 ? H : nullptr, nn);
   check_launch("k_noalloc_stage");
   if (n <= kJacWideMax) launch_sub_block(stream, dd, 1, n, mode, kJacMaxSweeps);
-  else launch_k_subspace(1, n, nthreads, stream, dd, mode, kJacMaxSweeps, 0);
+  else launch_sub_large(stream, dd, 1, n, nthreads, mode, kJacMaxSweeps);
   if (status) {
     hipLaunchKernelGGL(k_noalloc_status, dim3(1), dim3(64), 0, stream, d.scal, status, fail_code);
     check_launch("k_noalloc_status");
@@ -2068,7 +2034,7 @@ void configure_kernels() {
   allow_lds((const void*)k_grid_fft_xy);
   allow_lds((const void*)k_grid_fft_x);
   allow_lds((const void*)k_grid_fft_yz);
-  allow_lds((const void*)k_subspace);
+  allow_lds((const void*)k_subspace<1>);
   configure_sub_kernels();
   configure_wave();
   configure_plane_kernels();

@@ -69,6 +69,43 @@ def test_equal_diagonals(n):
     _check(S, H, M, e)
 
 
+@pytest.mark.parametrize("n", [200, 224, 255, 256])
+def test_largest_without_allocation(n):
+    S, H = _problem(n, "random")
+    M, e = _noalloc(S, H, 3)
+    _check(S, H, M, e)
+
+
+@pytest.mark.parametrize("n", [24, 48, 112, 198, 224])
+def test_captured(n):
+    """The allocation-free step in a HIP graph: every route is launches alone, and
+    each replay, on new matrices and with eager calls in between, gives the
+    eager bits."""
+    import torch
+    probs = [_problem(n, "random")]
+    probs.append((probs[0][0] + 0.01 * np.eye(n), probs[0][1][::-1, ::-1].copy()))
+    eager = [_noalloc(S, H, 3) for S, H in probs]
+    dev = [[torch.from_numpy(x).cuda() for x in p] for p in probs]
+    S, H = dev[0][0].clone(), dev[0][1].clone()
+    M, e = torch.zeros(n, n, dtype=torch.float64, device="cuda"), torch.zeros(n, dtype=torch.float64, device="cuda")
+    st = torch.ones(1, dtype=torch.int32, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        sgo.subspace_solve_noalloc(S.data_ptr(), H.data_ptr(), M.data_ptr(), e.data_ptr(), n, 3,
+                                   status=st.data_ptr(), stream=torch.cuda.current_stream().cuda_stream)
+    for k in (0, 1, 0, 1):
+        print("n=%d replay on matrices %d" % (n, k), flush=True)
+        S.copy_(dev[k][0])
+        H.copy_(dev[k][1])
+        M.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert int(st.item()) == 0
+        assert np.array_equal(M.cpu().numpy(), eager[k][0]) and np.array_equal(e.cpu().numpy(), eager[k][1])
+        _noalloc(*probs[1 - k], 3)
+
+
 @pytest.mark.parametrize("mode", [1, 3])
 @pytest.mark.parametrize("n", [20, 40, 100, 150, 198, 200])
 def test_not_positive_definite(n, mode):
