@@ -1519,6 +1519,10 @@ __global__ void __launch_bounds__(kNT) k_jac_round(const CandDesc* __restrict__ 
   const CandDesc& cd = cds[blockIdx.y];
   if (!cd.active || cd.red_part[kJacDone] != 0.0) return;
   const int n = cd.nb, n2 = n + (n & 1), npair = n2 / 2;
+  // the launches are the largest candidate's rounds: a smaller one's sweep is over
+  // before (in S, as its number of rounds is odd too), and beyond it there is
+  // no pair
+  if (r >= n2 - 1) return;
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   const double* A = (r & 1) ? cd.S : cd.Hs;
   double* B = (r & 1) ? cd.Hs : cd.S;

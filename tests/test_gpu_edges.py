@@ -182,3 +182,25 @@ def test_bands_are_ritz_vectors(nb):
     assert np.abs(psi @ psi.T - np.eye(nb)).max() < 1e-11
     assert np.all(np.diff(st["eig"]) >= 0)
     assert abs(st["occ"].sum() - 32.0) < 1e-9
+
+
+@pytest.mark.parametrize("graph", [0, 2])
+def test_uneven_bands_with_rounds_over_the_gpu(graph):
+    """Candidates of 20 to 200 bands in one batch: the Jacobi rounds of the largest
+    run over the GPU, and the smaller ones' sweeps end before theirs.  Converged
+    energies and forces against solves of one structure (1e-7 Ha, 1e-5 Ha/bohr:
+    the gate)."""
+    import paper_1603_02732_amd as sgo
+    gate = dict(tol_e=1e-10, tol_rho=1e-8, max_iter=100)
+    systems = [workloads.tiny_system("sip", ecut=4.0, grid=(15, 15, 16), nbands=nb, seed=11 + k)
+               for k, nb in enumerate((40, 200, 20, 65))]
+    b = sgo.Batch(len(systems), precision=sgo.SGO_FP64)
+    for x in systems:
+        b.add_system(x)
+    e, f, st = b.scf(sgo.default_opts(use_graph=graph, **gate))
+    for i, x in enumerate(systems):
+        one = sgo.context_from_system(x, sgo.SGO_FP64)
+        one.scf(**gate)
+        say("%d bands: dE %.2e dF %.2e" % (x["nbands"], e[i] - one.energy()[0], np.abs(f[i] - one.forces()).max()))
+        assert abs(e[i] - one.energy()[0]) < 1e-7
+        assert np.abs(f[i] - one.forces()).max() < 1e-5
