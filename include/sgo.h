@@ -318,7 +318,8 @@ int sgo_subspace_solve_noalloc(int device, int n, int mode, const double* S, con
  * "SGO_SP_CHUNK" (stick pairs per block of the LDS z transforms, used by
  * FP64 and by lines longer than 64; the FP32 register z passes take 16),
  * "SGO_DENS_CHUNKS" (band-pair chunks of the density planes),
- * "SGO_RR_SWEEPS" (Jacobi sweeps of the intermediate subspace steps),
+ * "SGO_RR_SWEEPS" (Jacobi sweeps of the intermediate subspace steps; up to 198
+ * bands at most 40, what a full solve may take),
  * "SGO_PLANE_KERNEL" (FP32 plane transforms: 1 = register-resident line
  * FFTs, the default where every line length is 2^a 3^b 5^c <= 64;
  * 2 = staged line transforms in LDS, used for FP64 and longer lines),
